@@ -1,4 +1,5 @@
 """Build the gfx950 library ``libcrfinside.so`` in-tree with hipcc."""
+import concurrent.futures
 import os
 import re
 import subprocess
@@ -8,7 +9,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 SOURCES = [os.path.join(CSRC, "crf_kernels.hip"), os.path.join(CSRC, "crf_biaffine.hip"),
-           os.path.join(CSRC, "crf_plan.cpp")]
+           os.path.join(CSRC, "crf_tile.hip"), os.path.join(CSRC, "crf_plan.cpp")]
 LIB = os.path.join(PKG, "libcrfinside.so")
 # microbenchmarks of the ceilings behind the roofline (bench.py --ceilings)
 CEIL_SOURCES = [os.path.join(CSRC, "crf_ceilings.hip")]
@@ -69,25 +70,29 @@ def _write_resources(stderr_text, path):
 
 
 def _compile(sources, lib, verbose, resources=None):
-    tmp = lib + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-o", tmp, *sources]
+    """Compile the sources side by side (one object each), then link."""
+    flags = [f for f in FLAGS if f != "-shared"]
     if resources is not None:
-        cmd[1:1] = ["-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics"]
-    if verbose:
-        print(" ".join(cmd), file=sys.stderr)
-    if resources is None:
-        subprocess.run(cmd, check=True)
-    else:
-        r = subprocess.run(cmd, capture_output=True, text=True)
-        rest = "\n".join(ln for ln in r.stderr.splitlines() if "kernel-resource-usage" not in ln)
+        flags = ["-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics", *flags]
+    objs = [f"{lib}.{os.path.basename(src)}.o" for src in sources]
+    cmds = [[HIPCC, *flags, "-c", "-o", obj, src] for src, obj in zip(sources, objs)]
+    with concurrent.futures.ThreadPoolExecutor(len(cmds)) as pool:
+        runs = list(pool.map(lambda c: subprocess.run(c, capture_output=True, text=True), cmds))
+    for cmd, r in zip(cmds, runs):
+        if verbose:
+            print(" ".join(cmd), file=sys.stderr)
+        rest = "\n".join(ln for ln in (r.stderr + r.stdout).splitlines() if "kernel-resource-usage" not in ln)
         if rest.strip():
             print(rest, file=sys.stderr)
-        if r.stdout.strip():
-            print(r.stdout, file=sys.stderr)
         if r.returncode != 0:
             raise subprocess.CalledProcessError(r.returncode, cmd)
-        _write_resources(r.stderr, resources)
+    tmp = lib + ".tmp"
+    subprocess.run([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp, *objs], check=True)
+    if resources is not None:
+        _write_resources("\n".join(r.stderr for r in runs), resources)
     os.replace(tmp, lib)
+    for obj in objs:
+        os.remove(obj)
 
 
 def build(verbose: bool = False) -> str:

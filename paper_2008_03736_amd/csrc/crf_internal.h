@@ -413,6 +413,40 @@ struct Schedule {
     int32_t threads;             // workgroup size of the LDS kernels
 };
 
+// Tile charts (crf_tile.hip): sentences of up to kTileMaxLen words, in
+// bundles of equal block count m = n/4 + 1 (four fence posts a block).  A
+// record of tile_stride ints: kind (kKindInside or kKindCky), m, count S, the
+// pitch of a row of tiles (inside), div_magic(S), then S pairs (sentence id,
+// length).
+constexpr int kTileMaxLen = 139;      // 35 blocks: the longest whose two inside squares fit in one CU's LDS
+constexpr int kTileThreads = 256;      // two workgroups per CU
+constexpr int kTileThreadsMax = 512;  // one workgroup per CU (bundles past half the LDS)
+constexpr int kTileTabWords = 6;
+// An inside bundle's score rows in 16-byte pieces (tiles are walked in folded
+// rows of m + 1), of which a thread keeps at most kTilePieces.
+constexpr int kTilePieces = 6;
+__host__ __device__ inline int tile_pieces(int m, int S) { return (m + 1) / 2 * 4 * (m + 1) * S; }
+enum TileRec { kTrKind = 0, kTrM, kTrCount, kTrPitch, kTrMagic, kTrHeader };
+__host__ __device__ inline int tile_blocks(int n) { return n / 4 + 1; }
+// Pitch of a row of tiles, in tiles: S m, made even (a tile is half of the 32
+// banks, and lanes one block apart are pitch + S tiles apart: with an even
+// pitch eight consecutive lanes hit distinct banks).
+__host__ __device__ inline int tile_pitch(int m, int S) { return (m * S + 1) & ~1; }
+// LDS of an inside bundle: the squares P and Q, the per-block partials (16 and
+// 8 bytes), the forced sums and the per-sentence tables.
+__host__ __device__ inline int64_t tile_io_bytes(int m, int S, int pitch) {
+    return 128 * (int64_t)m * pitch + 24 * (int64_t)m * S + (8 + 4 * kTileTabWords) * (int64_t)S;
+}
+// LDS of a CKY bundle: 128 bytes of chart and 16 of block numbers per tile,
+// ids and lengths.
+__host__ __device__ inline int64_t tile_ck_bytes(int m, int S) {
+    return 144 * (int64_t)S * (m * (m + 1) / 2) + 8 * (int64_t)S;
+}
+struct TileSchedule {
+    const int32_t *recs;
+    int32_t n, lds_bytes;
+};
+
 // Device-side view of a plan, passed by value to every kernel.
 //   mix: the records of the fused inside + CKY kernel, sorted by predicted
 //   duration (both kinds merged); its fused_grid workgroups take them in
@@ -454,6 +488,10 @@ struct KernelPlan {
     // launcher; 1: a workgroup per sentence pass, no team area used).
     int32_t *team_area;
     int32_t team_cap, team_k;
+    // tile charts: the bundles of the inside calls, of CKY and of the fused
+    // launch (both merged, by predicted duration); n = 0 when the plan has none
+    TileSchedule tile_io, tile_ck, tile_mix;
+    int32_t tile_stride, tile_threads;
 };
 
 // Teams for workspace sentences: up to kTeamMaxK workgroups of one XCD run a
@@ -528,6 +566,17 @@ hipError_t launch_label_spans(const KernelPlan &p, const float *label_scores, in
 hipError_t launch_parse(const KernelPlan &p, const float *scores, const float *grad, float *logZ,
                         float *marg, int32_t *spans, float *best, hipStream_t stream);
 hipError_t set_kernel_attributes(int max_lds_bytes);
+// The same calls for the sentences in tile bundles (crf_tile.hip).
+hipError_t set_tile_attributes(int max_lds_bytes);
+hipError_t launch_tile_inside(const KernelPlan &p, const float *scores, const float *grad, float *logZ, float *marg,
+                              hipStream_t stream);
+hipError_t launch_tile_loss(const KernelPlan &p, const float *scores, const int32_t *gold, const float *grad,
+                            float *loss, float *grad_scores, hipStream_t stream);
+hipError_t launch_tile_cky(const KernelPlan &p, const float *scores, int32_t *spans, float *best, hipStream_t stream);
+hipError_t launch_tile_parse(const KernelPlan &p, const float *scores, const float *grad, float *logZ, float *marg,
+                             int32_t *spans, float *best, hipStream_t stream);
+hipError_t launch_tile_mbr(const KernelPlan &p, const float *scores, float *logZ, float *marg, int32_t *spans,
+                           float *best, hipStream_t stream);
 // The biaffine scorer (crf_biaffine.hip): dynamic LDS per workgroup for d,
 // and the launch over the plan's tiles and L labels.
 int64_t biaffine_lds_bytes(int d);

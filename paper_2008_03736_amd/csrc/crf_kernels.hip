@@ -2103,6 +2103,8 @@ hipError_t set_kernel_attributes(int max_lds_bytes) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds_bytes);
         if (e != hipSuccess) return e;
     }
+    const hipError_t et = set_tile_attributes(max_lds_bytes);
+    if (et != hipSuccess) return et;
     // the label reduction's staging at the most labels a plan accepts
     return hipFuncSetAttribute((const void *)label_reduce_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)(kLabelWaves * (kLabelRowChunk + CRF_MAX_LABELS) * sizeof(float)));
@@ -2136,7 +2138,9 @@ static hipError_t launch_inside_sweeps(const KernelPlan &p, const float *scores,
                                        float *marg, hipStream_t stream) {
     const Schedule &q = p.inside;
     hipError_t e;
-    if (q.n_bundles > 0) {
+    if (!LAB && p.tile_io.n > 0) {
+        if ((e = launch_tile_inside(p, scores, grad, logZ, marg, stream)) != hipSuccess) return e;
+    } else if (q.n_bundles > 0) {
         launch_inside_k<false, LAB>(p, dim3(q.n_bundles), q.threads, q.lds_bytes, stream, scores, grad, logZ, marg);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -2189,7 +2193,9 @@ static hipError_t launch_cky_k(const KernelPlan &p, const float *scores, int32_t
                                hipStream_t stream, int32_t *labels) {
     const Schedule &q = p.cky;
     hipError_t e;
-    if (q.n_bundles > 0) {
+    if (!LAB && p.tile_ck.n > 0) {
+        if ((e = launch_tile_cky(p, scores, spans, best, stream)) != hipSuccess) return e;
+    } else if (q.n_bundles > 0) {
         hipLaunchKernelGGL((cky_kernel<false, LAB>), dim3(q.n_bundles), dim3(q.threads), (size_t)q.lds_bytes, stream, p,
                            scores, spans, best, labels);
         if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -2216,16 +2222,21 @@ hipError_t launch_cky(const KernelPlan &p, const float *scores, int32_t *spans, 
 
 hipError_t launch_mbr(const KernelPlan &p, const float *scores, float *logZ, float *marg, int32_t *spans,
                       float *best, hipStream_t stream) {
-    if (p.mbr == nullptr || p.counter == nullptr || p.mbr_grid < 1) {
+    if (p.tile_io.n == 0 && (p.mbr == nullptr || p.counter == nullptr || p.mbr_grid < 1)) {
         // separate launches, in stream order: inside + marginals, then CKY
         // over the marginals
         hipError_t e = launch_inside(p, scores, nullptr, logZ, marg, stream);
         if (e != hipSuccess) return e;
         return launch_cky(p, marg, spans, best, stream);
     }
-    hipLaunchKernelGGL(mbr_kernel, dim3(p.mbr_grid), dim3(p.inside.threads), (size_t)p.mbr_lds, stream, p, scores,
-                       logZ, marg, spans, best);
-    hipError_t e = hipGetLastError();
+    hipError_t e;
+    if (p.tile_io.n > 0) {
+        e = launch_tile_mbr(p, scores, logZ, marg, spans, best, stream);
+    } else {
+        hipLaunchKernelGGL(mbr_kernel, dim3(p.mbr_grid), dim3(p.inside.threads), (size_t)p.mbr_lds, stream, p, scores,
+                           logZ, marg, spans, best);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess) return e;
     // sentences too long for LDS (the plan has checked that the inside and
     // CKY workspace lists hold the same sentences): their marginals, then
@@ -2252,7 +2263,9 @@ hipError_t launch_loss(const KernelPlan &p, const float *scores, const int32_t *
                        float *loss, float *grad_scores, hipStream_t stream) {
     const Schedule &q = p.inside;
     hipError_t e;
-    if (q.n_bundles > 0) {
+    if (p.tile_io.n > 0) {
+        if ((e = launch_tile_loss(p, scores, gold, grad, loss, grad_scores, stream)) != hipSuccess) return e;
+    } else if (q.n_bundles > 0) {
         hipLaunchKernelGGL((loss_kernel<false>), dim3(q.n_bundles), dim3(q.threads), (size_t)q.lds_bytes, stream, p,
                            scores, gold, grad, loss, grad_scores);
         if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -2285,7 +2298,9 @@ hipError_t launch_parse(const KernelPlan &p, const float *scores, const float *g
                         float *marg, int32_t *spans, float *best, hipStream_t stream) {
     const Schedule &qi = p.inside, &qc = p.cky;
     hipError_t e;
-    if (p.mix != nullptr && p.counter != nullptr && p.fused_grid >= 1 && p.n_mix == qi.n_bundles + qc.n_bundles) {
+    if (p.tile_mix.n > 0) {
+        if ((e = launch_tile_parse(p, scores, grad, logZ, marg, spans, best, stream)) != hipSuccess) return e;
+    } else if (p.mix != nullptr && p.counter != nullptr && p.fused_grid >= 1 && p.n_mix == qi.n_bundles + qc.n_bundles) {
         const size_t lds = (size_t)(qi.lds_bytes > qc.lds_bytes ? qi.lds_bytes : qc.lds_bytes);
         hipLaunchKernelGGL(parse_kernel, dim3(p.fused_grid), dim3(qi.threads), lds, stream, p,
                            scores, grad, logZ, marg, spans, best);

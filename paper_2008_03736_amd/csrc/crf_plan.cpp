@@ -304,6 +304,49 @@ HostSchedule make_schedule(const std::vector<int32_t> &order, const int32_t *len
     return s;
 }
 
+// Tile bundles (crf_tile.hip): `order` by decreasing length, sentences of
+// equal block count together.  A bundle's work is its tiles over the stages;
+// it is aimed at the batch's share per slot, within the LDS budget, one tile
+// per lane and the pieces of score rows its threads load together.
+struct TileBundle {
+    int32_t first, count, m;
+    double us;   // predicted duration
+};
+struct TileHost {
+    std::vector<TileBundle> bundles;
+    int32_t lds_bytes = 0;
+};
+template <typename BB, typename US>
+TileHost make_tile_schedule(const std::vector<int32_t> &order, const int32_t *len, int64_t budget, int slots,
+                            int threads, BB &&bytes, US &&predict) {
+    TileHost t;
+    auto work = [](int m) { return (double)m * m * (250.0 + 38.0 * m); };
+    double total = 0.0;
+    for (int32_t b : order) total += work(crf::tile_blocks(len[b]));
+    const double target = total / slots;
+    for (size_t a = 0; a < order.size();) {
+        const int m = crf::tile_blocks(len[order[a]]);
+        size_t e = a;
+        while (e < order.size() && crf::tile_blocks(len[order[e]]) == m) ++e;
+        const int count = (int)(e - a);
+        int fit = 1;
+        while (fit < threads / m && bytes(m, fit + 1) <= budget &&
+               crf::tile_pieces(m, fit + 1) <= crf::kTilePieces * threads)
+            ++fit;
+        const int per = std::min(fit, std::max(1, (int)(target / work(m))));
+        const int nb = (count + per - 1) / per;
+        for (int q = 0; q < nb; ++q) {
+            const int lo = (int)((int64_t)count * q / nb), hi = (int)((int64_t)count * (q + 1) / nb);
+            t.bundles.push_back({(int32_t)(a + lo), hi - lo, m, predict(m, hi - lo)});
+            t.lds_bytes = std::max<int32_t>(t.lds_bytes, (int32_t)bytes(m, hi - lo));
+        }
+        a = e;
+    }
+    std::stable_sort(t.bundles.begin(), t.bundles.end(),
+                     [](const TileBundle &x, const TileBundle &y) { return x.us > y.us; });
+    return t;
+}
+
 }  // namespace
 
 extern "C" {
@@ -613,6 +656,80 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
     fill(kp.inside, si);
     fill(kp.cky, sc);
 
+    // Tile bundles: unlabelled plans whose LDS sentences all fit in tiles.
+    std::vector<int32_t> tile_recs;
+    TileHost tio, tck;
+    kp.tile_io = kp.tile_ck = kp.tile_mix = crf::TileSchedule{};
+    kp.tile_threads = crf::kTileThreads;
+    {
+        std::vector<int32_t> tile_order;
+        bool fit = num_labels == 1 && !force;
+        for (int32_t b : order) {
+            const int n = lengths_host[b];
+            if (n > crf::kMaxLenInLds) continue;
+            fit = fit && n <= crf::kTileMaxLen;
+            tile_order.push_back(b);
+        }
+        if (fit && !tile_order.empty()) {
+            const int m_max = crf::tile_blocks(lengths_host[tile_order[0]]);
+            // A pitch of m for a lone sentence of 25 blocks (96..99 words): made
+            // even, its two squares would no longer fit in half a CU.
+            auto pitch = [=](int m, int S) {
+                const int ev = crf::tile_pitch(m, S);
+                return S == 1 && crf::tile_io_bytes(m, 1, ev) > half_cu && crf::tile_io_bytes(m, 1, m) <= half_cu ? m : ev;
+            };
+            auto io_bytes = [=](int m, int S) { return crf::tile_io_bytes(m, S, pitch(m, S)); };
+            const bool small = io_bytes(m_max, 1) <= half_cu;
+            const int64_t budget = small ? half_cu : full_cu;
+            kp.tile_threads = small ? crf::kTileThreads : crf::kTileThreadsMax;
+            // Full bundles: a stage costs about the same whatever share of its
+            // lanes hold tiles.  Work per bundle aimed at 1/205 of the batch's
+            // (of 512 slots), which LDS caps first on large batches: the
+            // 5,000-sentence mixed batch fused 85.0 us at one share per slot,
+            // 72.6 here, 72.9 at half or a fifth of the slots, 123 at twice.
+            const int slots = small ? 205 : 102;
+            tio = make_tile_schedule(tile_order, lengths_host, budget, slots, kp.tile_threads, io_bytes,
+                                     [](int m, int S) { return (m + 1) * (1.0 + 0.004 * m * S); });
+            tck = make_tile_schedule(tile_order, lengths_host, budget, slots, kp.tile_threads,
+                                     [](int m, int S) { return crf::tile_ck_bytes(m, S); },
+                                     [](int m, int S) { return m * (1.5 + 0.005 * m * S); });
+            int most = 1;
+            for (const TileBundle &b : tio.bundles) most = std::max(most, (int)b.count);
+            for (const TileBundle &b : tck.bundles) most = std::max(most, (int)b.count);
+            kp.tile_stride = crf::kTrHeader + 2 * most;
+            auto put = [&](const TileBundle &b, int kind) {
+                const size_t at = tile_recs.size();
+                tile_recs.resize(at + kp.tile_stride, 0);
+                int32_t *q = tile_recs.data() + at;
+                q[crf::kTrKind] = kind;
+                q[crf::kTrM] = b.m;
+                q[crf::kTrCount] = b.count;
+                q[crf::kTrPitch] = pitch(b.m, b.count);
+                q[crf::kTrMagic] = (int32_t)crf::div_magic(b.count);
+                for (int t = 0; t < b.count; ++t) {
+                    const int32_t id = tile_order[b.first + t];
+                    q[crf::kTrHeader + 2 * t] = id;
+                    q[crf::kTrHeader + 2 * t + 1] = lengths_host[id];
+                }
+            };
+            for (const TileBundle &b : tio.bundles) put(b, crf::kKindInside);
+            for (const TileBundle &b : tck.bundles) put(b, crf::kKindCky);
+            size_t x = 0, y = 0;   // merged, longest predicted first
+            while (x < tio.bundles.size() || y < tck.bundles.size()) {
+                if (y == tck.bundles.size() || (x < tio.bundles.size() && tio.bundles[x].us >= tck.bundles[y].us))
+                    put(tio.bundles[x++], crf::kKindInside);
+                else
+                    put(tck.bundles[y++], crf::kKindCky);
+            }
+            kp.tile_io.n = (int32_t)tio.bundles.size();
+            kp.tile_io.lds_bytes = tio.lds_bytes;
+            kp.tile_ck.n = (int32_t)tck.bundles.size();
+            kp.tile_ck.lds_bytes = tck.lds_bytes;
+            kp.tile_mix.n = kp.tile_io.n + kp.tile_ck.n;
+            kp.tile_mix.lds_bytes = std::max(tio.lds_bytes, tck.lds_bytes);
+        }
+    }
+
     if ((e = upload(p, len, &kp.len)) != hipSuccess ||
         (e = upload(p, rec_in, &kp.inside.recs)) != hipSuccess ||
         (e = upload(p, si.spill, &kp.inside.order_spill)) != hipSuccess ||
@@ -623,12 +740,17 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
         (e = upload(p, rec_mix, &kp.mix)) != hipSuccess ||
         (e = upload(p, rec_mbr, &kp.mbr)) != hipSuccess ||
         (e = upload(p, lab_rows, &kp.lab_rows)) != hipSuccess ||
-        (e = upload(p, bia, &kp.bia_tiles)) != hipSuccess) {
+        (e = upload(p, bia, &kp.bia_tiles)) != hipSuccess ||
+        (e = upload(p, tile_recs, &kp.tile_io.recs)) != hipSuccess) {
         const int code = (e == hipErrorOutOfMemory) ? CRF_ENOMEM : CRF_EHIP;
         release(p);
         delete p;
         return code == CRF_ENOMEM ? fail(code, "device allocation of the schedule failed")
                                   : hip_fail(e, "schedule upload");
+    }
+    if (kp.tile_io.n > 0) {
+        kp.tile_ck.recs = kp.tile_io.recs + (size_t)kp.tile_io.n * kp.tile_stride;
+        kp.tile_mix.recs = kp.tile_ck.recs + (size_t)kp.tile_ck.n * kp.tile_stride;
     }
     kp.counter = nullptr;
     if (kp.fused_grid > 0 || kp.mbr_grid > 0) {
@@ -676,7 +798,7 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
     }
     // Best effort: ROCm launches with any dynamic LDS up to the per-block
     // limit without this attribute; a real shortfall surfaces as a launch error.
-    if (crf::set_kernel_attributes(std::max(std::max(si.lds_bytes, sc.lds_bytes), kp.mbr_lds)) != hipSuccess)
+    if (crf::set_kernel_attributes(std::max(std::max(std::max(si.lds_bytes, sc.lds_bytes), kp.mbr_lds), kp.tile_mix.lds_bytes)) != hipSuccess)
         (void)hipGetLastError();
     if (crf::set_biaffine_attributes() != hipSuccess) (void)hipGetLastError();
     // Resolve this device's scratch address for the no-allocation entry

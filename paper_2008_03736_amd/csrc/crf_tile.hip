@@ -1,0 +1,1366 @@
+// crf_tile.hip -- the chart recursions in 4 x 4 tiles of spans.
+//
+// The same recursions as crf_kernels.hip (inside with the outside beside it,
+// and CKY), for sentences whose charts fit in LDS, organised so that a step
+// advances four span widths at once and a lane owns a whole tile of spans.
+//
+// Fence posts are cut into m = n/4 + 1 blocks of four; tile (I,J), I <= J,
+// holds the spans from a post of block I to a post of block J.  Stage t
+// finishes the inside of every tile of tile diagonal D = J - I = t and the
+// outside of every tile of diagonal m - t: m + 1 stages and barriers where a
+// step per width takes n - 1.  A lane takes one tile (or G = 2 .. 16 lanes
+// share one, each with every G-th product, when a stage has few tiles):
+//   - the splits in the blocks strictly between (inside) or outside I..J
+//     (outside) are t - 1 products of two finished 4 x 4 tiles, 64 FMAs on
+//     eight 16-byte LDS reads each, the same count for every lane of a stage;
+//   - the splits inside blocks I and J, the only ones whose other part lies
+//     in the tile itself, are 48 further terms in the lane's registers.
+// Nothing is decoded per span, no lane reduces for a span (but for G > 1),
+// and the serial chain of a stage is one lane's 7-deep chain over its tile.
+//
+// Storage (float32).  Two m x m squares of tiles per sentence, P and Q:
+//   P[I][J], I <= J: alpha        P[J][I], I < J: O' transposed
+//   Q[I][J], I <= J: O'           Q[J][I], I < J: alpha transposed
+// (O' the outside score plus the span's own score, as in crf_kernels.hip).
+// Every product is then acc[r][c] += X[k][r] Y[k][c] over the rows k of two
+// tiles in one row of tiles K: inside X = Q[K][I], Y = P[K][J], I < K < J;
+// outside X = P[K][I], Y = Q[K][J], K < I or K > J.  Until a tile is finished
+// P[I][J] and Q[I][J] both hold its scores.
+//
+// A bundle's S sentences (equal m, any lengths) interleave sentence-minor:
+// tile (K,J) of sentence sb is slot K*rp + J*S + sb, 64 bytes, its row k at
+// 16-byte piece (k + (K*S + sb)/2) mod 4.  Consecutive lanes take consecutive
+// f = I*S + sb, so eight lanes' pieces cover the 32 banks (rp even); X and Y
+// of a product share K and sb, hence the rotation: the sum over k does not
+// mind in which order a lane meets its rows, and piece p of both tiles is a
+// constant offset.
+//
+// What bounds it: latency, in a stage's chain of address arithmetic, one LDS
+// round trip, the products (a wavefront issues an independent vector
+// instruction every 5 to 6 cycles, a dependent one every 9), the lanes'
+// combining, the finish and the barrier: about 3,000 cycles a stage where a
+// width step took 2,000, for four widths; not LDS (conflict-free but for the
+// shared tiles' lanes) and not HBM.  Measured against the one-width-a-step
+// kernels (us): 5,000 mixed sentences fused 96.5 -> 70.8, 2,000 longer ones
+// 130.5 -> 112.9, MBR of 1,700 134.5 -> 114.0, gold loss of 200 39.4 -> 33.6,
+// 32 short ones fused 26.7 -> 23.0, CKY of one sentence of 23 words 14.8 ->
+// 13.0.  Tried and dropped: 512 threads at 128 registers instead of 256 at 256
+// (mixed 72.6 -> 82.8, longer 113 -> 134), a second register buffer for the
+// next product's tiles (mixed 70.8 -> 72.6).
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "crf_internal.h"
+
+namespace crf {
+namespace {
+
+constexpr float LOG2E_F = 1.4426950408889634f;
+constexpr double LN2_D = 0.69314718055994530942;
+// "No split" and the score of a cell that is no span: far below any chart
+// value, and finite, so that sums and differences of two stay finite.
+constexpr float NEG = -1.0e30f;
+// Linear-domain range (see inside_block_impl): a larger value, or a root
+// outside [2^-100, 2^100], sends the bundle to the log domain.  So does a sum
+// over a span's splits below 2^-100 that is not zero (looked at on a quarter
+// of the spans, the tiles' diagonals): the scores then spread so far that
+// other sums have lost their digits, or themselves, to underflow.  (Zero is
+// what spans get whose every tree holds a near-forbidden score.)
+constexpr uint32_t kLinLowBits = 0x0D800000u;   // 2^-100
+constexpr uint32_t kLinMaxBits = 0x71800000u;   // 2^100; infinities and NaN compare above it
+constexpr float kLinMin = 0x1p-100f, kLinMax = 0x1p+100f;
+constexpr int kGoldMark = 0x7FBADBAD;           // a NaN bit pattern: no finite chart value has it
+
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
+// log2 of a positive normal float: the exact exponent plus the float32 log2
+// of the mantissa.
+__device__ __forceinline__ double log2_split(float x) {
+    return (double)__builtin_amdgcn_frexp_expf(x) + (double)fast_log2(__builtin_amdgcn_frexp_mantf(x));
+}
+// a / d for 0 <= a < 2^24, inv = 1.0f / d.
+__device__ __forceinline__ int div_small(int a, int d, float inv) {
+    int q = (int)((float)a * inv);
+    q += ((q + 1) * d <= a) ? 1 : 0;
+    q -= (q * d > a) ? 1 : 0;
+    return q;
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_i(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+    return __builtin_bit_cast(float, dpp_i<CTRL>(__builtin_bit_cast(int, v)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const int lo = dpp_i<CTRL>((int)(uint32_t)u), hi = dpp_i<CTRL>((int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
+}
+// row_ror:n inside each 16-lane row.  Lanes sharing a tile are the ones whose
+// lane numbers differ in the top lg bits of the low four, so rotations by 8,
+// 4, 2, 1 in that order leave the combined value in all of them.
+constexpr int kRor8 = 0x128, kRor4 = 0x124, kRor2 = 0x122, kRor1 = 0x121;
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+// a 16-byte access to global memory that is only 4-byte aligned
+typedef f4 f4u __attribute__((aligned(4)));
+
+struct Tile {
+    float v[4][4];
+};
+
+__device__ __forceinline__ f4 ld4(const char *sm, int off) { return *reinterpret_cast<const f4 *>(sm + off); }
+__device__ __forceinline__ void st4(char *sm, int off, f4 v) { *reinterpret_cast<f4 *>(sm + off) = v; }
+
+// ---------------------------------------------------------------------------
+// The two domains.  LIN: the chart holds exp2 of the shifted, log2-scaled
+// values, sums are sums.  Otherwise it holds those values, and sums are
+// pairwise log-sum-exps (only bundles that leave float32's range come here).
+template <bool LIN>
+struct Dom {
+    static constexpr float zero = LIN ? 0.f : NEG, one = LIN ? 1.f : 0.f;
+    __device__ static __forceinline__ float add(float a, float b) {
+        if constexpr (LIN) return a + b;
+        const float m = __builtin_fmaxf(a, b);
+        return m + fast_log2(fast_exp2(a - m) + fast_exp2(b - m));
+    }
+    __device__ static __forceinline__ float fma(float u, float x, float t) {
+        if constexpr (LIN) return __builtin_fmaf(u, x, t);
+        return add(t, u + x);
+    }
+    __device__ static __forceinline__ float mul(float a, float b) {
+        if constexpr (LIN) return a * b;
+        return a + b;
+    }
+    // own term of a span: its natural-unit score and its sentence's shift
+    __device__ static __forceinline__ float own(float s, float d) {
+        const float x = __builtin_fmaf(s, LOG2E_F, d);
+        if constexpr (LIN) return fast_exp2(x);
+        return x;
+    }
+    __device__ static __forceinline__ float log2(float x) {
+        if constexpr (LIN) return fast_log2(x);
+        return x;
+    }
+    // acc[r][c] += sum_k x[k][r] y[k][c]
+    __device__ static __forceinline__ void product(Tile &acc, const f4 (&x)[4], const f4 (&y)[4]) {
+        if constexpr (LIN) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) acc.v[r][c] = __builtin_fmaf(x[k][r], y[k][c], acc.v[r][c]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float m = acc.v[r][c];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) m = __builtin_fmaxf(m, x[k][r] + y[k][c]);
+                    float s = fast_exp2(acc.v[r][c] - m);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) s += fast_exp2(x[k][r] + y[k][c] - m);
+                    acc.v[r][c] = m + fast_log2(s);
+                }
+        }
+    }
+    template <int CTRL>
+    __device__ static __forceinline__ void combine(Tile &acc) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc.v[r][c] = add(acc.v[r][c], dpp_f<CTRL>(acc.v[r][c]));
+    }
+};
+
+// A bundle's charts and tables (byte offsets into the workgroup's LDS).
+struct Io_ctx {
+    int m, S, rpb, qo;   // blocks, sentences, bytes per row of tiles, offset of Q
+    uint32_t mag;        // div_magic(S)
+    int part, partd, forced, tab;
+    __device__ __forceinline__ int rot(int g) const { return (g >> 1) & 3; }
+};
+__device__ __forceinline__ Io_ctx io_ctx(const int32_t *rec) {
+    Io_ctx c;
+    c.m = rec[kTrM];
+    c.S = rec[kTrCount];
+    c.rpb = rec[kTrPitch] * 64;
+    c.mag = (uint32_t)rec[kTrMagic];
+    c.qo = c.m * c.rpb;
+    c.part = 2 * c.qo;
+    c.partd = c.part + 16 * c.m * c.S;
+    c.forced = c.partd + 8 * c.m * c.S;
+    c.tab = c.forced + 8 * c.S;
+    return c;
+}
+// per-sentence tables: word `which` of sentence sb
+enum { kTabD = 0, kTabDl, kTabG, kTabLz, kTabId, kTabN, kTabWords };
+template <typename T>
+__device__ __forceinline__ T &tab(char *sm, const Io_ctx &c, int which, int sb) {
+    return *reinterpret_cast<T *>(sm + c.tab + 4 * (which * c.S + sb));
+}
+static_assert(kTabWords == kTileTabWords, "tile_io_bytes counts the tables");
+
+// Hides a value from the optimiser: what follows from it is computed where it
+// is used, not hoisted out of the stage loops into registers that spill.
+__device__ __forceinline__ int here(int v) {   // a uniform value
+    asm volatile("" : "+s"(v));
+    return v;
+}
+__device__ __forceinline__ int here_lane(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+__device__ __forceinline__ int this_thread() { return here_lane((int)threadIdx.x); }
+
+// Which tile and which share of its products a lane of wavefront task w takes
+// with 2^lg lanes per tile.
+struct Lane_share {
+    int f, q;
+};
+__device__ __forceinline__ Lane_share lane_share(int w, int lg) {
+    const int l = this_thread() & 63, low = l & 15;
+    return Lane_share{(w * (64 >> lg)) + (low & ((16 >> lg) - 1)) + ((l >> 4) << (4 - lg)), low >> (4 - lg)};
+}
+
+// Lanes per tile of a stage whose tiles take np products each: as many as
+// the workgroup's wavefronts hold without a second pass (most: the lg at which
+// the bundle's m S tiles, of both kinds together, fill them), while a lane's
+// saved products (about 70 issue slots each) outweigh the combining levels
+// (16 each).
+__device__ __forceinline__ int stage_lg(int np, int cin, int cout, int nw, int most) {
+    int lg = min(np >= 12 ? 4 : np >= 6 ? 3 : np >= 3 ? 2 : np >> 1, most);
+    // (the two kinds start on wavefronts of their own)
+    return lg > 0 && (((cin << lg) + 63) >> 6) + (((cout << lg) + 63) >> 6) > nw ? lg - 1 : lg;
+}
+__device__ __forceinline__ int lanes_lg(int tiles, int nw) {
+    const int room = 64 * nw / tiles;
+    return room >= 16 ? 4 : room >= 8 ? 3 : room >= 4 ? 2 : room >= 2 ? 1 : 0;
+}
+
+// The spans of two and three words of a diagonal tile of P (the others it
+// holds are words, whose value is one): exactly the words read, so that no
+// load waits for an unused register.
+struct Diag3 {
+    float d02, d03, d13;
+};
+__device__ __forceinline__ Diag3 diag3(const char *sm, int at, int rot) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 a = *reinterpret_cast<const f2 *>(sm + at + (rot << 4) + 8);
+    return Diag3{a[0], a[1], *reinterpret_cast<const float *>(sm + at + (((1 + rot) & 3) << 4) + 12)};
+}
+
+// The inside of a tile from its products, its own terms and the diagonal
+// tiles of its blocks: x[r][c] = e[r][c] (acc[r][c] + the splits inside the
+// blocks); sum: the bracket on the tile's diagonal.  word: the tile's lower
+// left span is a word (diagonal 1).
+template <bool LIN>
+__device__ __forceinline__ void finish_inside(Tile &x, float (&sum)[4], const Tile &acc, const Tile &e, const Diag3 &U,
+                                              const Diag3 &V, bool word) {
+    typedef Dom<LIN> Dm;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int r = 3; r >= 0; --r) {
+            float t = acc.v[r][c];
+            if (r < 3) t = Dm::add(t, x.v[r + 1][c]);
+            if (r < 2) t = Dm::fma(r == 0 ? U.d02 : U.d13, x.v[r + 2][c], t);
+            if (r < 1) t = Dm::fma(U.d03, x.v[3][c], t);
+            if (c > 0) t = Dm::add(t, x.v[r][c - 1]);
+            if (c > 1) t = Dm::fma(c == 2 ? V.d02 : V.d13, x.v[r][c - 2], t);
+            if (c > 2) t = Dm::fma(V.d03, x.v[r][0], t);
+            if (r == c) sum[r] = t;
+            x.v[r][c] = Dm::mul(e.v[r][c], t);
+            if (r == 3 && c == 0) x.v[3][0] = word ? Dm::one : x.v[3][0];   // a word
+        }
+}
+
+// One wavefront's share of a stage's tiles of one kind: inside of diagonal
+// D (OUT = false) or outside of diagonal D; D >= 1 for the inside (diagonal 0
+// is inside_diagonal).  cnt tiles, np products each.
+template <bool LIN, bool OUT>
+__device__ __forceinline__ void tile_task(const Io_ctx &cx, char *sm, int D, int np, int cnt, int w, int lg, int *ovf) {
+    typedef Dom<LIN> Dm;
+    const int m = cx.m, S = cx.S;
+    const Lane_share ls = lane_share(here(w), here(lg));
+    const bool act = ls.f < cnt && ls.q == 0;
+    const int f = here_lane(ls.f < cnt ? ls.f : cnt - 1);
+    const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * S, J = I + D;
+    const int gi = f, gj = f + D * S;   // I*S + sb, J*S + sb
+
+    // The tile's scores, its sentence's shift and the diagonal tiles of I
+    // and J (their spans of two and three words).
+    const int own_at = (OUT ? cx.qo : 0) + I * cx.rpb + gj * 64, ri = cx.rot(gi), rj = cx.rot(gj);
+    f4 raw[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) raw[r] = ld4(sm, own_at + (((r + ri) & 3) << 4));
+    const float d = tab<float>(sm, cx, kTabD, sb);
+    const Diag3 U = diag3(sm, I * cx.rpb + gi * 64, ri), V = diag3(sm, J * cx.rpb + gj * 64, rj);
+
+    // Products, the first one's tiles in flight while the own terms are taken.
+    const int bx = (OUT ? 0 : cx.qo) + gi * 64, by = (OUT ? cx.qo : 0) + gj * 64;
+    const int lim = m * cx.rpb, step = cx.rpb << lg, iters = (np + (1 << lg) - 1) >> lg;
+    int off = ((OUT ? J : I) + 1 + ls.q) * cx.rpb;
+    f4 x[4], y[4];
+    auto load = [&]() {   // (a lane past its last product reads some row of tiles)
+        const int o = off >= lim ? (OUT ? off - lim : 0) : off;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            x[k] = ld4(sm, bx + o + 16 * k);
+            y[k] = ld4(sm, by + o + 16 * k);
+        }
+        off += step;
+    };
+    if (iters > 0) load();
+    Tile acc, e;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            acc.v[r][c] = Dm::zero;
+            e.v[r][c] = Dm::own(raw[r][c], d);
+        }
+#pragma unroll 1
+    for (int it = 0; it < iters; ++it) {
+        if (it > 0) load();
+        if (ls.q + (it << lg) < np) Dm::product(acc, x, y);
+    }
+    if (lg >= 1) Dm::template combine<kRor8>(acc);
+    if (lg >= 2) Dm::template combine<kRor4>(acc);
+    if (lg >= 3) Dm::template combine<kRor2>(acc);
+    if (lg >= 4) Dm::template combine<kRor1>(acc);
+    if (D == m - 1) {   // the root (0, n): own term 1; outside score 1
+        const int rc = tab<int>(sm, cx, kTabN, sb) - 4 * (m - 1);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            e.v[0][c] = I == 0 && c == rc ? Dm::one : e.v[0][c];
+            if constexpr (OUT) acc.v[0][c] = I == 0 && c == rc ? Dm::one : acc.v[0][c];
+        }
+    }
+
+    Tile t;
+    if constexpr (!OUT) {
+        float sum[4];
+        finish_inside<LIN>(t, sum, acc, e, U, V, D == 1);
+        if constexpr (LIN) {   // (zero wraps round to the largest)
+            uint32_t low = 0xFFFFFFFFu;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) low = min(low, __builtin_bit_cast(uint32_t, sum[r]) - 1u);
+            if (low < kLinLowBits) *ovf = 1;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 3; c >= 0; --c) {
+                float v = acc.v[r][c];
+                if (r > 0) v = Dm::add(v, t.v[r - 1][c]);
+                if (r > 1) v = Dm::fma(r == 2 ? U.d02 : U.d13, t.v[r - 2][c], v);
+                if (r > 2) v = Dm::fma(U.d03, t.v[0][c], v);
+                if (c < 3) v = Dm::add(v, t.v[r][c + 1]);
+                if (c < 2) v = Dm::fma(c == 1 ? V.d13 : V.d02, t.v[r][c + 2], v);
+                if (c < 1) v = Dm::fma(V.d03, t.v[r][3], v);
+                t.v[r][c] = Dm::mul(e.v[r][c], v);
+                if (r == 3 && c == 0) t.v[3][0] = D == 1 ? Dm::zero : t.v[3][0];   // a word: no term of any product
+            }
+    }
+    if constexpr (LIN) {   // every value is >= 0, so the sum shows an infinity, a NaN or a value past the range
+        float s = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s += (t.v[r][0] + t.v[r][1]) + (t.v[r][2] + t.v[r][3]);
+        if (__builtin_bit_cast(uint32_t, s) > kLinMaxBits) *ovf = 1;
+    }
+    if (act) {
+        const int up = (OUT ? cx.qo : 0) + I * cx.rpb + gj * 64, lo = (OUT ? 0 : cx.qo) + J * cx.rpb + gi * 64;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            st4(sm, up + (((k + ri) & 3) << 4), f4{t.v[k][0], t.v[k][1], t.v[k][2], t.v[k][3]});
+            st4(sm, lo + (((k + rj) & 3) << 4), f4{t.v[0][k], t.v[1][k], t.v[2][k], t.v[3][k]});
+        }
+    }
+}
+
+// Inside of tile diagonal 0: the spans of up to three words inside a block.
+// A lane per tile.
+template <bool LIN>
+__device__ __forceinline__ void inside_diagonal(const Io_ctx &cx, char *sm, int *ovf) {
+    typedef Dom<LIN> Dm;
+    const int cnt = cx.m * cx.S;
+    for (int f = this_thread(); f < cnt; f += (int)blockDim.x) {
+        const int I = cx.S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * cx.S;
+        const int at = I * cx.rpb + f * 64, ri = cx.rot(f);
+        const f4 r0 = ld4(sm, at + (ri << 4)), r1 = ld4(sm, at + (((1 + ri) & 3) << 4));
+        const float d = tab<float>(sm, cx, kTabD, sb);
+        const int n = tab<int>(sm, cx, kTabN, sb);
+        float e02 = Dm::own(r0[2], d), e13 = Dm::own(r1[3], d), e03 = Dm::own(r0[3], d);
+        if (cx.m == 1) {   // the root is in this tile
+            e02 = n == 2 ? Dm::one : e02;
+            e03 = n == 3 ? Dm::one : e03;
+        }
+        const float x03 = Dm::mul(e03, Dm::add(e13, e02));
+        if constexpr (LIN)
+            if (__builtin_bit_cast(uint32_t, e02 + e13 + x03) > kLinMaxBits) *ovf = 1;
+        const float z = Dm::zero, o = Dm::one;
+        st4(sm, at + (ri << 4), f4{z, o, e02, x03});
+        st4(sm, at + (((1 + ri) & 3) << 4), f4{z, z, o, e13});
+        st4(sm, at + (((2 + ri) & 3) << 4), f4{z, z, z, o});
+        st4(sm, at + (((3 + ri) & 3) << 4), f4{z, z, z, z});
+    }
+}
+
+// Outside of tile diagonal 0 (stage m): the products run over every other
+// block, the finish over the three spans of two and three words.
+template <bool LIN>
+__device__ __forceinline__ void outside_diagonal(const Io_ctx &cx, char *sm, int w, int lg, int *ovf) {
+    typedef Dom<LIN> Dm;
+    const int m = cx.m, S = cx.S, cnt = m * S, np = m - 1;
+    const Lane_share ls = lane_share(w, lg);
+    const bool act = ls.f < cnt && ls.q == 0;
+    const int f = ls.f < cnt ? ls.f : cnt - 1;
+    const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * S;
+    const int at = cx.qo + I * cx.rpb + f * 64, ri = cx.rot(f);
+    const f4 r0 = ld4(sm, at + (ri << 4)), r1 = ld4(sm, at + (((1 + ri) & 3) << 4));
+    const float d = tab<float>(sm, cx, kTabD, sb);
+    const int n = tab<int>(sm, cx, kTabN, sb);
+    float a02 = Dm::zero, a13 = Dm::zero, a03 = Dm::zero;
+    const int bx = f * 64, by = cx.qo + f * 64, lim = m * cx.rpb, step = cx.rpb << lg;
+    int off = (I + 1 + ls.q) * cx.rpb;
+    typedef float f2 __attribute__((ext_vector_type(2)));
+#pragma unroll 2
+    for (int p = ls.q; p < np; p += 1 << lg) {
+        const int o = off >= lim ? off - lim : off;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {   // columns 0, 1 of X and 2, 3 of Y
+            const f2 x = *reinterpret_cast<const f2 *>(sm + bx + o + 16 * k);
+            const f2 y = *reinterpret_cast<const f2 *>(sm + by + o + 16 * k + 8);
+            a02 = Dm::fma(x[0], y[0], a02);
+            a13 = Dm::fma(x[1], y[1], a13);
+            a03 = Dm::fma(x[0], y[1], a03);
+        }
+        off += step;
+    }
+    auto combine = [&](float &a) {
+        if (lg >= 1) a = Dm::add(a, dpp_f<kRor8>(a));
+        if (lg >= 2) a = Dm::add(a, dpp_f<kRor4>(a));
+        if (lg >= 3) a = Dm::add(a, dpp_f<kRor2>(a));
+        if (lg >= 4) a = Dm::add(a, dpp_f<kRor1>(a));
+    };
+    combine(a02);
+    combine(a13);
+    combine(a03);
+    float e02 = Dm::own(r0[2], d), e13 = Dm::own(r1[3], d), e03 = Dm::own(r0[3], d);
+    if (m == 1) {
+        a02 = n == 2 ? Dm::one : a02;
+        e02 = n == 2 ? Dm::one : e02;
+        a03 = n == 3 ? Dm::one : a03;
+        e03 = n == 3 ? Dm::one : e03;
+    }
+    const float o03 = Dm::mul(e03, a03);
+    const float o02 = Dm::mul(e02, Dm::add(a02, o03)), o13 = Dm::mul(e13, Dm::add(a13, o03));
+    if constexpr (LIN)
+        if (__builtin_bit_cast(uint32_t, o02 + o13 + o03) > kLinMaxBits) *ovf = 1;
+    if (act) {
+        st4(sm, at + (ri << 4), f4{Dm::zero, Dm::zero, o02, o03});
+        st4(sm, at + (((1 + ri) & 3) << 4), f4{Dm::zero, Dm::zero, Dm::zero, o13});
+    }
+}
+
+// Stages after which the chart is rescaled, the first >= lo, or 0.  The seed
+// (tile_seed) comes from the scores alone; sentences of fewer than 44 words
+// stay in range on it.  The log domain, which never leaves the range, rescales
+// once, a quarter of the way, to keep the values and so their rounding small.
+template <bool LIN>
+__device__ __forceinline__ int tile_rescale_after(int lo, int m) {
+    if (!LIN) return m >= 5 && m / 4 >= lo ? m / 4 : 0;
+    if (m >= 12 && lo <= 4) return 4;
+    if (m > 24 && m / 2 >= lo) return m / 2;
+    return 0;
+}
+
+// Sums over the 16 lanes of a row, left in all of them.
+__device__ __forceinline__ float row_sum(float v) {
+    v += dpp_f<kRor8>(v);
+    v += dpp_f<kRor4>(v);
+    v += dpp_f<kRor2>(v);
+    return v + dpp_f<kRor1>(v);
+}
+__device__ __forceinline__ float row_max(float v) {
+    v = __builtin_fmaxf(v, dpp_f<kRor8>(v));
+    v = __builtin_fmaxf(v, dpp_f<kRor4>(v));
+    v = __builtin_fmaxf(v, dpp_f<kRor2>(v));
+    return __builtin_fmaxf(v, dpp_f<kRor1>(v));
+}
+__device__ __forceinline__ double row_sum(double v) {
+    v += dpp_d<kRor8>(v);
+    v += dpp_d<kRor4>(v);
+    v += dpp_d<kRor2>(v);
+    return v + dpp_d<kRor1>(v);
+}
+
+// Growth of log2 alpha per node over a tile's spans (diagonal D >= 1): the
+// largest, the sum and the number of log2(x) / (w-1), spans of no value left
+// out.
+struct Growth {
+    float mx = NEG, sum = 0.f, cnt = 0.f;
+};
+template <bool LIN>
+__device__ __forceinline__ Growth tile_growth(const Tile &x, int D) {
+    Growth g;
+#pragma unroll
+    for (int j = -3; j <= 3; ++j) {
+        const int w = 4 * D + j;
+        const float inv = __builtin_amdgcn_rcpf((float)(w > 1 ? w - 1 : 1));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = r + j;
+            if (c < 0 || c > 3) continue;
+            const float v = Dom<LIN>::log2(x.v[r][c]) * inv;
+            const bool in = v > -200.f && v < 200.f && w >= 2;
+            g.mx = in ? __builtin_fmaxf(g.mx, v) : g.mx;
+            g.sum += in ? v : 0.f;
+            g.cnt += in ? 1.f : 0.f;
+        }
+    }
+    return g;
+}
+// The shift that a sentence's growth partials (part[I*S + sb], I < blocks)
+// call for: linear domain, minus the midpoint of the mean and the largest,
+// which keeps the largest values further from float32's limit; log domain,
+// minus the mean.  Left in table `which`; add: on top of what it holds.
+template <bool LIN>
+__device__ __forceinline__ void growth_shift(const Io_ctx &cx, char *sm, int blocks, int which) {
+    const int gl = this_thread() & 15, S = cx.S;
+    for (int sb = this_thread() >> 4; sb < S; sb += (int)blockDim.x >> 4) {
+        float mx = NEG, sum = 0.f, c = 0.f;
+        for (int I = gl; I < blocks; I += 16) {
+            const f4 p = ld4(sm, cx.part + 16 * (I * S + sb));
+            mx = __builtin_fmaxf(mx, p[0]);
+            sum += p[1];
+            c += p[2];
+        }
+        mx = row_max(mx);
+        sum = row_sum(sum);
+        c = row_sum(c);
+        if (gl == 0)
+            tab<float>(sm, cx, which, sb) = c > 0.f ? (LIN ? -0.5f * (mx + sum / c) : -sum / c) : 0.f;
+    }
+}
+
+// Score shift (see rescale_chart in crf_kernels.hip): after stage t0 the
+// growth per node of each sentence is estimated from its tiles of diagonal
+// t0, and the finished values move to the problem with every non-forced score
+// shifted by delta.
+template <bool LIN, bool REV>
+__device__ void tile_rescale(const Io_ctx &cx, char *sm, int t0) {
+    typedef Dom<LIN> Dm;
+    const int m = cx.m, S = cx.S, tid = this_thread(), NT = (int)blockDim.x;
+    for (int f = tid; f < (m - t0) * S; f += NT) {
+        const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, at = I * cx.rpb + (f + t0 * S) * 64, rt = cx.rot(f);
+        Tile x;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const f4 v = ld4(sm, at + (((r + rt) & 3) << 4));
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x.v[r][c] = v[c];
+        }
+        const Growth g = tile_growth<LIN>(x, t0);
+        st4(sm, cx.part + 16 * f, f4{g.mx, g.sum, g.cnt, 0.f});
+    }
+    __syncthreads();
+    growth_shift<LIN>(cx, sm, m - t0, kTabDl);
+    __syncthreads();
+    auto move_tile = [&](int at, int rt, int at2, int rt2, float dl, float base, float dir) {
+        // row r, column c of the tile at `at` moves by dl (base + dir (c - r)); copied transposed to at2
+        Tile x;
+        float fac[7];
+#pragma unroll
+        for (int j = 0; j < 7; ++j) {
+            const float k = dl * (base + dir * (float)(j - 3));
+            fac[j] = LIN ? fast_exp2(k) : k;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const f4 v = ld4(sm, at + (((r + rt) & 3) << 4));
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x.v[r][c] = Dm::mul(v[c], fac[c - r + 3]);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            st4(sm, at + (((k + rt) & 3) << 4), f4{x.v[k][0], x.v[k][1], x.v[k][2], x.v[k][3]});
+            if (at2 >= 0) st4(sm, at2 + (((k + rt2) & 3) << 4), f4{x.v[0][k], x.v[1][k], x.v[2][k], x.v[3][k]});
+        }
+    };
+    // a wavefront per tile diagonal
+    const int nw = NT >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    for (int D = wave; D <= t0; D += nw) {
+        const int cnt = (m - D) * S;
+        for (int f = lane; f < cnt; f += 64) {
+            const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * S, J = I + D, gj = f + D * S;
+            const float dl = tab<float>(sm, cx, kTabDl, sb);
+            move_tile(I * cx.rpb + gj * 64, cx.rot(f), D > 0 ? cx.qo + J * cx.rpb + f * 64 : -1, cx.rot(gj), dl,
+                      (float)(4 * D - 1), 1.f);
+        }
+    }
+    if constexpr (REV)
+        for (int D = m - t0 + wave; D < m; D += nw) {
+            const int cnt = (m - D) * S;
+            for (int f = lane; f < cnt; f += 64) {
+                const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * S, J = I + D, gj = f + D * S;
+                const float dl = tab<float>(sm, cx, kTabDl, sb);
+                const int n = tab<int>(sm, cx, kTabN, sb);
+                // (cells past the sentence hold zero; their factor may be anything finite)
+                move_tile(cx.qo + I * cx.rpb + gj * 64, cx.rot(f), J * cx.rpb + f * 64, cx.rot(gj), dl,
+                          (float)(n - 4 * D), -1.f);
+            }
+        }
+    for (int sb = tid; sb < S; sb += NT) tab<float>(sm, cx, kTabD, sb) += tab<float>(sm, cx, kTabDl, sb);
+    __syncthreads();
+}
+
+// Forced sums (float64) and the seed of each sentence's shift.  A node of a
+// tree adds about log2(4 mean(2^s)) to log2 alpha (four the growth of the
+// number of trees), the mean over the scores near it: block I's figure is
+// over the spans of tile (I,I+1), near-forbidden scores left out, words and
+// the root too; the sentence's shift takes away their mean.
+__device__ void tile_seed(const Io_ctx &cx, char *sm) {
+    const int m = cx.m, S = cx.S, tid = this_thread(), NT = (int)blockDim.x;
+    for (int f = tid; f < m * S; f += NT) {
+        const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * S;
+        const int n = tab<int>(sm, cx, kTabN, sb), ri = cx.rot(f), rc = n - 4 * (m - 1);
+        const int at = I * cx.rpb + f * 64, at1 = I + 1 < m ? at + S * 64 : at;   // tiles (I,I), (I,I+1)
+        f4 a[4], b[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            a[r] = ld4(sm, at + (((r + ri) & 3) << 4));
+            b[r] = ld4(sm, at1 + (((r + ri) & 3) << 4));
+        }
+        const f4 z = ld4(sm, ((m - 1) * S + sb) * 64 + (ri << 4));   // (row 0 of the root's tile, for I = 0)
+        double fs = 4 * I + 1 <= n ? (double)a[0][1] : 0.0;
+        fs += 4 * I + 2 <= n ? (double)a[1][2] : 0.0;
+        fs += 4 * I + 3 <= n ? (double)a[2][3] : 0.0;
+        fs += I + 1 < m ? (double)b[3][0] : 0.0;
+        fs += I == 0 && n >= 2 ? (double)(rc == 0 ? z[0] : rc == 1 ? z[1] : rc == 2 ? z[2] : z[3]) : 0.0;
+        *reinterpret_cast<double *>(sm + cx.partd + 8 * f) = fs;
+        b[3][0] = NEG;
+        if (m <= 2 && I == 0)   // the root
+#pragma unroll
+            for (int c = 0; c < 4; ++c) b[0][c] = c == rc ? NEG : b[0][c];
+        if (m == 1) {   // (the tile itself: two spans at most that are neither)
+            b[0][1] = b[1][2] = b[2][3] = NEG;
+        }
+        float mx = NEG;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mx = __builtin_fmaxf(mx, __builtin_fmaxf(__builtin_fmaxf(b[r][0], b[r][1]), __builtin_fmaxf(b[r][2], b[r][3])));
+        float sum = 0.f, cnt = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                sum += fast_exp2((b[r][c] - mx) * LOG2E_F);
+                cnt += b[r][c] > -700.f ? 1.f : 0.f;
+            }
+        const bool some = cnt > 0.f && (m == 1 || I + 1 < m);
+        st4(sm, cx.part + 16 * f, f4{0.f, some ? mx * LOG2E_F + fast_log2(sum) - fast_log2(cnt) + 2.f : 0.f, some ? 1.f : 0.f, 0.f});
+    }
+    __syncthreads();
+    growth_shift<false>(cx, sm, m, kTabD);
+    for (int sb = tid >> 4; sb < S; sb += NT >> 4) {   // a 16-lane row per sentence, in a fixed order
+        double fs = 0.0;
+        for (int I = tid & 15; I < m; I += 16) fs += *reinterpret_cast<const double *>(sm + cx.partd + 8 * (I * S + sb));
+        fs = row_sum(fs);
+        if ((tid & 15) == 0) *reinterpret_cast<double *>(sm + cx.forced + 8 * sb) = fs;
+    }
+    __syncthreads();
+}
+
+// The walk over a bundle's tile rows in the order of the score rows: rows of
+// blocks I and m-1-I share one folded row of m+1 tiles, so consecutive
+// threads take consecutive 16-byte pieces of a score row.
+struct Row_walk {
+    int m, W, per, total;
+    float inv_per, inv_w;
+    __device__ Row_walk(int m_, int S) : m(m_), W(m_ + 1) {
+        per = ((m + 1) / 2) * 4 * W;
+        total = per * S;
+        inv_per = 1.0f / (float)per;
+        inv_w = 1.0f / (float)W;
+    }
+    struct At {
+        int sb, I, J, r;
+        bool ok;
+    };
+    __device__ __forceinline__ At at(int c) const {
+        At e;
+        const int cc = c < total ? c : 0;
+        e.sb = div_small(cc, per, inv_per);
+        const int rem = cc - e.sb * per;
+        const int u = div_small(rem, W, inv_w), v = rem - u * W, h = u >> 2;
+        e.r = u & 3;
+        e.I = v < m - h ? h : m - 1 - h;
+        e.J = e.I + (v < m - h ? v : v - (m - h));
+        e.ok = c < total && (v < m - h || e.I > h);   // odd m: the middle row of tiles is not folded twice
+        return e;
+    }
+};
+// The scores (i, 4J .. 4J+3) of a row: in bounds for every row i < n (rows
+// from n on, which hold no span, read row n-1): the last ones run into row n,
+// which the padded block has, since N1 > n.
+__device__ __forceinline__ f4 load_row(const float *sent, int N1, int i, int J, int n) {
+    return *reinterpret_cast<const f4u *>(sent + (size_t)min(i, n - 1) * N1 + 4 * J);
+}
+
+// Inside (+ marginals) of a bundle: the tile form of inside_block_impl, same
+// outputs.  Returns false, having written no output, when a linear-domain
+// value leaves float32's range.
+template <bool LIN, bool REV, bool GOLD>
+__device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int32_t *rec, char *sm,
+                                                 const float *__restrict__ scores, const float *__restrict__ grad,
+                                                 float *__restrict__ logZ, float *__restrict__ marg,
+                                                 const int32_t *__restrict__ gold, float *__restrict__ loss) {
+    typedef Dom<LIN> Dm;
+    __shared__ int ovf;
+    const int tid = this_thread(), NT = (int)blockDim.x, N1 = p.n1;
+    const Io_ctx cx = io_ctx(rec);
+    const int m = cx.m, S = cx.S;
+    for (int sb = tid; sb < S; sb += NT) {
+        const int id = rec[kTrHeader + 2 * sb];
+        tab<int>(sm, cx, kTabId, sb) = id;
+        tab<int>(sm, cx, kTabN, sb) = rec[kTrHeader + 2 * sb + 1];
+        tab<float>(sm, cx, kTabG, sb) = grad ? grad[id] : 1.0f;
+    }
+    if (tid == 0) ovf = 0;
+    __syncthreads();
+
+    // Prologue: the score rows into P and Q, at most kTilePieces pieces a
+    // thread (the plan's limit), all in flight together.
+    const Row_walk rw(m, S);
+    const size_t sent_stride = (size_t)N1 * N1;
+    f4 piece[kTilePieces];
+    auto load_pieces = [&](int t0) {
+#pragma unroll
+        for (int u = 0; u < kTilePieces; ++u) {
+            const typename Row_walk::At a = rw.at(t0 + u * NT);
+            piece[u] = load_row(scores + (size_t)tab<int>(sm, cx, kTabId, a.sb) * sent_stride, N1, 4 * a.I + a.r, a.J,
+                                tab<int>(sm, cx, kTabN, a.sb));
+        }
+    };
+    load_pieces(tid);
+#pragma unroll
+    for (int u = 0; u < kTilePieces; ++u) {
+        const typename Row_walk::At a = rw.at(tid + u * NT);
+        const int n = tab<int>(sm, cx, kTabN, a.sb), i = 4 * a.I + a.r, j0 = 4 * a.J, g = a.I * S + a.sb;
+        f4 x;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[c] = j0 + c > i && j0 + c <= n ? piece[u][c] : NEG;
+        const int off = a.I * cx.rpb + (a.J * S + a.sb) * 64 + (((a.r + cx.rot(g)) & 3) << 4);
+        if (a.ok) {
+            st4(sm, off, x);
+            if constexpr (REV) st4(sm, cx.qo + off, x);
+        }
+    }
+    __syncthreads();
+    tile_seed(cx, sm);
+
+    // The stages.
+    const int nw = NT >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int most = lanes_lg(m * S, nw);
+    inside_diagonal<LIN>(cx, sm, &ovf);
+    __syncthreads();
+    int tr = tile_rescale_after<LIN>(1, m);
+    for (int t = 1; t < (REV ? m + 1 : m); ++t) {
+        const int cin = (m - t) * S, cout = REV ? t * S : 0;
+        const int lg = stage_lg(t - 1, cin, cout, nw, most);
+        const int win = ((cin << lg) + 63) >> 6, wout = ((cout << lg) + 63) >> 6;
+        for (int w = wave; w < win + wout; w += nw) {
+            if (w < win)
+                tile_task<LIN, false>(cx, sm, t, t - 1, cin, w, lg, &ovf);
+            else if (REV && t < m)
+                tile_task<LIN, true>(cx, sm, m - t, t - 1, cout, w - win, lg, &ovf);
+            else if (REV)
+                outside_diagonal<LIN>(cx, sm, w - win, lg, &ovf);
+        }
+        __syncthreads();
+        if (t == tr) {
+            tile_rescale<LIN, REV>(cx, sm, t);
+            tr = tile_rescale_after<LIN>(t + 1, m);
+        }
+    }
+
+    // The scores again, for the epilogue: in flight during the roots' sums.
+    const int tid_e = here_lane(tid);   // (the walk again too, not kept across the sweep)
+    if constexpr (REV) load_pieces(tid_e);
+
+    // The roots.
+    auto root_of = [&](int sb) {
+        const int rc = tab<int>(sm, cx, kTabN, sb) - 4 * (m - 1);
+        return *reinterpret_cast<const float *>(sm + ((m - 1) * S + sb) * 64 + (cx.rot(sb) << 4) + 4 * rc);
+    };
+    for (int sb = tid; sb < S; sb += NT) {
+        const float r = root_of(sb);
+        if constexpr (LIN)
+            if (!(r >= kLinMin) || !(r <= kLinMax)) ovf = 1;
+        tab<float>(sm, cx, kTabLz, sb) = Dm::log2(r);
+    }
+    __syncthreads();
+    if constexpr (LIN)
+        if (ovf) return false;
+    auto log_z = [&](int sb) {
+        const int n = tab<int>(sm, cx, kTabN, sb);
+        const float r = root_of(sb);
+        const double lr = LIN ? log2_split(r) : (double)r;
+        return (lr - (double)tab<float>(sm, cx, kTabD, sb) * (n >= 2 ? n - 2 : 0)) * LN2_D +
+               *reinterpret_cast<const double *>(sm + cx.forced + 8 * sb);
+    };
+    if (logZ != nullptr)
+        for (int sb = tid; sb < S; sb += NT) logZ[tab<int>(sm, cx, kTabId, sb)] = (float)log_z(sb);
+    if constexpr (!REV) return true;
+
+    if constexpr (GOLD) {
+        // A wavefront per sentence: the gold spans' scores summed in float64
+        // (a fixed order) and marked in the transposed outside tiles, which
+        // nothing reads any more (diagonal tiles: below their diagonal).
+        const int R = 2 * (N1 - 1) - 1, lane = tid & 63;
+        for (int sb = wave; sb < S; sb += nw) {
+            const int id = tab<int>(sm, cx, kTabId, sb), n = tab<int>(sm, cx, kTabN, sb);
+            const int32_t *g2 = gold + (size_t)id * R * 2;
+            double acc = 0.0;
+            for (int r = lane; r < 2 * n - 1; r += 64) {
+                const int i = g2[2 * r], j = g2[2 * r + 1];
+                if (0 <= i && i < j && j <= n) {
+                    acc += (double)scores[(size_t)id * sent_stride + (size_t)i * N1 + j];
+                    const int g = (j >> 2) * S + sb;
+                    *reinterpret_cast<int *>(sm + (j >> 2) * cx.rpb + ((i >> 2) * S + sb) * 64 +
+                                             (((j + cx.rot(g)) & 3) << 4) + 4 * (i & 3)) = kGoldMark;
+                }
+            }
+#pragma unroll
+            for (int s = 32; s >= 1; s >>= 1) acc += __shfl_xor(acc, s, 64);
+            if (lane == 0) loss[id] = (float)(log_z(sb) - acc);
+        }
+        __syncthreads();
+    }
+
+    // Epilogue: the marginals row piece by row piece,
+    //   mu(i,j) = g exp2(alpha~(i,j) + O'(i,j) - (s(i,j) + d) - alpha~(0,n)),
+    // and exactly g on forced spans.
+#pragma unroll
+    for (int u = 0; u < kTilePieces; ++u) {
+        const typename Row_walk::At a = rw.at(tid_e + u * NT);
+        const int sb = a.sb, n = tab<int>(sm, cx, kTabN, sb), id = tab<int>(sm, cx, kTabId, sb);
+        const int i = 4 * a.I + a.r, j0 = 4 * a.J, gi = a.I * S + sb;
+        if (!a.ok || i >= n) continue;
+        const int off = a.I * cx.rpb + (a.J * S + sb) * 64 + (((a.r + cx.rot(gi)) & 3) << 4);
+        const f4 al = ld4(sm, off), ou = ld4(sm, cx.qo + off);
+        const float d = tab<float>(sm, cx, kTabD, sb), g = tab<float>(sm, cx, kTabG, sb);
+        const float lz = tab<float>(sm, cx, kTabLz, sb);
+        f4 mu;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int j = j0 + c;
+            const bool forced = j == i + 1 || (i == 0 && j == n);
+            const float x = fast_exp2(((Dm::log2(al[c]) - lz) + Dm::log2(ou[c])) -
+                                      __builtin_fmaf(piece[u][c], LOG2E_F, d));
+            mu[c] = forced ? g : g * x;
+            if constexpr (GOLD) {
+                const int gj = a.J * S + sb;
+                const int mk = *reinterpret_cast<const int *>(sm + a.J * cx.rpb + gi * 64 +
+                                                              (((c + cx.rot(gj)) & 3) << 4) + 4 * a.r);
+                if (mk == kGoldMark && j > i) mu[c] -= g;
+            }
+        }
+        float *out = marg + (size_t)id * sent_stride + (size_t)i * N1 + j0;
+        if (j0 > i && j0 + 3 <= n) {
+            *reinterpret_cast<f4u *>(out) = mu;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (j0 + c > i && j0 + c <= n) out[c] = mu[c];
+        }
+    }
+    return true;
+}
+
+template <bool REV, bool GOLD = false>
+__device__ __forceinline__ void tile_inside(const KernelPlan &p, const int32_t *rec, char *sm,
+                                            const float *__restrict__ scores, const float *__restrict__ grad,
+                                            float *__restrict__ logZ, float *__restrict__ marg,
+                                            const int32_t *__restrict__ gold = nullptr,
+                                            float *__restrict__ loss = nullptr) {
+    if (tile_inside_impl<true, REV, GOLD>(p, rec, sm, scores, grad, logZ, marg, gold, loss)) return;
+    __syncthreads();   // every thread has left the linear attempt
+    tile_inside_impl<false, REV, GOLD>(p, rec, sm, scores, grad, logZ, marg, gold, loss);
+}
+
+// ---------------------------------------------------------------------------
+// CKY in tiles.  Float64 max-plus, beta(i,j) = (max_k fl(beta(i,k) +
+// beta(k,j))) + s(i,j), the same sums and the same lowest-split rule as
+// cky_block.  A stage finishes one tile diagonal.  When a stage has few tiles
+// four lanes share one, a row each (no combining over lanes, but for the
+// splits when 8 or 16 share it), and pass their rows round before the finish.
+//
+// Storage: the upper tiles by diagonal, each diagonal as eight planes of
+// 16-byte pieces (row r, columns 0-1 and 2-3), entry f = I*S + sb, so that
+// consecutive lanes read consecutive pieces; then 16 bytes of splits
+// (k - 4 I) per tile.
+struct Ck_ctx {
+    int m, S, split, tab;
+    uint32_t mag;
+    __device__ __forceinline__ int cnt(int D) const { return (m - D) * S; }
+    // tiles of the diagonals before D
+    __device__ __forceinline__ int before(int D) const { return S * (D * m - ((D * (D - 1)) >> 1)); }
+    __device__ __forceinline__ int plane0(int D, int f) const { return before(D) * 128 + f * 16; }
+    __device__ __forceinline__ int stride(int D) const { return cnt(D) * 16; }
+};
+__device__ __forceinline__ Ck_ctx ck_ctx(const int32_t *rec) {
+    Ck_ctx c;
+    c.m = rec[kTrM];
+    c.S = rec[kTrCount];
+    c.mag = (uint32_t)rec[kTrMagic];
+    c.split = c.before(c.m) * 128;
+    c.tab = c.before(c.m) * 144;
+    return c;
+}
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ d2 ldd(const char *sm, int off) { return *reinterpret_cast<const d2 *>(sm + off); }
+__device__ __forceinline__ void std2(char *sm, int off, d2 v) { *reinterpret_cast<d2 *>(sm + off) = v; }
+
+// Running maximum of a span's splits and the first split (from 4 I) at it.
+// The choice of the split goes through the sign of a difference (exact in
+// its sign) and a bit select: five vector operations, where a compare and a
+// conditional move, which pass a mask through the scalar registers, issue at
+// half rate each and slow each other down across a CU's wavefronts.
+struct Best {
+    double v;
+    int k;
+};
+__device__ __forceinline__ int neg_mask(double x) {   // all ones when x < 0
+    return (int)(__builtin_bit_cast(uint64_t, x) >> 32) >> 31;
+}
+__device__ __forceinline__ int bit_select(int mask, int a, int b) {   // mask ? a : b, bit by bit
+    int r;
+    asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(mask), "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ void take(Best &b, double t, int k) {   // t > b.v: t and k
+    b.k = bit_select(neg_mask(b.v - t), k, b.k);
+    b.v = fmax(b.v, t);
+}
+__device__ __forceinline__ void take_first(Best &b, double t, int k) {   // t >= b.v
+    b.k = bit_select(neg_mask(t - b.v), b.k, k);
+    b.v = fmax(b.v, t);
+}
+// Below any chart value, finite (differences of two stay finite).
+constexpr double kNoSplit = -1.0e300;
+// Over lanes with different splits of one span: the higher value, the lower
+// split among equals.
+template <int CTRL>
+__device__ __forceinline__ void best_level(Best (&b)[4]) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const double v = dpp_d<CTRL>(b[c].v);
+        const int k = dpp_i<CTRL>(b[c].k);
+        const double m = fmax(b[c].v, v);
+        b[c].k = min(b[c].k | (neg_mask(b[c].v - m) & 255), k | (neg_mask(v - m) & 255));
+        b[c].v = m;
+    }
+}
+// The same across the rows of 16 lanes (WIDE: the 32-lane halves): the swap of
+// a value with itself leaves one row's value in one result, the other's in the
+// other.
+template <bool WIDE>
+__device__ __forceinline__ void best_swap(Best (&b)[4]) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    auto swap = [](uint32_t v) -> u2 {
+        if constexpr (WIDE) return __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(v, v, false, false));
+        else return __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(v, v, false, false));
+    };
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const uint64_t u = __builtin_bit_cast(uint64_t, b[c].v);
+        const u2 lo = swap((uint32_t)u), hi = swap((uint32_t)(u >> 32)), k = swap((uint32_t)b[c].k);
+        const double v0 = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]);
+        const double v1 = __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+        const double m = fmax(v0, v1);
+        b[c].k = min((int)k[0] | (neg_mask(v0 - m) & 255), (int)k[1] | (neg_mask(v1 - m) & 255));
+        b[c].v = m;
+    }
+}
+// Lanes per tile of a CKY stage (2^lg, lg of 0, 2 .. 6): one pass of the
+// workgroup's wavefronts, and no more lanes than products.
+__device__ __forceinline__ int cky_stage_lg(int np, int cnt, int nw) {
+    const int room = 64 * nw / cnt;
+    const int fit = room >= 64 ? 6 : room >= 32 ? 5 : room >= 16 ? 4 : room >= 8 ? 3 : room >= 4 ? 2 : 0;
+    return min(np >= 12 ? 6 : np >= 6 ? 5 : np >= 3 ? 4 : np >= 2 ? 3 : np >= 1 ? 2 : 0, fit);
+}
+
+// One row of a tile's products: row r of tiles (I,K) with the four rows of
+// (K,J), splits in increasing order.
+__device__ __forceinline__ void cky_row(Best (&b)[4], const d2 (&L)[2], const d2 (&R)[4][2], int k0) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int kv = here_lane(k0 + k);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) take(b[c], L[k >> 1][k & 1] + R[k][c >> 1][c & 1], kv);
+    }
+}
+
+__device__ __forceinline__ void cky_tile_task(const Ck_ctx &cx, char *sm, int D, int w, int lg) {
+    D = here(D);
+    w = here(w);
+    lg = here(lg);
+    const int S = cx.S, cnt = cx.cnt(D), np = D - 1, l = this_thread() & 63;
+    int f = w * (64 >> lg) + l, row = 0, q = 0;
+    if (lg > 0) {
+        row = l & 3;
+        q = lg == 2 ? 0 : lg == 3 ? (l >> 3) & 1 : (l >> 2) & ((1 << (lg - 2)) - 1);
+        f = w * (64 >> lg) + (lg == 3 ? ((l >> 2) & 1) + 2 * (l >> 4) : l >> lg);
+    }
+    const bool act = f < cnt && row == 0 && q == 0;
+    f = min(f, cnt - 1);
+    const int at = cx.plane0(D, f), st = cx.stride(D), u = f * 16, v = (f + D * S) * 16, s0 = cx.stride(0);
+
+    Best best[4][4];
+    auto load_l = [&](d2 (&L)[2], int kk, int r) {
+        const int la = cx.plane0(kk, f), lst = cx.stride(kk);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) L[h] = ldd(sm, la + (2 * r + h) * lst);
+    };
+    auto load_r = [&](d2 (&R)[4][2], int kk) {
+        const int ra = cx.plane0(D - kk, f + kk * S), rst = cx.stride(D - kk);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) R[k][h] = ldd(sm, ra + (2 * k + h) * rst);
+    };
+    if (lg == 0) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) best[r][c] = Best{kNoSplit, 0};
+#pragma unroll 1
+        for (int kk = 1; kk <= np; ++kk) {
+            d2 R[4][2], L[2], N[2];   // (the next row of L in flight)
+            load_r(R, kk);
+            load_l(N, kk, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                __builtin_amdgcn_sched_barrier(0);
+                L[0] = N[0];
+                L[1] = N[1];
+                if (r < 3) load_l(N, kk, r + 1);
+                cky_row(best[r], L, R, 4 * kk);
+            }
+        }
+    } else {
+        // one row's products, the next tiles in flight during each
+        const Best none{kNoSplit, 0};
+        Best b[4] = {none, none, none, none};
+        struct Ops {
+            d2 L[2], R[4][2];
+        } o0, o1;
+        const int g = lg - 2, iters = (np + (1 << g) - 1) >> g;   // 2^g lanes per row
+        auto load = [&](Ops &o, int it) {
+            const int kk = min(1 + q + (it << g), np);
+            load_l(o.L, kk, row);
+            load_r(o.R, kk);
+        };
+        auto use = [&](const Ops &o, int it) {
+            const int kk = 1 + q + (it << g);
+            if (kk <= np) cky_row(b, o.L, o.R, 4 * kk);
+        };
+        load(o0, 0);
+#pragma unroll 1
+        for (int it = 0; it < iters; it += 2) {
+            if (it + 1 < iters) load(o1, it + 1);
+            use(o0, it);
+            if (it + 1 >= iters) break;
+            if (it + 2 < iters) load(o0, it + 2);
+            use(o1, it + 1);
+        }
+        if (g >= 1) best_level<kRor8>(b);
+        if (g >= 2) best_level<kRor4>(b);
+        if (g >= 3) best_swap<false>(b);
+        if (g >= 4) best_swap<true>(b);
+        auto rows = [&](auto rr) {   // row rr from the lane of each four that holds it
+            constexpr int R = decltype(rr)::value, ctrl = R * 0x55;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) best[R][c] = Best{dpp_d<ctrl>(b[c].v), dpp_i<ctrl>(b[c].k)};
+        };
+        rows(std::integral_constant<int, 0>{});
+        rows(std::integral_constant<int, 1>{});
+        rows(std::integral_constant<int, 2>{});
+        rows(std::integral_constant<int, 3>{});
+    }
+
+    __builtin_amdgcn_sched_barrier(0);   // (the loads below stay out of the products' registers)
+    d2 s[4][2];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) s[r][h] = ldd(sm, at + (2 * r + h) * st);
+    double U[4][4], V[4][4];   // above the diagonal
+    auto diag = [&](double (&T)[4][4], int a) {
+        const d2 a1 = ldd(sm, a + s0), b1 = ldd(sm, a + 3 * s0);
+        T[0][1] = *reinterpret_cast<const double *>(sm + a + 8);
+        T[0][2] = a1[0];
+        T[0][3] = a1[1];
+        T[1][2] = b1[0];
+        T[1][3] = b1[1];
+        T[2][3] = *reinterpret_cast<const double *>(sm + a + 5 * s0 + 8);
+    };
+    diag(U, u);
+    diag(V, v);
+    // Splits in block I (the lowest), in the blocks between, in block J.  By
+    // antidiagonals of the tile; the two splits whose other part the last
+    // antidiagonal finished come last (the lower one first at equal sums).
+    double x[4][4];
+#pragma unroll
+    for (int a = 0; a < 7; ++a) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int r = c + 3 - a;
+            if (r < 0 || r > 3) continue;
+            Best b = best[r][c];
+            if (r < 2) {
+                Best lo{U[r][r + 2] + x[r + 2][c], r + 2};
+                if (r < 1) take(lo, U[0][3] + x[3][c], 3);
+                take(lo, b.v, b.k);
+                b = lo;
+            }
+#pragma unroll
+            for (int q2 = 0; q2 + 1 < c; ++q2) take(b, x[r][q2] + V[q2][c], 4 * D + q2);
+            if (r < 3) {
+                const double t = U[r][r + 1] + x[r + 1][c];
+                take_first(b, t, r + 1);
+            }
+            if (c > 0) take(b, x[r][c - 1] + V[c - 1][c], 4 * D + c - 1);
+            const double sv = s[r][c >> 1][c & 1];
+            x[r][c] = b.v + sv;
+            best[r][c].k = b.k;
+            if (r == 3 && c == 0) x[3][0] = D == 1 ? sv : x[3][0];   // a word
+        }
+    }
+    if (act) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) std2(sm, at + (2 * r + h) * st, d2{x[r][2 * h], x[r][2 * h + 1]});
+        uint4 pk;
+        uint32_t *pq = &pk.x;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            pq[r] = (uint32_t)best[r][0].k | (uint32_t)best[r][1].k << 8 | (uint32_t)best[r][2].k << 16 |
+                    (uint32_t)best[r][3].k << 24;
+        *reinterpret_cast<uint4 *>(sm + cx.split + (cx.before(D) + f) * 16) = pk;
+    }
+}
+
+// The split of span (i, j), two words or more, of sentence sb.
+__device__ __forceinline__ int tile_split(const Ck_ctx &cx, const char *sm, int sb, int i, int j) {
+    const int I = i >> 2, D = (j >> 2) - I;
+    const int t = cx.before(D) + I * cx.S + sb;
+    const int k = 4 * I + (int)*reinterpret_cast<const uint8_t *>(sm + cx.split + t * 16 + 4 * (i & 3) + (j & 3));
+    return max(i + 1, min(k, j - 1));   // (already so, unless a score was not finite)
+}
+
+__device__ __forceinline__ void tile_cky(const KernelPlan &p, const int32_t *rec, char *sm,
+                                         const float *__restrict__ scores, int32_t *__restrict__ spans,
+                                         float *__restrict__ best) {
+    const int tid = this_thread(), NT = (int)blockDim.x, N1 = p.n1;
+    const Ck_ctx cx = ck_ctx(rec);
+    const int m = cx.m, S = cx.S;
+    int *const ids = reinterpret_cast<int *>(sm + cx.tab), *const ns = ids + S;
+    for (int sb = tid; sb < S; sb += NT) {
+        ids[sb] = rec[kTrHeader + 2 * sb];
+        ns[sb] = rec[kTrHeader + 2 * sb + 1];
+    }
+    __syncthreads();
+    const Row_walk rw(m, S);
+    const size_t sent_stride = (size_t)N1 * N1;
+    constexpr int kU = 6;
+    for (int c0 = tid; c0 < rw.total; c0 += NT * kU) {
+        typename Row_walk::At a[kU];
+        f4 v[kU];
+        int n[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            a[u] = rw.at(c0 + u * NT);
+            n[u] = ns[a[u].sb];
+            v[u] = load_row(scores + (size_t)ids[a[u].sb] * sent_stride, N1, 4 * a[u].I + a[u].r, a[u].J, n[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (!a[u].ok) continue;
+            const int i = 4 * a[u].I + a[u].r, j0 = 4 * a[u].J, D = a[u].J - a[u].I;
+            double x[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = (double)(j0 + c > i && j0 + c <= n[u] ? v[u][c] : NEG);
+            const int st = cx.stride(D), at = cx.plane0(D, a[u].I * S + a[u].sb) + 2 * a[u].r * st;
+            std2(sm, at, d2{x[0], x[1]});
+            std2(sm, at + st, d2{x[2], x[3]});
+        }
+    }
+    __syncthreads();
+    for (int f = tid; f < m * S; f += NT) {   // diagonal 0: spans of two and three words
+        const int s0 = cx.stride(0), at = f * 16;
+        const d2 a0 = ldd(sm, at), a1 = ldd(sm, at + s0), b1 = ldd(sm, at + 3 * s0), c1 = ldd(sm, at + 5 * s0);
+        const double x02 = (a0[1] + b1[0]) + a1[0], x13 = (b1[0] + c1[1]) + b1[1];
+        Best b{a0[1] + x13, 1};
+        take(b, x02 + c1[1], 2);
+        const double x03 = b.v + a1[1];
+        *reinterpret_cast<uint4 *>(sm + cx.split + f * 16) = make_uint4(1u << 16 | (uint32_t)b.k << 24, 2u << 24, 0u, 0u);
+        std2(sm, at + s0, d2{x02, x03});
+        std2(sm, at + 3 * s0, d2{b1[0], x13});
+    }
+    __syncthreads();
+    const int nw = NT >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int D = 1; D < m; ++D) {
+        const int cnt = cx.cnt(D), lg = cky_stage_lg(D - 1, cnt, nw), wn = ((cnt << lg) + 63) >> 6;
+        for (int w = wave; w < wn; w += nw) cky_tile_task(cx, sm, D, w, lg);
+        __syncthreads();
+    }
+
+    const int R = 2 * (N1 - 1) - 1;
+    for (int sb = wave; sb < S; sb += nw) {   // rows past each tree are -1
+        int2 *const out = reinterpret_cast<int2 *>(spans + (size_t)ids[sb] * R * 2);
+        for (int r = 2 * ns[sb] - 1 + (tid & 63); r < R; r += 64) out[r] = make_int2(-1, -1);
+    }
+    if (best != nullptr)
+        for (int sb = tid; sb < S; sb += NT) {
+            const int n = ns[sb], D = n >> 2, c = n & 3;
+            best[ids[sb]] = (float)*reinterpret_cast<const double *>(sm + cx.plane0(D, sb) + (c >> 1) * cx.stride(D) +
+                                                                     8 * (c & 1));
+        }
+    // The trees, one lane per word (see walk_trees).
+    const int per = 4 * m - 1, total = S * per;
+    const float inv_per = 1.0f / (float)per;
+    for (int t = tid; t < total; t += NT) {
+        const int sb = div_small(t, per, inv_per), w = t - sb * per, n = ns[sb];
+        if (w >= n) continue;
+        int2 *const out = reinterpret_cast<int2 *>(spans + (size_t)ids[sb] * R * 2);
+        int i = 0, j = n, row = 0;
+        for (int it = 0; i < w && it < n; ++it) {   // (the bounds only guard against a corrupt table)
+            const int k = tile_split(cx, sm, sb, i, j);
+            if (w < k) {
+                ++row;
+                j = k;
+            } else {
+                row += 2 * (k - i);
+                i = k;
+            }
+        }
+        for (int it = 0; it < n; ++it) {
+            out[row] = make_int2(i, j);
+            if (j - i < 2) break;
+            j = tile_split(cx, sm, sb, i, j);
+            ++row;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Kernels: a workgroup per bundle, the longest predicted first (the plan's
+// order); the dispatcher hands a workgroup to each slot that frees up.
+#define CRF_TILE_KERNEL \
+    __global__ __launch_bounds__(kTileThreadsMax) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+
+template <bool REV>
+CRF_TILE_KERNEL tile_inside_kernel(KernelPlan p, const float *__restrict__ scores, const float *__restrict__ grad,
+                                   float *__restrict__ logZ, float *__restrict__ marg) {
+    extern __shared__ __align__(16) char smem_raw[];
+    tile_inside<REV>(p, p.tile_io.recs + (size_t)blockIdx.x * p.tile_stride, smem_raw, scores, grad, logZ, marg);
+}
+
+CRF_TILE_KERNEL tile_loss_kernel(KernelPlan p, const float *__restrict__ scores, const int32_t *__restrict__ gold,
+                                 const float *__restrict__ grad, float *__restrict__ loss, float *__restrict__ marg) {
+    extern __shared__ __align__(16) char smem_raw[];
+    tile_inside<true, true>(p, p.tile_io.recs + (size_t)blockIdx.x * p.tile_stride, smem_raw, scores, grad, nullptr,
+                            marg, gold, loss);
+}
+
+CRF_TILE_KERNEL tile_cky_kernel(KernelPlan p, const float *__restrict__ scores, int32_t *__restrict__ spans,
+                                float *__restrict__ best) {
+    extern __shared__ __align__(16) char smem_raw[];
+    tile_cky(p, p.tile_ck.recs + (size_t)blockIdx.x * p.tile_stride, smem_raw, scores, spans, best);
+}
+
+// Inside with the marginals and CKY in one launch, bundles of both merged.
+CRF_TILE_KERNEL tile_parse_kernel(KernelPlan p, const float *__restrict__ scores, const float *__restrict__ grad,
+                                  float *__restrict__ logZ, float *__restrict__ marg, int32_t *__restrict__ spans,
+                                  float *__restrict__ best) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const int32_t *rec = p.tile_mix.recs + (size_t)blockIdx.x * p.tile_stride;
+    if (rec[kTrKind] == kKindInside) tile_inside<true>(p, rec, smem_raw, scores, grad, logZ, marg);
+    else tile_cky(p, rec, smem_raw, scores, spans, best);
+}
+
+// MBR decoding: a bundle's marginals, then CKY over them (read back by the
+// workgroup that wrote them) in the same LDS.
+CRF_TILE_KERNEL tile_mbr_kernel(KernelPlan p, const float *__restrict__ scores, float *__restrict__ logZ, float *marg,
+                                int32_t *__restrict__ spans, float *__restrict__ best) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const int32_t *rec = p.tile_io.recs + (size_t)blockIdx.x * p.tile_stride;
+    tile_inside<true>(p, rec, smem_raw, scores, nullptr, logZ, marg);
+    __syncthreads();   // the marginals are written and the charts are free
+    tile_cky(p, rec, smem_raw, marg, spans, best);
+}
+
+}  // namespace
+
+hipError_t set_tile_attributes(int max_lds_bytes) {
+    const void *fns[] = {(const void *)tile_inside_kernel<false>, (const void *)tile_inside_kernel<true>,
+                         (const void *)tile_loss_kernel, (const void *)tile_cky_kernel, (const void *)tile_parse_kernel,
+                         (const void *)tile_mbr_kernel};
+    for (const void *f : fns) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds_bytes);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_tile_inside(const KernelPlan &p, const float *scores, const float *grad, float *logZ, float *marg,
+                              hipStream_t stream) {
+    const dim3 grid(p.tile_io.n), block(p.tile_threads);
+    const size_t lds = (size_t)p.tile_io.lds_bytes;
+    if (marg != nullptr)
+        hipLaunchKernelGGL(tile_inside_kernel<true>, grid, block, lds, stream, p, scores, grad, logZ, marg);
+    else
+        hipLaunchKernelGGL(tile_inside_kernel<false>, grid, block, lds, stream, p, scores, grad, logZ, marg);
+    return hipGetLastError();
+}
+hipError_t launch_tile_loss(const KernelPlan &p, const float *scores, const int32_t *gold, const float *grad,
+                            float *loss, float *grad_scores, hipStream_t stream) {
+    hipLaunchKernelGGL(tile_loss_kernel, dim3(p.tile_io.n), dim3(p.tile_threads), (size_t)p.tile_io.lds_bytes, stream,
+                       p, scores, gold, grad, loss, grad_scores);
+    return hipGetLastError();
+}
+hipError_t launch_tile_cky(const KernelPlan &p, const float *scores, int32_t *spans, float *best, hipStream_t stream) {
+    hipLaunchKernelGGL(tile_cky_kernel, dim3(p.tile_ck.n), dim3(p.tile_threads), (size_t)p.tile_ck.lds_bytes, stream, p,
+                       scores, spans, best);
+    return hipGetLastError();
+}
+hipError_t launch_tile_parse(const KernelPlan &p, const float *scores, const float *grad, float *logZ, float *marg,
+                             int32_t *spans, float *best, hipStream_t stream) {
+    hipLaunchKernelGGL(tile_parse_kernel, dim3(p.tile_mix.n), dim3(p.tile_threads), (size_t)p.tile_mix.lds_bytes, stream,
+                       p, scores, grad, logZ, marg, spans, best);
+    return hipGetLastError();
+}
+hipError_t launch_tile_mbr(const KernelPlan &p, const float *scores, float *logZ, float *marg, int32_t *spans,
+                           float *best, hipStream_t stream) {
+    hipLaunchKernelGGL(tile_mbr_kernel, dim3(p.tile_io.n), dim3(p.tile_threads), (size_t)p.tile_io.lds_bytes, stream, p,
+                       scores, logZ, marg, spans, best);
+    return hipGetLastError();
+}
+
+}  // namespace crf
