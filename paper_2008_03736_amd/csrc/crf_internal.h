@@ -421,6 +421,7 @@ struct Schedule {
 constexpr int kTileMaxLen = 139;      // 35 blocks: the longest whose two inside squares fit in one CU's LDS
 constexpr int kTileThreads = 256;      // two workgroups per CU
 constexpr int kTileThreadsMax = 512;  // one workgroup per CU (bundles past half the LDS)
+constexpr int kTileThreadsWs = 512;  // workspace charts: a sentence and pass per workgroup
 constexpr int kTileTabWords = 6;
 // An inside bundle's score rows in 16-byte pieces (tiles are walked in folded
 // rows of m + 1), of which a thread keeps at most kTilePieces.
@@ -492,7 +493,26 @@ struct KernelPlan {
     // launch (both merged, by predicted duration); n = 0 when the plan has none
     TileSchedule tile_io, tile_ck, tile_mix;
     int32_t tile_stride, tile_threads;
+    // sentences past LDS on tile charts in the workspace: 2 n records of
+    // kTrHeader + 2 ints (inside and CKY of each, longest first; kTrPitch holds
+    // the chart's place in the workspace / 256)
+    TileSchedule tile_ws;
+    // tile_on: the plan's calls run on tile charts (unlabelled plans);
+    // tile_long: the sentences of more than kMaxLenInLds words too (else the
+    // workspace kernels of crf_kernels.hip take those); tile_scratch: the
+    // workspace tile charts fit in the no-allocation scratch
+    int32_t tile_on, tile_long, tile_scratch;
 };
+// Batches of at most kTileTeamCount sentences past LDS whose longest has more
+// than kTileTeamLen words leave those sentences to the workspace kernels'
+// teams: one workgroup a sentence (tile charts) loses to 16 there (a lone
+// sentence fused: 256 words 493 against 1,095 us in teams, 400 words 1,411
+// against about 1,530, 512 words 2,100 in teams).
+constexpr int kTileTeamCount = 16, kTileTeamLen = 400;
+// Bytes of a sentence's tile charts in the workspace: inside (alpha and O', each
+// also transposed) and CKY (chart and 16-bit splits).
+__host__ __device__ inline int64_t tile_ws_io_bytes(int m) { return 128 * (int64_t)m * (m + 1); }
+__host__ __device__ inline int64_t tile_ws_ck_bytes(int m) { return 80 * (int64_t)m * (m + 1); }
 
 // Teams for workspace sentences: up to kTeamMaxK workgroups of one XCD run a
 // sentence's pass together.  The team area holds kTeamHeaderWords words

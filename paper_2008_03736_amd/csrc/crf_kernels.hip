@@ -2067,6 +2067,7 @@ hipError_t launch_parse_scratch(const KernelPlan &p, char *scr, const float *sco
     q.counter = reinterpret_cast<int32_t *>(scr);
     q.ws = scr + kScratchCounterBytes;
     q.team_area = nullptr;   // workspace sentences on lone workgroups: no memory beyond the scratch
+    if (!p.tile_scratch) q.tile_on = 0;   // the bundles' own charts, which need less of it
     hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, stream, q.counter, (int)(kScratchCounterBytes / 4));
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -2138,13 +2139,13 @@ static hipError_t launch_inside_sweeps(const KernelPlan &p, const float *scores,
                                        float *marg, hipStream_t stream) {
     const Schedule &q = p.inside;
     hipError_t e;
-    if (!LAB && p.tile_io.n > 0) {
+    if (!LAB && p.tile_on) {
         if ((e = launch_tile_inside(p, scores, grad, logZ, marg, stream)) != hipSuccess) return e;
     } else if (q.n_bundles > 0) {
         launch_inside_k<false, LAB>(p, dim3(q.n_bundles), q.threads, q.lds_bytes, stream, scores, grad, logZ, marg);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (q.n_spill > 0) {
+    if (q.n_spill > 0 && !(p.tile_on && p.tile_long)) {
         KernelPlan t = p;
         dim3 grid;
         if ((e = spill_launch_shape(t, q.n_spill, stream, &grid)) != hipSuccess) return e;
@@ -2193,14 +2194,14 @@ static hipError_t launch_cky_k(const KernelPlan &p, const float *scores, int32_t
                                hipStream_t stream, int32_t *labels) {
     const Schedule &q = p.cky;
     hipError_t e;
-    if (!LAB && p.tile_ck.n > 0) {
+    if (!LAB && p.tile_on) {
         if ((e = launch_tile_cky(p, scores, spans, best, stream)) != hipSuccess) return e;
     } else if (q.n_bundles > 0) {
         hipLaunchKernelGGL((cky_kernel<false, LAB>), dim3(q.n_bundles), dim3(q.threads), (size_t)q.lds_bytes, stream, p,
                            scores, spans, best, labels);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (q.n_spill > 0) {
+    if (q.n_spill > 0 && !(p.tile_on && p.tile_long)) {
         KernelPlan t = p;
         dim3 grid;
         if ((e = spill_launch_shape(t, q.n_spill, stream, &grid)) != hipSuccess) return e;
@@ -2222,7 +2223,7 @@ hipError_t launch_cky(const KernelPlan &p, const float *scores, int32_t *spans, 
 
 hipError_t launch_mbr(const KernelPlan &p, const float *scores, float *logZ, float *marg, int32_t *spans,
                       float *best, hipStream_t stream) {
-    if (p.tile_io.n == 0 && (p.mbr == nullptr || p.counter == nullptr || p.mbr_grid < 1)) {
+    if (!p.tile_on && (p.mbr == nullptr || p.counter == nullptr || p.mbr_grid < 1)) {
         // separate launches, in stream order: inside + marginals, then CKY
         // over the marginals
         hipError_t e = launch_inside(p, scores, nullptr, logZ, marg, stream);
@@ -2230,7 +2231,7 @@ hipError_t launch_mbr(const KernelPlan &p, const float *scores, float *logZ, flo
         return launch_cky(p, marg, spans, best, stream);
     }
     hipError_t e;
-    if (p.tile_io.n > 0) {
+    if (p.tile_on) {
         e = launch_tile_mbr(p, scores, logZ, marg, spans, best, stream);
     } else {
         hipLaunchKernelGGL(mbr_kernel, dim3(p.mbr_grid), dim3(p.inside.threads), (size_t)p.mbr_lds, stream, p, scores,
@@ -2241,7 +2242,7 @@ hipError_t launch_mbr(const KernelPlan &p, const float *scores, float *logZ, flo
     // sentences too long for LDS (the plan has checked that the inside and
     // CKY workspace lists hold the same sentences): their marginals, then
     // CKY over them
-    if (p.inside.n_spill > 0) {
+    if (p.inside.n_spill > 0 && !(p.tile_on && p.tile_long)) {
         KernelPlan t = p;
         dim3 grid;
         if ((e = spill_launch_shape(t, p.inside.n_spill, stream, &grid)) != hipSuccess) return e;
@@ -2263,14 +2264,14 @@ hipError_t launch_loss(const KernelPlan &p, const float *scores, const int32_t *
                        float *loss, float *grad_scores, hipStream_t stream) {
     const Schedule &q = p.inside;
     hipError_t e;
-    if (p.tile_io.n > 0) {
+    if (p.tile_on) {
         if ((e = launch_tile_loss(p, scores, gold, grad, loss, grad_scores, stream)) != hipSuccess) return e;
     } else if (q.n_bundles > 0) {
         hipLaunchKernelGGL((loss_kernel<false>), dim3(q.n_bundles), dim3(q.threads), (size_t)q.lds_bytes, stream, p,
                            scores, gold, grad, loss, grad_scores);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (q.n_spill > 0) {
+    if (q.n_spill > 0 && !(p.tile_on && p.tile_long)) {
         KernelPlan t = p;
         dim3 grid;
         if ((e = spill_launch_shape(t, q.n_spill, stream, &grid)) != hipSuccess) return e;
@@ -2298,7 +2299,7 @@ hipError_t launch_parse(const KernelPlan &p, const float *scores, const float *g
                         float *marg, int32_t *spans, float *best, hipStream_t stream) {
     const Schedule &qi = p.inside, &qc = p.cky;
     hipError_t e;
-    if (p.tile_mix.n > 0) {
+    if (p.tile_on) {
         if ((e = launch_tile_parse(p, scores, grad, logZ, marg, spans, best, stream)) != hipSuccess) return e;
     } else if (p.mix != nullptr && p.counter != nullptr && p.fused_grid >= 1 && p.n_mix == qi.n_bundles + qc.n_bundles) {
         const size_t lds = (size_t)(qi.lds_bytes > qc.lds_bytes ? qi.lds_bytes : qc.lds_bytes);
@@ -2317,7 +2318,7 @@ hipError_t launch_parse(const KernelPlan &p, const float *scores, const float *g
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
     }
-    if (qi.n_spill + qc.n_spill > 0) {
+    if (qi.n_spill + qc.n_spill > 0 && !(p.tile_on && p.tile_long)) {
         KernelPlan t = p;
         dim3 grid;
         if ((e = spill_launch_shape(t, qi.n_spill + qc.n_spill, stream, &grid)) != hipSuccess) return e;

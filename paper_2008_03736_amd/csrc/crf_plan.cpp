@@ -52,7 +52,8 @@ struct crf_plan {
     uint32_t flags = 0;
     std::vector<void *> allocations;
     crf::KernelPlan kp{};
-    int64_t ws_bytes = 0;
+    int64_t ws_bytes = 0;          // device workspace owned
+    int64_t scratch_bytes = 0;     // of it, what the no-allocation call needs at least
     int32_t split_ws_count = 0;    // sentences with CKY split tables in the workspace
     int32_t workspace_users = 0;   // sentences using the workspace in some call
 };
@@ -656,21 +657,41 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
     fill(kp.inside, si);
     fill(kp.cky, sc);
 
-    // Tile bundles: unlabelled plans whose LDS sentences all fit in tiles.
-    std::vector<int32_t> tile_recs;
+    // Tile charts (unlabelled plans): bundles of the sentences that fit in
+    // LDS, workspace slots for the others.
+    std::vector<int32_t> tile_recs, tile_ws_recs;
     TileHost tio, tck;
-    kp.tile_io = kp.tile_ck = kp.tile_mix = crf::TileSchedule{};
+    kp.tile_io = kp.tile_ck = kp.tile_mix = kp.tile_ws = crf::TileSchedule{};
     kp.tile_threads = crf::kTileThreads;
-    {
-        std::vector<int32_t> tile_order;
-        bool fit = num_labels == 1 && !force;
-        for (int32_t b : order) {
-            const int n = lengths_host[b];
-            if (n > crf::kMaxLenInLds) continue;
-            fit = fit && n <= crf::kTileMaxLen;
-            tile_order.push_back(b);
+    kp.tile_on = num_labels == 1;
+    kp.tile_long = kp.tile_scratch = 1;
+    p->scratch_bytes = p->ws_bytes;
+    if (kp.tile_on) {
+        std::vector<int32_t> tile_order, ws_order;
+        for (int32_t b : order) (!force && lengths_host[b] <= crf::kTileMaxLen ? tile_order : ws_order).push_back(b);
+        if ((int)ws_order.size() <= crf::kTileTeamCount && max_len > crf::kTileTeamLen) {
+            kp.tile_long = 0;
+            ws_order.erase(std::remove_if(ws_order.begin(), ws_order.end(),
+                                          [&](int32_t b) { return force || lengths_host[b] > crf::kMaxLenInLds; }),
+                           ws_order.end());
         }
-        if (fit && !tile_order.empty()) {
+        int64_t at = kp.tile_long ? 0 : p->ws_bytes;   // (behind the charts of the kernels that take the others)
+        for (int32_t b : ws_order) {
+            const int n = lengths_host[b], m = crf::tile_blocks(n);
+            for (int kind : {crf::kKindInside, crf::kKindCky}) {
+                for (int32_t v : {(int32_t)kind, (int32_t)m, (int32_t)1, (int32_t)(at / 256), (int32_t)0, b, (int32_t)n})
+                    tile_ws_recs.push_back(v);
+                at += ((kind == crf::kKindInside ? crf::tile_ws_io_bytes(m) : crf::tile_ws_ck_bytes(m)) + 255) / 256 * 256;
+            }
+            kp.tile_ws.lds_bytes = std::max<int32_t>(
+                kp.tile_ws.lds_bytes, (int32_t)(24 * m + 8 + 4 * crf::kTileTabWords + 8));
+        }
+        kp.tile_ws.n = (int32_t)ws_order.size();
+        if (kp.tile_ws.n > 0) {
+            p->ws_bytes = std::max(p->ws_bytes, at);
+            kp.tile_scratch = at <= crf::kScratchBytes - crf::kScratchCounterBytes;
+        }
+        if (!tile_order.empty()) {
             const int m_max = crf::tile_blocks(lengths_host[tile_order[0]]);
             // A pitch of m for a lone sentence of 25 blocks (96..99 words): made
             // even, its two squares would no longer fit in half a CU.
@@ -741,7 +762,8 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
         (e = upload(p, rec_mbr, &kp.mbr)) != hipSuccess ||
         (e = upload(p, lab_rows, &kp.lab_rows)) != hipSuccess ||
         (e = upload(p, bia, &kp.bia_tiles)) != hipSuccess ||
-        (e = upload(p, tile_recs, &kp.tile_io.recs)) != hipSuccess) {
+        (e = upload(p, tile_recs, &kp.tile_io.recs)) != hipSuccess ||
+        (e = upload(p, tile_ws_recs, &kp.tile_ws.recs)) != hipSuccess) {
         const int code = (e == hipErrorOutOfMemory) ? CRF_ENOMEM : CRF_EHIP;
         release(p);
         delete p;
@@ -901,11 +923,11 @@ int crf_inside_fwd_bwd_cky_noalloc(const crf_plan *plan, const float *scores, co
         return fail(CRF_EINVAL, "scores/marginals/spans is NULL");
     if (plan->L != 1)
         return fail(CRF_EUNSUPPORTED, "CKY decode of labelled scores (L = %d)", plan->L);
-    if (plan->ws_bytes > crf::kScratchBytes - crf::kScratchCounterBytes)
+    if (plan->scratch_bytes > crf::kScratchBytes - crf::kScratchCounterBytes)
         return fail(CRF_EINVAL,
                     "the plan needs %lld bytes of workspace, more than the %lld bytes of static scratch "
                     "(use crf_inside_fwd_bwd_cky)",
-                    (long long)plan->ws_bytes, (long long)(crf::kScratchBytes - crf::kScratchCounterBytes));
+                    (long long)plan->scratch_bytes, (long long)(crf::kScratchBytes - crf::kScratchCounterBytes));
     int rc = check_device(plan);
     if (rc != CRF_OK) return rc;
     char *scr = nullptr;

@@ -115,8 +115,10 @@ struct Tile {
     float v[4][4];
 };
 
-__device__ __forceinline__ f4 ld4(const char *sm, int off) { return *reinterpret_cast<const f4 *>(sm + off); }
-__device__ __forceinline__ void st4(char *sm, int off, f4 v) { *reinterpret_cast<f4 *>(sm + off) = v; }
+// (offsets unsigned: a workspace access is then a uniform base and a 32-bit
+// offset, with no 64-bit address per lane)
+__device__ __forceinline__ f4 ld4(const char *sm, int off) { return *reinterpret_cast<const f4 *>(sm + (uint32_t)off); }
+__device__ __forceinline__ void st4(char *sm, int off, f4 v) { *reinterpret_cast<f4 *>(sm + (uint32_t)off) = v; }
 
 // ---------------------------------------------------------------------------
 // The two domains.  LIN: the chart holds exp2 of the shifted, log2-scaled
@@ -181,31 +183,57 @@ struct Dom {
     }
 };
 
-// A bundle's charts and tables (byte offsets into the workgroup's LDS).
+// A bundle's charts (byte offsets from `sm`: the workgroup's LDS, or, GLOB, a
+// sentence's slot of the workspace) and tables (from tb, in LDS).  Tile (I,J)
+// of sentence sb: alpha at a, O' at o, both transposed at at and ot, rows
+// rs(J - I) bytes apart.  In the workspace the four are arrays of their own,
+// each by diagonal and row, so that consecutive lanes, which take consecutive
+// I of a diagonal, read consecutive 16-byte pieces (64 sentences of 256 words,
+// inside and marginals: 466 us with whole tiles side by side, 396 so, part of
+// it from the 32-bit offsets).
+template <bool GLOB>
 struct Io_ctx {
-    int m, S, rpb, qo;   // blocks, sentences, bytes per row of tiles, offset of Q
+    static constexpr bool kGlob = GLOB;
+    int m, S, rpb, qo;   // blocks, sentences, bytes per row of tiles, offset of Q (GLOB: bytes per array)
     uint32_t mag;        // div_magic(S)
     int part, partd, forced, tab;
-    __device__ __forceinline__ int rot(int g) const { return (g >> 1) & 3; }
+    char *tb;
+    __device__ __forceinline__ int rot(int g) const { return GLOB ? 0 : (g >> 1) & 3; }
+    __device__ __forceinline__ int diag(int D) const { return 64 * (D * m - ((D * (D - 1)) >> 1)); }
+    __device__ __forceinline__ int rs(int D) const { return GLOB ? 16 * (m - D) : 16; }
+    __device__ __forceinline__ int a(int I, int J, int sb) const {
+        return GLOB ? diag(J - I) + I * 16 : I * rpb + (J * S + sb) * 64;
+    }
+    __device__ __forceinline__ int at(int I, int J, int sb) const {
+        return qo + (GLOB ? diag(J - I) + I * 16 : J * rpb + (I * S + sb) * 64);
+    }
+    __device__ __forceinline__ int o(int I, int J, int sb) const {
+        return GLOB ? 2 * qo + diag(J - I) + I * 16 : qo + I * rpb + (J * S + sb) * 64;
+    }
+    __device__ __forceinline__ int ot(int I, int J, int sb) const {
+        return GLOB ? 3 * qo + diag(J - I) + I * 16 : J * rpb + (I * S + sb) * 64;
+    }
 };
-__device__ __forceinline__ Io_ctx io_ctx(const int32_t *rec) {
-    Io_ctx c;
+template <bool GLOB>
+__device__ __forceinline__ Io_ctx<GLOB> io_ctx(const int32_t *rec, char *lds) {
+    Io_ctx<GLOB> c;
     c.m = rec[kTrM];
-    c.S = rec[kTrCount];
+    c.S = GLOB ? 1 : rec[kTrCount];
     c.rpb = rec[kTrPitch] * 64;
     c.mag = (uint32_t)rec[kTrMagic];
-    c.qo = c.m * c.rpb;
-    c.part = 2 * c.qo;
+    c.qo = GLOB ? 32 * c.m * (c.m + 1) : c.m * c.rpb;
+    c.part = GLOB ? 0 : 2 * c.qo;
     c.partd = c.part + 16 * c.m * c.S;
     c.forced = c.partd + 8 * c.m * c.S;
     c.tab = c.forced + 8 * c.S;
+    c.tb = lds;
     return c;
 }
 // per-sentence tables: word `which` of sentence sb
 enum { kTabD = 0, kTabDl, kTabG, kTabLz, kTabId, kTabN, kTabWords };
-template <typename T>
-__device__ __forceinline__ T &tab(char *sm, const Io_ctx &c, int which, int sb) {
-    return *reinterpret_cast<T *>(sm + c.tab + 4 * (which * c.S + sb));
+template <typename T, typename CX>
+__device__ __forceinline__ T &tab(const CX &c, int which, int sb) {
+    return *reinterpret_cast<T *>(c.tb + c.tab + 4 * (which * c.S + sb));
 }
 static_assert(kTabWords == kTileTabWords, "tile_io_bytes counts the tables");
 
@@ -253,10 +281,10 @@ __device__ __forceinline__ int lanes_lg(int tiles, int nw) {
 struct Diag3 {
     float d02, d03, d13;
 };
-__device__ __forceinline__ Diag3 diag3(const char *sm, int at, int rot) {
+__device__ __forceinline__ Diag3 diag3(const char *sm, int at, int rot, int rs) {
     typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 a = *reinterpret_cast<const f2 *>(sm + at + (rot << 4) + 8);
-    return Diag3{a[0], a[1], *reinterpret_cast<const float *>(sm + at + (((1 + rot) & 3) << 4) + 12)};
+    const f2 a = *reinterpret_cast<const f2 *>(sm + (uint32_t)(at + rot * rs + 8));
+    return Diag3{a[0], a[1], *reinterpret_cast<const float *>(sm + (uint32_t)(at + ((1 + rot) & 3) * rs + 12))};
 }
 
 // The inside of a tile from its products, its own terms and the diagonal
@@ -287,8 +315,8 @@ __device__ __forceinline__ void finish_inside(Tile &x, float (&sum)[4], const Ti
 // One wavefront's share of a stage's tiles of one kind: inside of diagonal
 // D (OUT = false) or outside of diagonal D; D >= 1 for the inside (diagonal 0
 // is inside_diagonal).  cnt tiles, np products each.
-template <bool LIN, bool OUT>
-__device__ __forceinline__ void tile_task(const Io_ctx &cx, char *sm, int D, int np, int cnt, int w, int lg, int *ovf) {
+template <bool LIN, bool OUT, typename CX>
+__device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np, int cnt, int w, int lg, int *ovf) {
     typedef Dom<LIN> Dm;
     const int m = cx.m, S = cx.S;
     const Lane_share ls = lane_share(here(w), here(lg));
@@ -299,28 +327,53 @@ __device__ __forceinline__ void tile_task(const Io_ctx &cx, char *sm, int D, int
 
     // The tile's scores, its sentence's shift and the diagonal tiles of I
     // and J (their spans of two and three words).
-    const int own_at = (OUT ? cx.qo : 0) + I * cx.rpb + gj * 64, ri = cx.rot(gi), rj = cx.rot(gj);
+    const int own_at = OUT ? cx.o(I, J, sb) : cx.a(I, J, sb), ri = cx.rot(gi), rj = cx.rot(gj), rs = cx.rs(D);
     f4 raw[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) raw[r] = ld4(sm, own_at + (((r + ri) & 3) << 4));
-    const float d = tab<float>(sm, cx, kTabD, sb);
-    const Diag3 U = diag3(sm, I * cx.rpb + gi * 64, ri), V = diag3(sm, J * cx.rpb + gj * 64, rj);
+    for (int r = 0; r < 4; ++r) raw[r] = ld4(sm, own_at + ((r + ri) & 3) * rs);
+    const float d = tab<float>(cx, kTabD, sb);
+    const Diag3 U = diag3(sm, cx.a(I, I, sb), ri, cx.rs(0)), V = diag3(sm, cx.a(J, J, sb), rj, cx.rs(0));
 
-    // Products, the first one's tiles in flight while the own terms are taken.
+    // Products, the first one's tiles in flight while the own terms are taken
+    // (in the workspace, whose loads take longer, three products' throughout).
+    const int iters = (np + (1 << lg) - 1) >> lg;
+    constexpr int kAhead = 1;
+    struct Pair {
+        f4 x[4], y[4];
+    } pr[kAhead];
     const int bx = (OUT ? 0 : cx.qo) + gi * 64, by = (OUT ? cx.qo : 0) + gj * 64;
-    const int lim = m * cx.rpb, step = cx.rpb << lg, iters = (np + (1 << lg) - 1) >> lg;
+    const int lim = m * cx.rpb, step = cx.rpb << lg;
     int off = ((OUT ? J : I) + 1 + ls.q) * cx.rpb;
-    f4 x[4], y[4];
-    auto load = [&]() {   // (a lane past its last product reads some row of tiles)
-        const int o = off >= lim ? (OUT ? off - lim : 0) : off;
+    auto load_at = [&](Pair &q, int ax, int rx, int ay, int ry) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            x[k] = ld4(sm, bx + o + 16 * k);
-            y[k] = ld4(sm, by + o + 16 * k);
+            q.x[k] = ld4(sm, ax + rx * k);
+            q.y[k] = ld4(sm, ay + ry * k);
         }
-        off += step;
     };
-    if (iters > 0) load();
+    auto load = [&](Pair &q, int it) {   // (a lane past its last product reads some tiles of the chart)
+        if constexpr (CX::kGlob) {
+            const int p = min(ls.q + (it << lg), np - 1);
+            if constexpr (!OUT) {
+                load_at(q, cx.qo + cx.diag(p + 1) + I * 16, cx.rs(p + 1), cx.diag(D - p - 1) + (I + p + 1) * 16,
+                        cx.rs(D - p - 1));
+            } else {
+                const int K = J + 1 + p;
+                const bool right = K < m;
+                const int L = K - m;   // the block left of I
+                load_at(q, right ? 3 * cx.qo + cx.diag(K - I) + I * 16 : cx.diag(I - L) + L * 16, cx.rs(right ? K - I : I - L),
+                        right ? cx.qo + cx.diag(K - J) + J * 16 : 2 * cx.qo + cx.diag(J - L) + L * 16,
+                        cx.rs(right ? K - J : J - L));
+            }
+        } else {
+            const int o = off >= lim ? (OUT ? off - lim : 0) : off;
+            load_at(q, bx + o, 16, by + o, 16);
+            off += step;
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j)
+        if (iters > 0) load(pr[j], j);
     Tile acc, e;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
@@ -330,16 +383,19 @@ __device__ __forceinline__ void tile_task(const Io_ctx &cx, char *sm, int D, int
             e.v[r][c] = Dm::own(raw[r][c], d);
         }
 #pragma unroll 1
-    for (int it = 0; it < iters; ++it) {
-        if (it > 0) load();
-        if (ls.q + (it << lg) < np) Dm::product(acc, x, y);
-    }
+    for (int i0 = 0; i0 < iters; i0 += kAhead)
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const int it = i0 + j;
+            if (kAhead == 1 && it > 0) load(pr[j], it);
+            if (ls.q + (it << lg) < np) Dm::product(acc, pr[j].x, pr[j].y);
+        }
     if (lg >= 1) Dm::template combine<kRor8>(acc);
     if (lg >= 2) Dm::template combine<kRor4>(acc);
     if (lg >= 3) Dm::template combine<kRor2>(acc);
     if (lg >= 4) Dm::template combine<kRor1>(acc);
     if (D == m - 1) {   // the root (0, n): own term 1; outside score 1
-        const int rc = tab<int>(sm, cx, kTabN, sb) - 4 * (m - 1);
+        const int rc = tab<int>(cx, kTabN, sb) - 4 * (m - 1);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             e.v[0][c] = I == 0 && c == rc ? Dm::one : e.v[0][c];
@@ -380,27 +436,27 @@ __device__ __forceinline__ void tile_task(const Io_ctx &cx, char *sm, int D, int
         if (__builtin_bit_cast(uint32_t, s) > kLinMaxBits) *ovf = 1;
     }
     if (act) {
-        const int up = (OUT ? cx.qo : 0) + I * cx.rpb + gj * 64, lo = (OUT ? 0 : cx.qo) + J * cx.rpb + gi * 64;
+        const int up = OUT ? cx.o(I, J, sb) : cx.a(I, J, sb), lo = OUT ? cx.ot(I, J, sb) : cx.at(I, J, sb);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            st4(sm, up + (((k + ri) & 3) << 4), f4{t.v[k][0], t.v[k][1], t.v[k][2], t.v[k][3]});
-            st4(sm, lo + (((k + rj) & 3) << 4), f4{t.v[0][k], t.v[1][k], t.v[2][k], t.v[3][k]});
+            st4(sm, up + ((k + ri) & 3) * rs, f4{t.v[k][0], t.v[k][1], t.v[k][2], t.v[k][3]});
+            st4(sm, lo + ((k + rj) & 3) * rs, f4{t.v[0][k], t.v[1][k], t.v[2][k], t.v[3][k]});
         }
     }
 }
 
 // Inside of tile diagonal 0: the spans of up to three words inside a block.
 // A lane per tile.
-template <bool LIN>
-__device__ __forceinline__ void inside_diagonal(const Io_ctx &cx, char *sm, int *ovf) {
+template <bool LIN, typename CX>
+__device__ __forceinline__ void inside_diagonal(const CX &cx, char *sm, int *ovf) {
     typedef Dom<LIN> Dm;
     const int cnt = cx.m * cx.S;
     for (int f = this_thread(); f < cnt; f += (int)blockDim.x) {
         const int I = cx.S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * cx.S;
-        const int at = I * cx.rpb + f * 64, ri = cx.rot(f);
-        const f4 r0 = ld4(sm, at + (ri << 4)), r1 = ld4(sm, at + (((1 + ri) & 3) << 4));
-        const float d = tab<float>(sm, cx, kTabD, sb);
-        const int n = tab<int>(sm, cx, kTabN, sb);
+        const int at = cx.a(I, I, sb), ri = cx.rot(f), rs = cx.rs(0);
+        const f4 r0 = ld4(sm, at + ri * rs), r1 = ld4(sm, at + ((1 + ri) & 3) * rs);
+        const float d = tab<float>(cx, kTabD, sb);
+        const int n = tab<int>(cx, kTabN, sb);
         float e02 = Dm::own(r0[2], d), e13 = Dm::own(r1[3], d), e03 = Dm::own(r0[3], d);
         if (cx.m == 1) {   // the root is in this tile
             e02 = n == 2 ? Dm::one : e02;
@@ -410,27 +466,27 @@ __device__ __forceinline__ void inside_diagonal(const Io_ctx &cx, char *sm, int 
         if constexpr (LIN)
             if (__builtin_bit_cast(uint32_t, e02 + e13 + x03) > kLinMaxBits) *ovf = 1;
         const float z = Dm::zero, o = Dm::one;
-        st4(sm, at + (ri << 4), f4{z, o, e02, x03});
-        st4(sm, at + (((1 + ri) & 3) << 4), f4{z, z, o, e13});
-        st4(sm, at + (((2 + ri) & 3) << 4), f4{z, z, z, o});
-        st4(sm, at + (((3 + ri) & 3) << 4), f4{z, z, z, z});
+        st4(sm, at + ri * rs, f4{z, o, e02, x03});
+        st4(sm, at + ((1 + ri) & 3) * rs, f4{z, z, o, e13});
+        st4(sm, at + ((2 + ri) & 3) * rs, f4{z, z, z, o});
+        st4(sm, at + ((3 + ri) & 3) * rs, f4{z, z, z, z});
     }
 }
 
 // Outside of tile diagonal 0 (stage m): the products run over every other
 // block, the finish over the three spans of two and three words.
-template <bool LIN>
-__device__ __forceinline__ void outside_diagonal(const Io_ctx &cx, char *sm, int w, int lg, int *ovf) {
+template <bool LIN, typename CX>
+__device__ __forceinline__ void outside_diagonal(const CX &cx, char *sm, int w, int lg, int *ovf) {
     typedef Dom<LIN> Dm;
     const int m = cx.m, S = cx.S, cnt = m * S, np = m - 1;
     const Lane_share ls = lane_share(w, lg);
     const bool act = ls.f < cnt && ls.q == 0;
     const int f = ls.f < cnt ? ls.f : cnt - 1;
     const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * S;
-    const int at = cx.qo + I * cx.rpb + f * 64, ri = cx.rot(f);
-    const f4 r0 = ld4(sm, at + (ri << 4)), r1 = ld4(sm, at + (((1 + ri) & 3) << 4));
-    const float d = tab<float>(sm, cx, kTabD, sb);
-    const int n = tab<int>(sm, cx, kTabN, sb);
+    const int at = cx.o(I, I, sb), ri = cx.rot(f), rs = cx.rs(0);
+    const f4 r0 = ld4(sm, at + ri * rs), r1 = ld4(sm, at + ((1 + ri) & 3) * rs);
+    const float d = tab<float>(cx, kTabD, sb);
+    const int n = tab<int>(cx, kTabN, sb);
     float a02 = Dm::zero, a13 = Dm::zero, a03 = Dm::zero;
     const int bx = f * 64, by = cx.qo + f * 64, lim = m * cx.rpb, step = cx.rpb << lg;
     int off = (I + 1 + ls.q) * cx.rpb;
@@ -438,10 +494,17 @@ __device__ __forceinline__ void outside_diagonal(const Io_ctx &cx, char *sm, int
 #pragma unroll 2
     for (int p = ls.q; p < np; p += 1 << lg) {
         const int o = off >= lim ? off - lim : off;
+        int ax = bx + o, ay = by + o, rx = 16, ry = 16;
+        if constexpr (CX::kGlob) {
+            const int K = I + 1 + p, L = K - m;
+            ax = K < m ? 3 * cx.qo + cx.diag(K - I) + I * 16 : cx.diag(I - L) + L * 16;
+            ay = K < m ? cx.qo + cx.diag(K - I) + I * 16 : 2 * cx.qo + cx.diag(I - L) + L * 16;
+            rx = ry = cx.rs(K < m ? K - I : I - L);
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {   // columns 0, 1 of X and 2, 3 of Y
-            const f2 x = *reinterpret_cast<const f2 *>(sm + bx + o + 16 * k);
-            const f2 y = *reinterpret_cast<const f2 *>(sm + by + o + 16 * k + 8);
+            const f2 x = *reinterpret_cast<const f2 *>(sm + (uint32_t)(ax + rx * k));
+            const f2 y = *reinterpret_cast<const f2 *>(sm + (uint32_t)(ay + ry * k + 8));
             a02 = Dm::fma(x[0], y[0], a02);
             a13 = Dm::fma(x[1], y[1], a13);
             a03 = Dm::fma(x[0], y[1], a03);
@@ -469,8 +532,11 @@ __device__ __forceinline__ void outside_diagonal(const Io_ctx &cx, char *sm, int
     if constexpr (LIN)
         if (__builtin_bit_cast(uint32_t, o02 + o13 + o03) > kLinMaxBits) *ovf = 1;
     if (act) {
-        st4(sm, at + (ri << 4), f4{Dm::zero, Dm::zero, o02, o03});
-        st4(sm, at + (((1 + ri) & 3) << 4), f4{Dm::zero, Dm::zero, Dm::zero, o13});
+        st4(sm, at + ri * rs, f4{Dm::zero, Dm::zero, o02, o03});
+        st4(sm, at + ((1 + ri) & 3) * rs, f4{Dm::zero, Dm::zero, Dm::zero, o13});
+        if constexpr (CX::kGlob)   // (where gold spans are marked; in LDS the alpha tile's lower half)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) st4(sm, cx.ot(I, I, sb) + rs * k, f4{0.f, 0.f, 0.f, 0.f});
     }
 }
 
@@ -482,6 +548,8 @@ template <bool LIN>
 __device__ __forceinline__ int tile_rescale_after(int lo, int m) {
     if (!LIN) return m >= 5 && m / 4 >= lo ? m / 4 : 0;
     if (m >= 12 && lo <= 4) return 4;
+    if (m > 32 && lo <= 12) return 12;
+    if (m > 64 && m / 4 >= lo) return m / 4;
     if (m > 24 && m / 2 >= lo) return m / 2;
     return 0;
 }
@@ -536,13 +604,13 @@ __device__ __forceinline__ Growth tile_growth(const Tile &x, int D) {
 // call for: linear domain, minus the midpoint of the mean and the largest,
 // which keeps the largest values further from float32's limit; log domain,
 // minus the mean.  Left in table `which`; add: on top of what it holds.
-template <bool LIN>
-__device__ __forceinline__ void growth_shift(const Io_ctx &cx, char *sm, int blocks, int which) {
+template <bool LIN, typename CX>
+__device__ __forceinline__ void growth_shift(const CX &cx, int blocks, int which) {
     const int gl = this_thread() & 15, S = cx.S;
     for (int sb = this_thread() >> 4; sb < S; sb += (int)blockDim.x >> 4) {
         float mx = NEG, sum = 0.f, c = 0.f;
         for (int I = gl; I < blocks; I += 16) {
-            const f4 p = ld4(sm, cx.part + 16 * (I * S + sb));
+            const f4 p = ld4(cx.tb, cx.part + 16 * (I * S + sb));
             mx = __builtin_fmaxf(mx, p[0]);
             sum += p[1];
             c += p[2];
@@ -551,7 +619,7 @@ __device__ __forceinline__ void growth_shift(const Io_ctx &cx, char *sm, int blo
         sum = row_sum(sum);
         c = row_sum(c);
         if (gl == 0)
-            tab<float>(sm, cx, which, sb) = c > 0.f ? (LIN ? -0.5f * (mx + sum / c) : -sum / c) : 0.f;
+            tab<float>(cx, which, sb) = c > 0.f ? (LIN ? -0.5f * (mx + sum / c) : -sum / c) : 0.f;
     }
 }
 
@@ -559,26 +627,26 @@ __device__ __forceinline__ void growth_shift(const Io_ctx &cx, char *sm, int blo
 // growth per node of each sentence is estimated from its tiles of diagonal
 // t0, and the finished values move to the problem with every non-forced score
 // shifted by delta.
-template <bool LIN, bool REV>
-__device__ void tile_rescale(const Io_ctx &cx, char *sm, int t0) {
+template <bool LIN, bool REV, typename CX>
+__device__ void tile_rescale(const CX &cx, char *sm, int t0) {
     typedef Dom<LIN> Dm;
     const int m = cx.m, S = cx.S, tid = this_thread(), NT = (int)blockDim.x;
     for (int f = tid; f < (m - t0) * S; f += NT) {
-        const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, at = I * cx.rpb + (f + t0 * S) * 64, rt = cx.rot(f);
+        const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, at = cx.a(I, I + t0, f - I * S), rt = cx.rot(f);
         Tile x;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const f4 v = ld4(sm, at + (((r + rt) & 3) << 4));
+            const f4 v = ld4(sm, at + ((r + rt) & 3) * cx.rs(t0));
 #pragma unroll
             for (int c = 0; c < 4; ++c) x.v[r][c] = v[c];
         }
         const Growth g = tile_growth<LIN>(x, t0);
-        st4(sm, cx.part + 16 * f, f4{g.mx, g.sum, g.cnt, 0.f});
+        st4(cx.tb, cx.part + 16 * f, f4{g.mx, g.sum, g.cnt, 0.f});
     }
     __syncthreads();
-    growth_shift<LIN>(cx, sm, m - t0, kTabDl);
+    growth_shift<LIN>(cx, m - t0, kTabDl);
     __syncthreads();
-    auto move_tile = [&](int at, int rt, int at2, int rt2, float dl, float base, float dir) {
+    auto move_tile = [&](int at, int rt, int at2, int rt2, int rs, float dl, float base, float dir) {
         // row r, column c of the tile at `at` moves by dl (base + dir (c - r)); copied transposed to at2
         Tile x;
         float fac[7];
@@ -589,14 +657,14 @@ __device__ void tile_rescale(const Io_ctx &cx, char *sm, int t0) {
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const f4 v = ld4(sm, at + (((r + rt) & 3) << 4));
+            const f4 v = ld4(sm, at + ((r + rt) & 3) * rs);
 #pragma unroll
             for (int c = 0; c < 4; ++c) x.v[r][c] = Dm::mul(v[c], fac[c - r + 3]);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            st4(sm, at + (((k + rt) & 3) << 4), f4{x.v[k][0], x.v[k][1], x.v[k][2], x.v[k][3]});
-            if (at2 >= 0) st4(sm, at2 + (((k + rt2) & 3) << 4), f4{x.v[0][k], x.v[1][k], x.v[2][k], x.v[3][k]});
+            st4(sm, at + ((k + rt) & 3) * rs, f4{x.v[k][0], x.v[k][1], x.v[k][2], x.v[k][3]});
+            if (at2 >= 0) st4(sm, at2 + ((k + rt2) & 3) * rs, f4{x.v[0][k], x.v[1][k], x.v[2][k], x.v[3][k]});
         }
     };
     // a wavefront per tile diagonal
@@ -605,8 +673,8 @@ __device__ void tile_rescale(const Io_ctx &cx, char *sm, int t0) {
         const int cnt = (m - D) * S;
         for (int f = lane; f < cnt; f += 64) {
             const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * S, J = I + D, gj = f + D * S;
-            const float dl = tab<float>(sm, cx, kTabDl, sb);
-            move_tile(I * cx.rpb + gj * 64, cx.rot(f), D > 0 ? cx.qo + J * cx.rpb + f * 64 : -1, cx.rot(gj), dl,
+            const float dl = tab<float>(cx, kTabDl, sb);
+            move_tile(cx.a(I, J, sb), cx.rot(f), D > 0 ? cx.at(I, J, sb) : -1, cx.rot(gj), cx.rs(D), dl,
                       (float)(4 * D - 1), 1.f);
         }
     }
@@ -615,14 +683,14 @@ __device__ void tile_rescale(const Io_ctx &cx, char *sm, int t0) {
             const int cnt = (m - D) * S;
             for (int f = lane; f < cnt; f += 64) {
                 const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * S, J = I + D, gj = f + D * S;
-                const float dl = tab<float>(sm, cx, kTabDl, sb);
-                const int n = tab<int>(sm, cx, kTabN, sb);
+                const float dl = tab<float>(cx, kTabDl, sb);
+                const int n = tab<int>(cx, kTabN, sb);
                 // (cells past the sentence hold zero; their factor may be anything finite)
-                move_tile(cx.qo + I * cx.rpb + gj * 64, cx.rot(f), J * cx.rpb + f * 64, cx.rot(gj), dl,
+                move_tile(cx.o(I, J, sb), cx.rot(f), cx.ot(I, J, sb), cx.rot(gj), cx.rs(D), dl,
                           (float)(n - 4 * D), -1.f);
             }
         }
-    for (int sb = tid; sb < S; sb += NT) tab<float>(sm, cx, kTabD, sb) += tab<float>(sm, cx, kTabDl, sb);
+    for (int sb = tid; sb < S; sb += NT) tab<float>(cx, kTabD, sb) += tab<float>(cx, kTabDl, sb);
     __syncthreads();
 }
 
@@ -631,25 +699,27 @@ __device__ void tile_rescale(const Io_ctx &cx, char *sm, int t0) {
 // number of trees), the mean over the scores near it: block I's figure is
 // over the spans of tile (I,I+1), near-forbidden scores left out, words and
 // the root too; the sentence's shift takes away their mean.
-__device__ void tile_seed(const Io_ctx &cx, char *sm) {
+template <typename CX>
+__device__ void tile_seed(const CX &cx, char *sm) {
     const int m = cx.m, S = cx.S, tid = this_thread(), NT = (int)blockDim.x;
     for (int f = tid; f < m * S; f += NT) {
         const int I = S > 1 ? (int)__umulhi((uint32_t)f, cx.mag) : f, sb = f - I * S;
-        const int n = tab<int>(sm, cx, kTabN, sb), ri = cx.rot(f), rc = n - 4 * (m - 1);
-        const int at = I * cx.rpb + f * 64, at1 = I + 1 < m ? at + S * 64 : at;   // tiles (I,I), (I,I+1)
+        const int n = tab<int>(cx, kTabN, sb), ri = cx.rot(f), rc = n - 4 * (m - 1);
+        const int at = cx.a(I, I, sb), at1 = I + 1 < m ? cx.a(I, I + 1, sb) : at;
+        const int rs0 = cx.rs(0), rs1 = I + 1 < m ? cx.rs(1) : rs0;
         f4 a[4], b[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            a[r] = ld4(sm, at + (((r + ri) & 3) << 4));
-            b[r] = ld4(sm, at1 + (((r + ri) & 3) << 4));
+            a[r] = ld4(sm, at + ((r + ri) & 3) * rs0);
+            b[r] = ld4(sm, at1 + ((r + ri) & 3) * rs1);
         }
-        const f4 z = ld4(sm, ((m - 1) * S + sb) * 64 + (ri << 4));   // (row 0 of the root's tile, for I = 0)
+        const f4 z = ld4(sm, cx.a(0, m - 1, sb) + cx.rot(sb) * cx.rs(m - 1));   // (row 0 of the root's tile, for I = 0)
         double fs = 4 * I + 1 <= n ? (double)a[0][1] : 0.0;
         fs += 4 * I + 2 <= n ? (double)a[1][2] : 0.0;
         fs += 4 * I + 3 <= n ? (double)a[2][3] : 0.0;
         fs += I + 1 < m ? (double)b[3][0] : 0.0;
         fs += I == 0 && n >= 2 ? (double)(rc == 0 ? z[0] : rc == 1 ? z[1] : rc == 2 ? z[2] : z[3]) : 0.0;
-        *reinterpret_cast<double *>(sm + cx.partd + 8 * f) = fs;
+        *reinterpret_cast<double *>(cx.tb + cx.partd + 8 * f) = fs;
         b[3][0] = NEG;
         if (m <= 2 && I == 0)   // the root
 #pragma unroll
@@ -669,15 +739,15 @@ __device__ void tile_seed(const Io_ctx &cx, char *sm) {
                 cnt += b[r][c] > -700.f ? 1.f : 0.f;
             }
         const bool some = cnt > 0.f && (m == 1 || I + 1 < m);
-        st4(sm, cx.part + 16 * f, f4{0.f, some ? mx * LOG2E_F + fast_log2(sum) - fast_log2(cnt) + 2.f : 0.f, some ? 1.f : 0.f, 0.f});
+        st4(cx.tb, cx.part + 16 * f, f4{0.f, some ? mx * LOG2E_F + fast_log2(sum) - fast_log2(cnt) + 2.f : 0.f, some ? 1.f : 0.f, 0.f});
     }
     __syncthreads();
-    growth_shift<false>(cx, sm, m, kTabD);
+    growth_shift<false>(cx, m, kTabD);
     for (int sb = tid >> 4; sb < S; sb += NT >> 4) {   // a 16-lane row per sentence, in a fixed order
         double fs = 0.0;
-        for (int I = tid & 15; I < m; I += 16) fs += *reinterpret_cast<const double *>(sm + cx.partd + 8 * (I * S + sb));
+        for (int I = tid & 15; I < m; I += 16) fs += *reinterpret_cast<const double *>(cx.tb + cx.partd + 8 * (I * S + sb));
         fs = row_sum(fs);
-        if ((tid & 15) == 0) *reinterpret_cast<double *>(sm + cx.forced + 8 * sb) = fs;
+        if ((tid & 15) == 0) *reinterpret_cast<double *>(cx.tb + cx.forced + 8 * sb) = fs;
     }
     __syncthreads();
 }
@@ -721,21 +791,21 @@ __device__ __forceinline__ f4 load_row(const float *sent, int N1, int i, int J, 
 // Inside (+ marginals) of a bundle: the tile form of inside_block_impl, same
 // outputs.  Returns false, having written no output, when a linear-domain
 // value leaves float32's range.
-template <bool LIN, bool REV, bool GOLD>
-__device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int32_t *rec, char *sm,
+template <bool LIN, bool REV, bool GOLD, bool GLOB>
+__device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int32_t *rec, char *sm, char *lds,
                                                  const float *__restrict__ scores, const float *__restrict__ grad,
                                                  float *__restrict__ logZ, float *__restrict__ marg,
                                                  const int32_t *__restrict__ gold, float *__restrict__ loss) {
     typedef Dom<LIN> Dm;
     __shared__ int ovf;
     const int tid = this_thread(), NT = (int)blockDim.x, N1 = p.n1;
-    const Io_ctx cx = io_ctx(rec);
+    const Io_ctx<GLOB> cx = io_ctx<GLOB>(rec, lds);
     const int m = cx.m, S = cx.S;
     for (int sb = tid; sb < S; sb += NT) {
         const int id = rec[kTrHeader + 2 * sb];
-        tab<int>(sm, cx, kTabId, sb) = id;
-        tab<int>(sm, cx, kTabN, sb) = rec[kTrHeader + 2 * sb + 1];
-        tab<float>(sm, cx, kTabG, sb) = grad ? grad[id] : 1.0f;
+        tab<int>(cx, kTabId, sb) = id;
+        tab<int>(cx, kTabN, sb) = rec[kTrHeader + 2 * sb + 1];
+        tab<float>(cx, kTabG, sb) = grad ? grad[id] : 1.0f;
     }
     if (tid == 0) ovf = 0;
     __syncthreads();
@@ -749,23 +819,25 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
 #pragma unroll
         for (int u = 0; u < kTilePieces; ++u) {
             const typename Row_walk::At a = rw.at(t0 + u * NT);
-            piece[u] = load_row(scores + (size_t)tab<int>(sm, cx, kTabId, a.sb) * sent_stride, N1, 4 * a.I + a.r, a.J,
-                                tab<int>(sm, cx, kTabN, a.sb));
+            piece[u] = load_row(scores + (size_t)tab<int>(cx, kTabId, a.sb) * sent_stride, N1, 4 * a.I + a.r, a.J,
+                                tab<int>(cx, kTabN, a.sb));
         }
     };
-    load_pieces(tid);
+    for (int c0 = tid; c0 < rw.total; c0 += NT * kTilePieces) {   // (one round in LDS)
+    load_pieces(c0);
 #pragma unroll
     for (int u = 0; u < kTilePieces; ++u) {
-        const typename Row_walk::At a = rw.at(tid + u * NT);
-        const int n = tab<int>(sm, cx, kTabN, a.sb), i = 4 * a.I + a.r, j0 = 4 * a.J, g = a.I * S + a.sb;
+        const typename Row_walk::At a = rw.at(c0 + u * NT);
+        const int n = tab<int>(cx, kTabN, a.sb), i = 4 * a.I + a.r, j0 = 4 * a.J, g = a.I * S + a.sb;
         f4 x;
 #pragma unroll
         for (int c = 0; c < 4; ++c) x[c] = j0 + c > i && j0 + c <= n ? piece[u][c] : NEG;
-        const int off = a.I * cx.rpb + (a.J * S + a.sb) * 64 + (((a.r + cx.rot(g)) & 3) << 4);
+        const int rr = ((a.r + cx.rot(g)) & 3) * cx.rs(a.J - a.I);
         if (a.ok) {
-            st4(sm, off, x);
-            if constexpr (REV) st4(sm, cx.qo + off, x);
+            st4(sm, cx.a(a.I, a.J, a.sb) + rr, x);
+            if constexpr (REV) st4(sm, cx.o(a.I, a.J, a.sb) + rr, x);
         }
+    }
     }
     __syncthreads();
     tile_seed(cx, sm);
@@ -797,31 +869,31 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
 
     // The scores again, for the epilogue: in flight during the roots' sums.
     const int tid_e = here_lane(tid);   // (the walk again too, not kept across the sweep)
-    if constexpr (REV) load_pieces(tid_e);
+    if constexpr (REV && !GLOB) load_pieces(tid_e);
 
     // The roots.
     auto root_of = [&](int sb) {
-        const int rc = tab<int>(sm, cx, kTabN, sb) - 4 * (m - 1);
-        return *reinterpret_cast<const float *>(sm + ((m - 1) * S + sb) * 64 + (cx.rot(sb) << 4) + 4 * rc);
+        const int rc = tab<int>(cx, kTabN, sb) - 4 * (m - 1);
+        return *reinterpret_cast<const float *>(sm + cx.a(0, m - 1, sb) + cx.rot(sb) * cx.rs(m - 1) + 4 * rc);
     };
     for (int sb = tid; sb < S; sb += NT) {
         const float r = root_of(sb);
         if constexpr (LIN)
             if (!(r >= kLinMin) || !(r <= kLinMax)) ovf = 1;
-        tab<float>(sm, cx, kTabLz, sb) = Dm::log2(r);
+        tab<float>(cx, kTabLz, sb) = Dm::log2(r);
     }
     __syncthreads();
     if constexpr (LIN)
         if (ovf) return false;
     auto log_z = [&](int sb) {
-        const int n = tab<int>(sm, cx, kTabN, sb);
+        const int n = tab<int>(cx, kTabN, sb);
         const float r = root_of(sb);
         const double lr = LIN ? log2_split(r) : (double)r;
-        return (lr - (double)tab<float>(sm, cx, kTabD, sb) * (n >= 2 ? n - 2 : 0)) * LN2_D +
-               *reinterpret_cast<const double *>(sm + cx.forced + 8 * sb);
+        return (lr - (double)tab<float>(cx, kTabD, sb) * (n >= 2 ? n - 2 : 0)) * LN2_D +
+               *reinterpret_cast<const double *>(cx.tb + cx.forced + 8 * sb);
     };
     if (logZ != nullptr)
-        for (int sb = tid; sb < S; sb += NT) logZ[tab<int>(sm, cx, kTabId, sb)] = (float)log_z(sb);
+        for (int sb = tid; sb < S; sb += NT) logZ[tab<int>(cx, kTabId, sb)] = (float)log_z(sb);
     if constexpr (!REV) return true;
 
     if constexpr (GOLD) {
@@ -830,7 +902,7 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
         // nothing reads any more (diagonal tiles: below their diagonal).
         const int R = 2 * (N1 - 1) - 1, lane = tid & 63;
         for (int sb = wave; sb < S; sb += nw) {
-            const int id = tab<int>(sm, cx, kTabId, sb), n = tab<int>(sm, cx, kTabN, sb);
+            const int id = tab<int>(cx, kTabId, sb), n = tab<int>(cx, kTabN, sb);
             const int32_t *g2 = gold + (size_t)id * R * 2;
             double acc = 0.0;
             for (int r = lane; r < 2 * n - 1; r += 64) {
@@ -838,8 +910,7 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
                 if (0 <= i && i < j && j <= n) {
                     acc += (double)scores[(size_t)id * sent_stride + (size_t)i * N1 + j];
                     const int g = (j >> 2) * S + sb;
-                    *reinterpret_cast<int *>(sm + (j >> 2) * cx.rpb + ((i >> 2) * S + sb) * 64 +
-                                             (((j + cx.rot(g)) & 3) << 4) + 4 * (i & 3)) = kGoldMark;
+                    *reinterpret_cast<int *>(sm + cx.ot(i >> 2, j >> 2, sb) + ((j + cx.rot(g)) & 3) * cx.rs((j >> 2) - (i >> 2)) + 4 * (i & 3)) = kGoldMark;
                 }
             }
 #pragma unroll
@@ -852,16 +923,18 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
     // Epilogue: the marginals row piece by row piece,
     //   mu(i,j) = g exp2(alpha~(i,j) + O'(i,j) - (s(i,j) + d) - alpha~(0,n)),
     // and exactly g on forced spans.
+    for (int c0 = tid_e; c0 < rw.total; c0 += NT * kTilePieces) {
+    if constexpr (GLOB) load_pieces(c0);
 #pragma unroll
     for (int u = 0; u < kTilePieces; ++u) {
-        const typename Row_walk::At a = rw.at(tid_e + u * NT);
-        const int sb = a.sb, n = tab<int>(sm, cx, kTabN, sb), id = tab<int>(sm, cx, kTabId, sb);
+        const typename Row_walk::At a = rw.at(c0 + u * NT);
+        const int sb = a.sb, n = tab<int>(cx, kTabN, sb), id = tab<int>(cx, kTabId, sb);
         const int i = 4 * a.I + a.r, j0 = 4 * a.J, gi = a.I * S + sb;
         if (!a.ok || i >= n) continue;
-        const int off = a.I * cx.rpb + (a.J * S + sb) * 64 + (((a.r + cx.rot(gi)) & 3) << 4);
-        const f4 al = ld4(sm, off), ou = ld4(sm, cx.qo + off);
-        const float d = tab<float>(sm, cx, kTabD, sb), g = tab<float>(sm, cx, kTabG, sb);
-        const float lz = tab<float>(sm, cx, kTabLz, sb);
+        const int rr = ((a.r + cx.rot(gi)) & 3) * cx.rs(a.J - a.I);
+        const f4 al = ld4(sm, cx.a(a.I, a.J, sb) + rr), ou = ld4(sm, cx.o(a.I, a.J, sb) + rr);
+        const float d = tab<float>(cx, kTabD, sb), g = tab<float>(cx, kTabG, sb);
+        const float lz = tab<float>(cx, kTabLz, sb);
         f4 mu;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -872,8 +945,8 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
             mu[c] = forced ? g : g * x;
             if constexpr (GOLD) {
                 const int gj = a.J * S + sb;
-                const int mk = *reinterpret_cast<const int *>(sm + a.J * cx.rpb + gi * 64 +
-                                                              (((c + cx.rot(gj)) & 3) << 4) + 4 * a.r);
+                const int mk = *reinterpret_cast<const int *>(sm + cx.ot(a.I, a.J, sb) +
+                                                              ((c + cx.rot(gj)) & 3) * cx.rs(a.J - a.I) + 4 * a.r);
                 if (mk == kGoldMark && j > i) mu[c] -= g;
             }
         }
@@ -886,18 +959,19 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
                 if (j0 + c > i && j0 + c <= n) out[c] = mu[c];
         }
     }
+    }
     return true;
 }
 
-template <bool REV, bool GOLD = false>
-__device__ __forceinline__ void tile_inside(const KernelPlan &p, const int32_t *rec, char *sm,
+template <bool REV, bool GOLD = false, bool GLOB = false>
+__device__ __forceinline__ void tile_inside(const KernelPlan &p, const int32_t *rec, char *sm, char *lds,
                                             const float *__restrict__ scores, const float *__restrict__ grad,
                                             float *__restrict__ logZ, float *__restrict__ marg,
                                             const int32_t *__restrict__ gold = nullptr,
                                             float *__restrict__ loss = nullptr) {
-    if (tile_inside_impl<true, REV, GOLD>(p, rec, sm, scores, grad, logZ, marg, gold, loss)) return;
+    if (tile_inside_impl<true, REV, GOLD, GLOB>(p, rec, sm, lds, scores, grad, logZ, marg, gold, loss)) return;
     __syncthreads();   // every thread has left the linear attempt
-    tile_inside_impl<false, REV, GOLD>(p, rec, sm, scores, grad, logZ, marg, gold, loss);
+    tile_inside_impl<false, REV, GOLD, GLOB>(p, rec, sm, lds, scores, grad, logZ, marg, gold, loss);
 }
 
 // ---------------------------------------------------------------------------
@@ -911,7 +985,11 @@ __device__ __forceinline__ void tile_inside(const KernelPlan &p, const int32_t *
 // 16-byte pieces (row r, columns 0-1 and 2-3), entry f = I*S + sb, so that
 // consecutive lanes read consecutive pieces; then 16 bytes of splits
 // (k - 4 I) per tile.
+// GLOB: the chart in the workspace, one sentence, splits in 16 bits each.
+template <bool GLOB>
 struct Ck_ctx {
+    static constexpr bool kGlob = GLOB;
+    static constexpr int kSplitTile = GLOB ? 32 : 16, kNone = GLOB ? 0xFFFF : 0xFF;
     int m, S, split, tab;
     uint32_t mag;
     __device__ __forceinline__ int cnt(int D) const { return (m - D) * S; }
@@ -920,19 +998,20 @@ struct Ck_ctx {
     __device__ __forceinline__ int plane0(int D, int f) const { return before(D) * 128 + f * 16; }
     __device__ __forceinline__ int stride(int D) const { return cnt(D) * 16; }
 };
-__device__ __forceinline__ Ck_ctx ck_ctx(const int32_t *rec) {
-    Ck_ctx c;
+template <bool GLOB>
+__device__ __forceinline__ Ck_ctx<GLOB> ck_ctx(const int32_t *rec) {
+    Ck_ctx<GLOB> c;
     c.m = rec[kTrM];
-    c.S = rec[kTrCount];
+    c.S = GLOB ? 1 : rec[kTrCount];
     c.mag = (uint32_t)rec[kTrMagic];
     c.split = c.before(c.m) * 128;
-    c.tab = c.before(c.m) * 144;
+    c.tab = GLOB ? 0 : c.before(c.m) * 144;
     return c;
 }
 
 typedef double d2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ d2 ldd(const char *sm, int off) { return *reinterpret_cast<const d2 *>(sm + off); }
-__device__ __forceinline__ void std2(char *sm, int off, d2 v) { *reinterpret_cast<d2 *>(sm + off) = v; }
+__device__ __forceinline__ d2 ldd(const char *sm, int off) { return *reinterpret_cast<const d2 *>(sm + (uint32_t)off); }
+__device__ __forceinline__ void std2(char *sm, int off, d2 v) { *reinterpret_cast<d2 *>(sm + (uint32_t)off) = v; }
 
 // Running maximum of a span's splits and the first split (from 4 I) at it.
 // The choice of the split goes through the sign of a difference (exact in
@@ -963,21 +1042,21 @@ __device__ __forceinline__ void take_first(Best &b, double t, int k) {   // t >=
 constexpr double kNoSplit = -1.0e300;
 // Over lanes with different splits of one span: the higher value, the lower
 // split among equals.
-template <int CTRL>
+template <int CTRL, int NONE>
 __device__ __forceinline__ void best_level(Best (&b)[4]) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const double v = dpp_d<CTRL>(b[c].v);
         const int k = dpp_i<CTRL>(b[c].k);
         const double m = fmax(b[c].v, v);
-        b[c].k = min(b[c].k | (neg_mask(b[c].v - m) & 255), k | (neg_mask(v - m) & 255));
+        b[c].k = min(b[c].k | (neg_mask(b[c].v - m) & NONE), k | (neg_mask(v - m) & NONE));
         b[c].v = m;
     }
 }
 // The same across the rows of 16 lanes (WIDE: the 32-lane halves): the swap of
 // a value with itself leaves one row's value in one result, the other's in the
 // other.
-template <bool WIDE>
+template <bool WIDE, int NONE>
 __device__ __forceinline__ void best_swap(Best (&b)[4]) {
     typedef uint32_t u2 __attribute__((ext_vector_type(2)));
     auto swap = [](uint32_t v) -> u2 {
@@ -991,7 +1070,7 @@ __device__ __forceinline__ void best_swap(Best (&b)[4]) {
         const double v0 = __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]);
         const double v1 = __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
         const double m = fmax(v0, v1);
-        b[c].k = min((int)k[0] | (neg_mask(v0 - m) & 255), (int)k[1] | (neg_mask(v1 - m) & 255));
+        b[c].k = min((int)k[0] | (neg_mask(v0 - m) & NONE), (int)k[1] | (neg_mask(v1 - m) & NONE));
         b[c].v = m;
     }
 }
@@ -1014,7 +1093,8 @@ __device__ __forceinline__ void cky_row(Best (&b)[4], const d2 (&L)[2], const d2
     }
 }
 
-__device__ __forceinline__ void cky_tile_task(const Ck_ctx &cx, char *sm, int D, int w, int lg) {
+template <typename CX>
+__device__ __forceinline__ void cky_tile_task(const CX &cx, char *sm, int D, int w, int lg) {
     D = here(D);
     w = here(w);
     lg = here(lg);
@@ -1065,32 +1145,32 @@ __device__ __forceinline__ void cky_tile_task(const Ck_ctx &cx, char *sm, int D,
         // one row's products, the next tiles in flight during each
         const Best none{kNoSplit, 0};
         Best b[4] = {none, none, none, none};
+        constexpr int kAhead = 2;
         struct Ops {
             d2 L[2], R[4][2];
-        } o0, o1;
+        } op[kAhead];
         const int g = lg - 2, iters = (np + (1 << g) - 1) >> g;   // 2^g lanes per row
         auto load = [&](Ops &o, int it) {
             const int kk = min(1 + q + (it << g), np);
             load_l(o.L, kk, row);
             load_r(o.R, kk);
         };
-        auto use = [&](const Ops &o, int it) {
-            const int kk = 1 + q + (it << g);
-            if (kk <= np) cky_row(b, o.L, o.R, 4 * kk);
-        };
-        load(o0, 0);
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j)
+            if (j < iters) load(op[j], j);
 #pragma unroll 1
-        for (int it = 0; it < iters; it += 2) {
-            if (it + 1 < iters) load(o1, it + 1);
-            use(o0, it);
-            if (it + 1 >= iters) break;
-            if (it + 2 < iters) load(o0, it + 2);
-            use(o1, it + 1);
-        }
-        if (g >= 1) best_level<kRor8>(b);
-        if (g >= 2) best_level<kRor4>(b);
-        if (g >= 3) best_swap<false>(b);
-        if (g >= 4) best_swap<true>(b);
+        for (int i0 = 0; i0 < iters; i0 += kAhead)
+#pragma unroll
+            for (int j = 0; j < kAhead; ++j) {
+                const int it = i0 + j, kk = 1 + q + (it << g);
+                if (it >= iters) break;
+                if (kk <= np) cky_row(b, op[j].L, op[j].R, 4 * kk);
+                if (it + kAhead < iters) load(op[j], it + kAhead);
+            }
+        if (g >= 1) best_level<kRor8, CX::kNone>(b);
+        if (g >= 2) best_level<kRor4, CX::kNone>(b);
+        if (g >= 3) best_swap<false, CX::kNone>(b);
+        if (g >= 4) best_swap<true, CX::kNone>(b);
         auto rows = [&](auto rr) {   // row rr from the lane of each four that holds it
             constexpr int R = decltype(rr)::value, ctrl = R * 0x55;
 #pragma unroll
@@ -1111,12 +1191,12 @@ __device__ __forceinline__ void cky_tile_task(const Ck_ctx &cx, char *sm, int D,
     double U[4][4], V[4][4];   // above the diagonal
     auto diag = [&](double (&T)[4][4], int a) {
         const d2 a1 = ldd(sm, a + s0), b1 = ldd(sm, a + 3 * s0);
-        T[0][1] = *reinterpret_cast<const double *>(sm + a + 8);
+        T[0][1] = *reinterpret_cast<const double *>(sm + (uint32_t)(a + 8));
         T[0][2] = a1[0];
         T[0][3] = a1[1];
         T[1][2] = b1[0];
         T[1][3] = b1[1];
-        T[2][3] = *reinterpret_cast<const double *>(sm + a + 5 * s0 + 8);
+        T[2][3] = *reinterpret_cast<const double *>(sm + (uint32_t)(a + 5 * s0 + 8));
     };
     diag(U, u);
     diag(V, v);
@@ -1156,31 +1236,41 @@ __device__ __forceinline__ void cky_tile_task(const Ck_ctx &cx, char *sm, int D,
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int h = 0; h < 2; ++h) std2(sm, at + (2 * r + h) * st, d2{x[r][2 * h], x[r][2 * h + 1]});
-        uint4 pk;
-        uint32_t *pq = &pk.x;
+        uint32_t pk[8];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            pq[r] = (uint32_t)best[r][0].k | (uint32_t)best[r][1].k << 8 | (uint32_t)best[r][2].k << 16 |
-                    (uint32_t)best[r][3].k << 24;
-        *reinterpret_cast<uint4 *>(sm + cx.split + (cx.before(D) + f) * 16) = pk;
+        for (int r = 0; r < 4; ++r) {
+            const Best(&q)[4] = best[r];
+            if constexpr (CX::kGlob) {
+                pk[2 * r] = (uint32_t)q[0].k | (uint32_t)q[1].k << 16;
+                pk[2 * r + 1] = (uint32_t)q[2].k | (uint32_t)q[3].k << 16;
+            } else {
+                pk[r] = (uint32_t)q[0].k | (uint32_t)q[1].k << 8 | (uint32_t)q[2].k << 16 | (uint32_t)q[3].k << 24;
+            }
+        }
+        uint4 *const out = reinterpret_cast<uint4 *>(sm + cx.split + (cx.before(D) + f) * CX::kSplitTile);
+        out[0] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+        if constexpr (CX::kGlob) out[1] = make_uint4(pk[4], pk[5], pk[6], pk[7]);
     }
 }
 
 // The split of span (i, j), two words or more, of sentence sb.
-__device__ __forceinline__ int tile_split(const Ck_ctx &cx, const char *sm, int sb, int i, int j) {
+template <typename CX>
+__device__ __forceinline__ int tile_split(const CX &cx, const char *sm, int sb, int i, int j) {
     const int I = i >> 2, D = (j >> 2) - I;
     const int t = cx.before(D) + I * cx.S + sb;
-    const int k = 4 * I + (int)*reinterpret_cast<const uint8_t *>(sm + cx.split + t * 16 + 4 * (i & 3) + (j & 3));
+    typedef typename std::conditional<CX::kGlob, uint16_t, uint8_t>::type SP;
+    const int k = 4 * I + (int)reinterpret_cast<const SP *>(sm + cx.split + t * CX::kSplitTile)[4 * (i & 3) + (j & 3)];
     return max(i + 1, min(k, j - 1));   // (already so, unless a score was not finite)
 }
 
-__device__ __forceinline__ void tile_cky(const KernelPlan &p, const int32_t *rec, char *sm,
+template <bool GLOB = false>
+__device__ __forceinline__ void tile_cky(const KernelPlan &p, const int32_t *rec, char *sm, char *lds,
                                          const float *__restrict__ scores, int32_t *__restrict__ spans,
                                          float *__restrict__ best) {
     const int tid = this_thread(), NT = (int)blockDim.x, N1 = p.n1;
-    const Ck_ctx cx = ck_ctx(rec);
+    const Ck_ctx<GLOB> cx = ck_ctx<GLOB>(rec);
     const int m = cx.m, S = cx.S;
-    int *const ids = reinterpret_cast<int *>(sm + cx.tab), *const ns = ids + S;
+    int *const ids = reinterpret_cast<int *>(lds + cx.tab), *const ns = ids + S;
     for (int sb = tid; sb < S; sb += NT) {
         ids[sb] = rec[kTrHeader + 2 * sb];
         ns[sb] = rec[kTrHeader + 2 * sb + 1];
@@ -1219,7 +1309,9 @@ __device__ __forceinline__ void tile_cky(const KernelPlan &p, const int32_t *rec
         Best b{a0[1] + x13, 1};
         take(b, x02 + c1[1], 2);
         const double x03 = b.v + a1[1];
-        *reinterpret_cast<uint4 *>(sm + cx.split + f * 16) = make_uint4(1u << 16 | (uint32_t)b.k << 24, 2u << 24, 0u, 0u);
+        uint4 *const out = reinterpret_cast<uint4 *>(sm + cx.split + f * Ck_ctx<GLOB>::kSplitTile);
+        if constexpr (GLOB) out[0] = make_uint4(0u, 1u | (uint32_t)b.k << 16, 0u, 2u << 16);
+        else out[0] = make_uint4(1u << 16 | (uint32_t)b.k << 24, 2u << 24, 0u, 0u);
         std2(sm, at + s0, d2{x02, x03});
         std2(sm, at + 3 * s0, d2{b1[0], x13});
     }
@@ -1279,20 +1371,20 @@ template <bool REV>
 CRF_TILE_KERNEL tile_inside_kernel(KernelPlan p, const float *__restrict__ scores, const float *__restrict__ grad,
                                    float *__restrict__ logZ, float *__restrict__ marg) {
     extern __shared__ __align__(16) char smem_raw[];
-    tile_inside<REV>(p, p.tile_io.recs + (size_t)blockIdx.x * p.tile_stride, smem_raw, scores, grad, logZ, marg);
+    tile_inside<REV>(p, p.tile_io.recs + (size_t)blockIdx.x * p.tile_stride, smem_raw, smem_raw, scores, grad, logZ, marg);
 }
 
 CRF_TILE_KERNEL tile_loss_kernel(KernelPlan p, const float *__restrict__ scores, const int32_t *__restrict__ gold,
                                  const float *__restrict__ grad, float *__restrict__ loss, float *__restrict__ marg) {
     extern __shared__ __align__(16) char smem_raw[];
-    tile_inside<true, true>(p, p.tile_io.recs + (size_t)blockIdx.x * p.tile_stride, smem_raw, scores, grad, nullptr,
+    tile_inside<true, true>(p, p.tile_io.recs + (size_t)blockIdx.x * p.tile_stride, smem_raw, smem_raw, scores, grad, nullptr,
                             marg, gold, loss);
 }
 
 CRF_TILE_KERNEL tile_cky_kernel(KernelPlan p, const float *__restrict__ scores, int32_t *__restrict__ spans,
                                 float *__restrict__ best) {
     extern __shared__ __align__(16) char smem_raw[];
-    tile_cky(p, p.tile_ck.recs + (size_t)blockIdx.x * p.tile_stride, smem_raw, scores, spans, best);
+    tile_cky(p, p.tile_ck.recs + (size_t)blockIdx.x * p.tile_stride, smem_raw, smem_raw, scores, spans, best);
 }
 
 // Inside with the marginals and CKY in one launch, bundles of both merged.
@@ -1301,8 +1393,8 @@ CRF_TILE_KERNEL tile_parse_kernel(KernelPlan p, const float *__restrict__ scores
                                   float *__restrict__ best) {
     extern __shared__ __align__(16) char smem_raw[];
     const int32_t *rec = p.tile_mix.recs + (size_t)blockIdx.x * p.tile_stride;
-    if (rec[kTrKind] == kKindInside) tile_inside<true>(p, rec, smem_raw, scores, grad, logZ, marg);
-    else tile_cky(p, rec, smem_raw, scores, spans, best);
+    if (rec[kTrKind] == kKindInside) tile_inside<true>(p, rec, smem_raw, smem_raw, scores, grad, logZ, marg);
+    else tile_cky(p, rec, smem_raw, smem_raw, scores, spans, best);
 }
 
 // MBR decoding: a bundle's marginals, then CKY over them (read back by the
@@ -1311,9 +1403,58 @@ CRF_TILE_KERNEL tile_mbr_kernel(KernelPlan p, const float *__restrict__ scores, 
                                 int32_t *__restrict__ spans, float *__restrict__ best) {
     extern __shared__ __align__(16) char smem_raw[];
     const int32_t *rec = p.tile_io.recs + (size_t)blockIdx.x * p.tile_stride;
-    tile_inside<true>(p, rec, smem_raw, scores, nullptr, logZ, marg);
+    tile_inside<true>(p, rec, smem_raw, smem_raw, scores, nullptr, logZ, marg);
     __syncthreads();   // the marginals are written and the charts are free
-    tile_cky(p, rec, smem_raw, marg, spans, best);
+    tile_cky(p, rec, smem_raw, smem_raw, marg, spans, best);
+}
+
+#define CRF_TILE_WS_KERNEL __global__ __launch_bounds__(kTileThreadsWs) void
+
+// The same on charts in the workspace, for sentences past LDS: a workgroup per
+// sentence and pass, record 2 b of the b-th longest sentence its inside pass,
+// 2 b + 1 its CKY (their charts are disjoint, so that the fused launch runs
+// both side by side).  Bound by the stages' products, whose tiles come from L2
+// (a sentence's charts are 0.9 MB at 256 words): 64 sentences of 256 words
+// fused 1,709 -> 540 us, a lone one 1,095 -> 493 (the kernels that take a width a
+// step, on teams of 16 workgroups).  1,024 threads were slower (635 us), and so
+// were three products' loads in flight instead of one or two.
+__device__ __forceinline__ const int32_t *ws_record(const KernelPlan &p, int b) {
+    return p.tile_ws.recs + (size_t)b * (kTrHeader + 2);
+}
+__device__ __forceinline__ char *ws_chart(const KernelPlan &p, const int32_t *rec) {
+    return p.ws + (size_t)rec[kTrPitch] * 256;
+}
+
+template <bool REV>
+CRF_TILE_WS_KERNEL tile_ws_inside_kernel(KernelPlan p, const float *__restrict__ scores, const float *__restrict__ grad,
+                                      float *__restrict__ logZ, float *__restrict__ marg) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const int32_t *rec = ws_record(p, 2 * (int)blockIdx.x);
+    tile_inside<REV, false, true>(p, rec, ws_chart(p, rec), smem_raw, scores, grad, logZ, marg);
+}
+
+CRF_TILE_WS_KERNEL tile_ws_loss_kernel(KernelPlan p, const float *__restrict__ scores, const int32_t *__restrict__ gold,
+                                    const float *__restrict__ grad, float *__restrict__ loss,
+                                    float *__restrict__ marg) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const int32_t *rec = ws_record(p, 2 * (int)blockIdx.x);
+    tile_inside<true, true, true>(p, rec, ws_chart(p, rec), smem_raw, scores, grad, nullptr, marg, gold, loss);
+}
+
+CRF_TILE_WS_KERNEL tile_ws_cky_kernel(KernelPlan p, const float *__restrict__ scores, int32_t *__restrict__ spans,
+                                   float *__restrict__ best) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const int32_t *rec = ws_record(p, 2 * (int)blockIdx.x + 1);
+    tile_cky<true>(p, rec, ws_chart(p, rec), smem_raw, scores, spans, best);
+}
+
+CRF_TILE_WS_KERNEL tile_ws_parse_kernel(KernelPlan p, const float *__restrict__ scores, const float *__restrict__ grad,
+                                     float *__restrict__ logZ, float *__restrict__ marg, int32_t *__restrict__ spans,
+                                     float *__restrict__ best) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const int32_t *rec = ws_record(p, (int)blockIdx.x);
+    if (rec[kTrKind] == kKindInside) tile_inside<true, false, true>(p, rec, ws_chart(p, rec), smem_raw, scores, grad, logZ, marg);
+    else tile_cky<true>(p, rec, ws_chart(p, rec), smem_raw, scores, spans, best);
 }
 
 }  // namespace
@@ -1331,6 +1472,17 @@ hipError_t set_tile_attributes(int max_lds_bytes) {
 
 hipError_t launch_tile_inside(const KernelPlan &p, const float *scores, const float *grad, float *logZ, float *marg,
                               hipStream_t stream) {
+    if (p.tile_ws.n > 0) {
+        const dim3 grid(p.tile_ws.n), block(kTileThreadsWs);
+        const size_t lds = (size_t)p.tile_ws.lds_bytes;
+        if (marg != nullptr)
+            hipLaunchKernelGGL(tile_ws_inside_kernel<true>, grid, block, lds, stream, p, scores, grad, logZ, marg);
+        else
+            hipLaunchKernelGGL(tile_ws_inside_kernel<false>, grid, block, lds, stream, p, scores, grad, logZ, marg);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (p.tile_io.n == 0) return hipSuccess;
     const dim3 grid(p.tile_io.n), block(p.tile_threads);
     const size_t lds = (size_t)p.tile_io.lds_bytes;
     if (marg != nullptr)
@@ -1341,23 +1493,54 @@ hipError_t launch_tile_inside(const KernelPlan &p, const float *scores, const fl
 }
 hipError_t launch_tile_loss(const KernelPlan &p, const float *scores, const int32_t *gold, const float *grad,
                             float *loss, float *grad_scores, hipStream_t stream) {
+    if (p.tile_ws.n > 0) {
+        hipLaunchKernelGGL(tile_ws_loss_kernel, dim3(p.tile_ws.n), dim3(kTileThreadsWs), (size_t)p.tile_ws.lds_bytes, stream,
+                           p, scores, gold, grad, loss, grad_scores);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (p.tile_io.n == 0) return hipSuccess;
     hipLaunchKernelGGL(tile_loss_kernel, dim3(p.tile_io.n), dim3(p.tile_threads), (size_t)p.tile_io.lds_bytes, stream,
                        p, scores, gold, grad, loss, grad_scores);
     return hipGetLastError();
 }
 hipError_t launch_tile_cky(const KernelPlan &p, const float *scores, int32_t *spans, float *best, hipStream_t stream) {
+    if (p.tile_ws.n > 0) {
+        hipLaunchKernelGGL(tile_ws_cky_kernel, dim3(p.tile_ws.n), dim3(kTileThreadsWs), (size_t)p.tile_ws.lds_bytes, stream,
+                           p, scores, spans, best);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (p.tile_io.n == 0) return hipSuccess;
     hipLaunchKernelGGL(tile_cky_kernel, dim3(p.tile_ck.n), dim3(p.tile_threads), (size_t)p.tile_ck.lds_bytes, stream, p,
                        scores, spans, best);
     return hipGetLastError();
 }
 hipError_t launch_tile_parse(const KernelPlan &p, const float *scores, const float *grad, float *logZ, float *marg,
                              int32_t *spans, float *best, hipStream_t stream) {
+    if (p.tile_ws.n > 0) {
+        hipLaunchKernelGGL(tile_ws_parse_kernel, dim3(2 * p.tile_ws.n), dim3(kTileThreadsWs), (size_t)p.tile_ws.lds_bytes, stream,
+                           p, scores, grad, logZ, marg, spans, best);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (p.tile_io.n == 0) return hipSuccess;
     hipLaunchKernelGGL(tile_parse_kernel, dim3(p.tile_mix.n), dim3(p.tile_threads), (size_t)p.tile_mix.lds_bytes, stream,
                        p, scores, grad, logZ, marg, spans, best);
     return hipGetLastError();
 }
 hipError_t launch_tile_mbr(const KernelPlan &p, const float *scores, float *logZ, float *marg, int32_t *spans,
                            float *best, hipStream_t stream) {
+    if (p.tile_ws.n > 0) {   // the marginals, then CKY over them
+        hipLaunchKernelGGL(tile_ws_inside_kernel<true>, dim3(p.tile_ws.n), dim3(kTileThreadsWs),
+                           (size_t)p.tile_ws.lds_bytes, stream, p, scores, nullptr, logZ, marg);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(tile_ws_cky_kernel, dim3(p.tile_ws.n), dim3(kTileThreadsWs), (size_t)p.tile_ws.lds_bytes,
+                           stream, p, marg, spans, best);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (p.tile_io.n == 0) return hipSuccess;
     hipLaunchKernelGGL(tile_mbr_kernel, dim3(p.tile_io.n), dim3(p.tile_threads), (size_t)p.tile_io.lds_bytes, stream, p,
                        scores, logZ, marg, spans, best);
     return hipGetLastError();

@@ -39,6 +39,11 @@ CASES = {
     # to 7e-5 at sd 12, on this chart and on the one-width-a-step one.)
     "log_domain_6": dict(lengths=[6, 25, 26, 27, 27, 60, 110], sd=6.0),
     "log_domain_10": dict(lengths=[6, 25, 26, 27, 27, 60, 99], sd=10.0),
+    # charts in the workspace beside bundles in LDS: one block past LDS, splits
+    # past 8 bits, the rescales of long sentences
+    "workspace": dict(lengths=[140, 143, 255, 256, 260, 30]),
+    # too many long sentences for teams, and one of more than 400 words
+    "workspace_many": dict(lengths=[150] * 16 + [402], sd=1.0),
     # scores of a trained model: one tree's spans far above the rest
     "planted": dict(lengths=[8, 25, 26, 50, 99, 130], sd=1.0, plant=9.0),
 }
@@ -59,8 +64,10 @@ def make(lengths, seed=0, sd=2.0, n1=None, integer=None, forbid=0.0, plant=0.0):
     return b
 
 
-@pytest.mark.parametrize("name", sorted(CASES))
-def test_tile_charts(name):
+@pytest.mark.parametrize("name,flags", [(n, 0) for n in sorted(CASES)] + [
+    (n, B.CRF_FORCE_SPILL) for n in ("block_edges", "rescale_and_half_cu", "ties", "near_forbidden", "log_domain_6",
+                                     "planted")])
+def test_tile_charts(name, flags):
     import torch
 
     b = make(seed=60 + len(name), **CASES[name])
@@ -72,7 +79,7 @@ def test_tile_charts(name):
     lz_ref, mu_ref = orc.marginals(b.scores, b.lengths, grad=grad, threads=16)
     sp_ref, be_ref = orc.cky(b.scores, b.lengths, threads=16)
     valid = W.valid_mask(b.lengths, b.n1)
-    with B.Plan(b.lengths, n1=b.n1, device=dev) as plan:
+    with B.Plan(b.lengths, n1=b.n1, flags=flags, device=dev) as plan:
         mu = torch.full_like(s, 7.5)
         lz, mu, sp, be = plan.parse(s, grad_logZ=g, marginals=mu)
         lzf = plan.inside_fwd(s)
