@@ -11,7 +11,12 @@
 // Design.  A workgroup (four wavefronts) takes a tile of kBiaRows rows (left
 // fence posts) and kBiaCols columns (right fence posts) -- short sentences
 // packed whole into one tile (their scores are the tile's diagonal blocks),
-// longer ones cut into row and column blocks -- and one label.  For each
+// longer ones cut into row and column blocks -- and up to kBiaLabels labels, one
+// after the other with the tile's rows kept in registers.  The label groups of
+// a tile are neighbours on one XCD (each XCD takes a contiguous share of the
+// work), so the r^r they share and the lines of the scores they write (a
+// span's labels are adjacent) meet in one L2.  138 labels of 100 sentences at
+// d = 100, with the labelling stage: 109.8 -> 98.4 us.  For each label and
 // chunk of kBiaChunk of the d output dimensions of W it computes
 // U = [R^l ; 1] W[:, chunk] on MFMA with K = d+1 split four ways: wavefront w
 // keeps the tile's 64 rows over its quarter of K (with the 1 and the zero
@@ -32,6 +37,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "crf_internal.h"
@@ -46,6 +52,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPad = 8;                       // bf16 of padding per staged row (keeps 16-byte reads conflict-free)
 constexpr int kUStride = kBiaChunk + kPad;    // row stride of the staged U and R^r chunks
 constexpr int kPStride = kBiaChunk + 4;       // row stride (floats) of the staged partial sums of U
+constexpr int kBiaLabels = 8;                 // most labels a workgroup takes
 constexpr int kNM = kBiaChunk / 16;           // 16-column blocks of U in a chunk
 constexpr int kNN = kBiaRows / 16;            // 16-row blocks of the tile
 
@@ -96,8 +103,8 @@ __device__ __forceinline__ uint32_t keep_word(int k, int d) {
 constexpr int kRAhead = 3;   // chunks of r^r in flight
 template <int KS, int P>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void biaffine_kernel(
-    const int32_t *__restrict__ tiles, const int32_t *__restrict__ len, int N1, int d, int ldw, int L,
-    const uint16_t *__restrict__ rl, const uint16_t *__restrict__ rr, const uint16_t *__restrict__ w,
+    const int32_t *__restrict__ tiles, const int32_t *__restrict__ len, int N1, int d, int ldw, int L, int n_work,
+    int groups, int per_group, const uint16_t *__restrict__ rl, const uint16_t *__restrict__ rr, const uint16_t *__restrict__ w,
     float *__restrict__ scores) {
     static_assert(KS % 4 == 0, "K splits four ways");
     constexpr int KQ = KS / 4;               // steps of this wavefront's quarter of K
@@ -111,9 +118,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     int32_t *Ob = reinterpret_cast<int32_t *>(Ul + kBiaRows * kUStride);   // [kBiaRows + kBiaCols]
     int32_t *Oi = Ob + kBiaRows + kBiaCols;                                // [kBiaRows + kBiaCols]
     int32_t *On = Oi + kBiaRows + kBiaCols;                                // [kBiaRows]
-    const int32_t *rec = tiles + (size_t)blockIdx.x * (kBiaRows + kBiaCols);
-    const int l = blockIdx.y;
-    const uint16_t *wl = w + (size_t)l * d * ldw;
+    // Workgroup b runs on XCD b mod 8 (dealt in turn); each XCD takes a
+    // contiguous share of the work, a tile's label groups side by side: a
+    // cell's labels are neighbours in memory, and lines written by several
+    // workgroups meet in one L2.
+    const int per_xcd = (n_work + 7) >> 3;
+    const int work = groups > 1 ? ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+    if (work >= n_work) return;
+    const int tile = groups > 1 ? work / groups : work, l0 = (work - tile * groups) * per_group;
+    const int l1 = min(l0 + per_group, L);
+    const int32_t *rec = tiles + (size_t)tile * (kBiaRows + kBiaCols);
+    const uint16_t *wl = w + (size_t)l0 * d * ldw;
 
     // Issue the first W chunk's loads before anything waits.
     uint4 wf[kNM][KQ];
@@ -134,11 +149,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int cid = rec[kBiaRows + sj];
     const uint16_t *crow = rr + (size_t)(cid >= 0 ? cid : 0) * d;
     uint2 rn[kRAhead][2];
+    auto load_first_rr = [&]() {
 #pragma unroll
-    for (int a = 0; a < kRAhead; ++a)
+        for (int a = 0; a < kRAhead; ++a)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-            rn[a][h] = *reinterpret_cast<const uint2 *>(crow + min(kBiaChunk * a + sk + 4 * h, d - 4));
+            for (int h = 0; h < 2; ++h)
+                rn[a][h] = *reinterpret_cast<const uint2 *>(crow + min(kBiaChunk * a + sk + 4 * h, d - 4));
+    };
+    load_first_rr();
 
     // The tile's rows [r^l_i ; 1 ; 0 ...] over this wavefront's quarter of K
     // as MFMA fragments, in registers for the whole tile: row 16 n + lane%16,
@@ -178,6 +196,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (tid < kBiaRows) On[tid] = len[b >= 0 ? b : 0];
     }
 
+    // A label at a time: the tile's rows stay in registers.
+    for (int l = l0; l < l1; ++l) {
+    if (l > l0) {
+        wl += (size_t)d * ldw;
+        load_wq<KQ, P>(wf, wl, 0, d, ldw, kq0, lane);
+        load_first_rr();
+    }
     f32x4 acc[kBiaCols / 16];   // S rows 16 wave + 4 (lane/16) + t, columns 16 c + lane%16
 #pragma unroll
     for (int c = 0; c < kBiaCols / 16; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -282,6 +307,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             if (b == Ob[q] && i < j && j <= n) scores[(((size_t)b * N1 + i) * N1 + j) * L + l] = acc[c][t];
         }
     }
+    }
 }
 
 }  // namespace
@@ -304,31 +330,37 @@ int64_t biaffine_lds_bytes(int) {
 }
 
 template <int P>
-static void launch_biaffine_p(const KernelPlan &p, dim3 grid, size_t lds, hipStream_t stream, const uint16_t *rl,
-                              const uint16_t *rr, const uint16_t *w, int d, int ldw, int L, float *scores) {
-    const dim3 block(256);
+static void launch_biaffine_p(const KernelPlan &p, int n_work, int groups, int per_group, size_t lds,
+                              hipStream_t stream, const uint16_t *rl, const uint16_t *rr, const uint16_t *w, int d,
+                              int ldw, int L, float *scores) {
+    const dim3 grid(groups > 1 ? (n_work + 7) / 8 * 8 : n_work), block(256);
     const int kp = bia_kp(d);
     if (kp == 128)
-        hipLaunchKernelGGL((biaffine_kernel<4, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L, rl,
-                           rr, w, scores);
+        hipLaunchKernelGGL((biaffine_kernel<4, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L,
+                           n_work, groups, per_group, rl, rr, w, scores);
     else if (kp == 256)
-        hipLaunchKernelGGL((biaffine_kernel<8, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L, rl,
-                           rr, w, scores);
+        hipLaunchKernelGGL((biaffine_kernel<8, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L,
+                           n_work, groups, per_group, rl, rr, w, scores);
     else
-        hipLaunchKernelGGL((biaffine_kernel<16, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L, rl,
-                           rr, w, scores);
+        hipLaunchKernelGGL((biaffine_kernel<16, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L,
+                           n_work, groups, per_group, rl, rr, w, scores);
 }
 
 hipError_t launch_biaffine(const KernelPlan &p, const uint16_t *rl, const uint16_t *rr, const uint16_t *w, int d,
                            int ldw, int L, float *scores, hipStream_t stream) {
     if (p.n_bia_tiles < 1) return hipSuccess;
     const size_t lds = (size_t)biaffine_lds_bytes(d);
-    const dim3 grid(p.n_bia_tiles, L);
+    // Labels per workgroup: enough workgroups for a few per CU slot first (two
+    // slots a CU), then up to kBiaLabels, so that a tile's rows are loaded and
+    // its records decoded once for several labels.
+    const int64_t all = (int64_t)p.n_bia_tiles * L;
+    const int per_group = (int)std::min<int64_t>(kBiaLabels, std::max<int64_t>(1, all / 2048));
+    const int groups = (L + per_group - 1) / per_group, n_work = p.n_bia_tiles * groups;
     // 16-byte W pieces when every row starts 16-byte aligned
     if (ldw % 8 == 0 && ((uintptr_t)w & 15) == 0)
-        launch_biaffine_p<8>(p, grid, lds, stream, rl, rr, w, d, ldw, L, scores);
+        launch_biaffine_p<8>(p, n_work, groups, per_group, lds, stream, rl, rr, w, d, ldw, L, scores);
     else
-        launch_biaffine_p<4>(p, grid, lds, stream, rl, rr, w, d, ldw, L, scores);
+        launch_biaffine_p<4>(p, n_work, groups, per_group, lds, stream, rl, rr, w, d, ldw, L, scores);
     return hipGetLastError();
 }
 

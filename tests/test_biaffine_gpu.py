@@ -95,3 +95,12 @@ def test_biaffine_row_strides(torch, d, ldw, labels):
     # widths: 16-byte pieces when ldw is a multiple of 8, 8-byte ones else
     inp = W.biaffine_inputs([1, 9, 40, 66], d, labels=labels, seed=ldw)
     check(run(torch, inp, ldw=ldw), inp)
+
+
+@pytest.mark.parametrize("d,ldw", [(100, 104), (100, 108), (4, 8), (124, 128), (128, 132)])
+def test_biaffine_label_groups(torch, d, ldw):
+    # enough tiles and labels that a workgroup takes several labels (three
+    # or four here), a number of labels that the groups do not divide, and a
+    # number of groups that the XCDs do not share evenly
+    inp = W.biaffine_inputs([70, 61, 62, 63] * 8 + [130, 9], d, labels=137, seed=d + ldw)
+    check(run(torch, inp, ldw=ldw), inp)
