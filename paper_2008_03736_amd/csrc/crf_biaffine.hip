@@ -62,8 +62,8 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t *p) {
 }
 __device__ __forceinline__ bf16x8 frag(const uint4 &v) { return __builtin_bit_cast(bf16x8, v); }
 
-// K of the first product: d + 1 padded to 128, 256 or 512.
-__host__ __device__ inline int bia_kp(int d) { return d + 1 <= 128 ? 128 : d + 1 <= 256 ? 256 : 512; }
+// K of the split first product (d > kBiaSmallD): d + 1 padded to 256 or 512.
+__host__ __device__ inline int bia_kp(int d) { return d + 1 <= 256 ? 256 : 512; }
 
 // This wavefront's A fragments of one chunk: W^T rows c0 + 16 m + lane%16
 // (clamped to row d-1: the columns of U past d meet zero r^r entries), K
@@ -99,7 +99,7 @@ __device__ __forceinline__ uint32_t keep_word(int k, int d) {
 
 // Tile record: kBiaRows row ids then kBiaCols column ids, each b * N1 + i
 // (sentence b, fence post i) or -1.  KS = K / 32 steps of the first product
-// (K = d + 1 padded to 128, 256 or 512); each wavefront takes KS / 4 of them.
+// (K = d + 1 padded to 256 or 512); each wavefront takes KS / 4 of them.
 constexpr int kRAhead = 3;   // chunks of r^r in flight
 template <int KS, int P>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void biaffine_kernel(
@@ -310,15 +310,184 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 }
 
+// Representations of up to kBiaSmallD dimensions (label scorers): K = d + 1
+// fits in 128, so a wavefront takes its sixteen rows over all of K and nothing
+// of U leaves it.  A label's whole W sits in LDS (the next label's in registers
+// meanwhile), as do the tile's r^r for every label: two barriers a label, where
+// biaffine_kernel's split of K takes three per 32 columns (16,000 cycles a
+// label at d = 100, most of them the partial sums' way through LDS and the
+// barriers, for 32 products a wavefront).  138 labels of 100 sentences at
+// d = 100, with the labelling stage: 98.4 -> 76.6 us.  U's way from one product's
+// layout to the other's goes through the wavefront's own rows of LDS, whose
+// accesses a wavefront sees in order.
+constexpr int kBiaSmallD = 124;
+constexpr int kWStride = 128 + kPad;   // row stride of the staged W and r^r
+__host__ __device__ inline int small_rows(int d) { return (d + kBiaChunk - 1) / kBiaChunk * kBiaChunk; }
+inline int64_t small_lds_bytes(int d) {
+    return 2 * ((small_rows(d) + kBiaCols) * (int64_t)kWStride + 2 * kBiaRows * (int64_t)kUStride) +
+           4 * (2 * (kBiaRows + kBiaCols) + kBiaRows);
+}
+
+template <int P>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void biaffine_small_kernel(
+    const int32_t *__restrict__ tiles, const int32_t *__restrict__ len, int N1, int d, int ldw, int L, int n_work,
+    int groups, int per_group, const uint16_t *__restrict__ rl, const uint16_t *__restrict__ rr,
+    const uint16_t *__restrict__ w, float *__restrict__ scores) {
+    constexpr int KS = 4, kPieces = 128 * 128 / 8 / 256;   // steps of K; pieces of W a thread stages
+    extern __shared__ __align__(16) char smem_raw[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rows = small_rows(d);
+    uint16_t *Ws = reinterpret_cast<uint16_t *>(smem_raw);   // [rows][kWStride]: W^T of the label
+    uint16_t *Rs = Ws + rows * kWStride;                     // [kBiaCols][kWStride]: r^r of the columns
+    uint16_t *Uh = Rs + kBiaCols * kWStride + wave * 2 * 16 * kUStride;   // [16][kUStride]: this wavefront's U hi
+    uint16_t *Ul = Uh + 16 * kUStride;                                    // and lo
+    int32_t *Ob = reinterpret_cast<int32_t *>(Rs + kBiaCols * kWStride + 2 * kBiaRows * kUStride);
+    int32_t *Oi = Ob + kBiaRows + kBiaCols, *On = Oi + kBiaRows + kBiaCols;
+    const int per_xcd = (n_work + 7) >> 3;   // (the work's order: see biaffine_kernel)
+    const int work = groups > 1 ? ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+    if (work >= n_work) return;
+    const int tile = groups > 1 ? work / groups : work, l0 = (work - tile * groups) * per_group;
+    const int l1 = min(l0 + per_group, L);
+    const int32_t *rec = tiles + (size_t)tile * (kBiaRows + kBiaCols);
+
+    // A label's W: 16 pieces of eight a row, rows clamped to d - 1 (they meet
+    // zero r^r entries), pieces to the one that holds k = d.
+    uint4 wr[kPieces];
+    const int dp = d - d % P;
+    auto load_w = [&](int l) {
+        const uint16_t *wl = w + (size_t)l * d * ldw;
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int q = tid + 256 * i, k = 8 * (q & 15);
+            const uint16_t *row = wl + (size_t)min(q >> 4, d - 1) * ldw;
+            if constexpr (P == 8) {
+                wr[i] = *reinterpret_cast<const uint4 *>(row + min(k, dp));
+            } else {
+                const uint2 a = *reinterpret_cast<const uint2 *>(row + min(k, dp));
+                const uint2 b = *reinterpret_cast<const uint2 *>(row + min(k + 4, dp));
+                wr[i] = make_uint4(a.x, a.y, b.x, b.y);
+            }
+        }
+    };
+    load_w(l0);
+
+    {   // r^r: thread t stages column t/4, dimensions 8 (t%4) + 32 i .. +7
+        const int cid = rec[kBiaRows + (tid >> 2)];
+        const uint16_t *crow = rr + (size_t)(cid >= 0 ? cid : 0) * d;
+        uint2 v[KS][2];
+#pragma unroll
+        for (int i = 0; i < KS; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                v[i][h] = *reinterpret_cast<const uint2 *>(crow + min(32 * i + 8 * (tid & 3) + 4 * h, d - 4));
+#pragma unroll
+        for (int i = 0; i < KS; ++i)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = 32 * i + 8 * (tid & 3) + 4 * h;
+                *reinterpret_cast<uint2 *>(Rs + (tid >> 2) * kWStride + k) = cid >= 0 && k < d ? v[i][h] : make_uint2(0u, 0u);
+            }
+    }
+    uint4 rf[KS];   // this wavefront's rows [r^l ; 1 ; 0 ...] as fragments
+    {
+        const int id = rec[16 * wave + (lane & 15)];
+        const uint16_t *row = rl + (size_t)(id >= 0 ? id : 0) * d;
+        uint2 v[KS][2];
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                v[s][h] = *reinterpret_cast<const uint2 *>(row + min(32 * s + 8 * (lane >> 4) + 4 * h, d - 4));
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            uint2 q[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int k = 32 * s + 8 * (lane >> 4) + 4 * h;
+                q[h] = id >= 0 && k < d ? v[s][h] : make_uint2(0u, 0u);
+                if (k == d) q[h].x = 0x3F80u;   // the appended 1
+            }
+            rf[s] = make_uint4(q[0].x, q[0].y, q[1].x, q[1].y);
+        }
+    }
+    if (tid < kBiaRows + kBiaCols) {
+        const int id = rec[tid], b = id >= 0 ? id / N1 : tid < kBiaRows ? -1 : -2;
+        Ob[tid] = b;
+        Oi[tid] = id - b * N1;
+        if (tid < kBiaRows) On[tid] = len[b >= 0 ? b : 0];
+    }
+
+    for (int l = l0; l < l1; ++l) {
+        __syncthreads();   // the last label's readers of Ws are done
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int q = tid + 256 * i, k = 8 * (q & 15);
+            if ((q >> 4) < rows)
+                *reinterpret_cast<uint4 *>(Ws + (q >> 4) * kWStride + k) =
+                    make_uint4(wr[i].x & keep_word(k, d), wr[i].y & keep_word(k + 2, d), wr[i].z & keep_word(k + 4, d),
+                               wr[i].w & keep_word(k + 6, d));
+        }
+        if (l + 1 < l1) load_w(l + 1);
+        __syncthreads();
+
+        f32x4 acc[kBiaCols / 16];   // S rows 16 wave + 4 (lane/16) + t, columns 16 c + lane%16
+#pragma unroll
+        for (int c = 0; c < kBiaCols / 16; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int c0 = 0; c0 < rows; c0 += kBiaChunk) {
+            // U^T[chunk][this wavefront's rows], to bf16 hi + lo
+            f32x4 u[kNM];
+#pragma unroll
+            for (int m = 0; m < kNM; ++m) u[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int m = 0; m < kNM; ++m)
+                    u[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        frag(Ws + (c0 + 16 * m + (lane & 15)) * kWStride + 32 * s + 8 * (lane >> 4)), frag(rf[s]), u[m],
+                        0, 0, 0);
+#pragma unroll
+            for (int m = 0; m < kNM; ++m) {
+                const bf16x4 hi = __builtin_convertvector(u[m], bf16x4);
+                const bf16x4 lo = __builtin_convertvector(u[m] - __builtin_convertvector(hi, f32x4), bf16x4);
+                const int at = (lane & 15) * kUStride + 16 * m + 4 * (lane >> 4);
+                *reinterpret_cast<bf16x4 *>(Uh + at) = hi;
+                *reinterpret_cast<bf16x4 *>(Ul + at) = lo;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const int urow = (lane & 15) * kUStride + 8 * (lane >> 4);
+            const bf16x8 ah = frag(Uh + urow), al = frag(Ul + urow);
+#pragma unroll
+            for (int c = 0; c < kBiaCols / 16; ++c) {
+                const bf16x8 br = frag(Rs + (16 * c + (lane & 15)) * kWStride + c0 + 8 * (lane >> 4));
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, br, acc[c], 0, 0, 0);
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, br, acc[c], 0, 0, 0);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int r = 16 * wave + 4 * (lane >> 4) + t;
+            const int b = Ob[r], i = Oi[r], n = On[r];
+#pragma unroll
+            for (int c = 0; c < kBiaCols / 16; ++c) {
+                const int q = kBiaRows + 16 * c + (lane & 15), j = Oi[q];
+                if (b == Ob[q] && i < j && j <= n) scores[(((size_t)b * N1 + i) * N1 + j) * L + l] = acc[c][t];
+            }
+        }
+    }
+}
+
 }  // namespace
 
 hipError_t set_biaffine_attributes() {
-    const void *fns[] = {(const void *)biaffine_kernel<4, 4>,  (const void *)biaffine_kernel<8, 4>,
-                         (const void *)biaffine_kernel<16, 4>, (const void *)biaffine_kernel<4, 8>,
-                         (const void *)biaffine_kernel<8, 8>,  (const void *)biaffine_kernel<16, 8>};
-    const int lds[] = {(int)biaffine_lds_bytes(127), (int)biaffine_lds_bytes(255), (int)biaffine_lds_bytes(kBiaMaxD)};
-    for (int k = 0; k < 6; ++k) {
-        const hipError_t e = hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, lds[k % 3]);
+    const void *fns[] = {(const void *)biaffine_kernel<8, 4>, (const void *)biaffine_kernel<16, 4>,
+                         (const void *)biaffine_kernel<8, 8>, (const void *)biaffine_kernel<16, 8>};
+    for (const void *f : fns) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)biaffine_lds_bytes(kBiaMaxD));
+        if (e != hipSuccess) return e;
+    }
+    const void *small[] = {(const void *)biaffine_small_kernel<4>, (const void *)biaffine_small_kernel<8>};
+    for (const void *f : small) {
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)small_lds_bytes(kBiaSmallD));
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -335,9 +504,11 @@ static void launch_biaffine_p(const KernelPlan &p, int n_work, int groups, int p
                               int ldw, int L, float *scores) {
     const dim3 grid(groups > 1 ? (n_work + 7) / 8 * 8 : n_work), block(256);
     const int kp = bia_kp(d);
-    if (kp == 128)
-        hipLaunchKernelGGL((biaffine_kernel<4, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L,
-                           n_work, groups, per_group, rl, rr, w, scores);
+    // K in one wavefront's registers and W in LDS, or K split over four (98.4
+    // and 76.6 us at d = 100)
+    if (d <= kBiaSmallD)
+        hipLaunchKernelGGL((biaffine_small_kernel<P>), grid, block, (size_t)small_lds_bytes(d), stream, p.bia_tiles, p.len,
+                           p.n1, d, ldw, L, n_work, groups, per_group, rl, rr, w, scores);
     else if (kp == 256)
         hipLaunchKernelGGL((biaffine_kernel<8, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L,
                            n_work, groups, per_group, rl, rr, w, scores);
@@ -352,7 +523,9 @@ hipError_t launch_biaffine(const KernelPlan &p, const uint16_t *rl, const uint16
     const size_t lds = (size_t)biaffine_lds_bytes(d);
     // Labels per workgroup: enough workgroups for a few per CU slot first (two
     // slots a CU), then up to kBiaLabels, so that a tile's rows are loaded and
-    // its records decoded once for several labels.
+    // its records decoded once for several labels (138 labels of 43 tiles at
+    // d = 100, with the labelling stage: 96 us at one label a workgroup, 77 at
+    // two, 76 at five).
     const int64_t all = (int64_t)p.n_bia_tiles * L;
     const int per_group = (int)std::min<int64_t>(kBiaLabels, std::max<int64_t>(1, all / 2048));
     const int groups = (L + per_group - 1) / per_group, n_work = p.n_bia_tiles * groups;
