@@ -502,6 +502,7 @@ struct KernelPlan {
     // workspace kernels of crf_kernels.hip take those); tile_scratch: the
     // workspace tile charts fit in the no-allocation scratch
     int32_t tile_on, tile_long, tile_scratch;
+    int32_t tile_cky;   // CKY alone too (see kTileCkyLen)
 };
 // Batches of at most kTileTeamCount sentences past LDS whose longest has more
 // than kTileTeamLen words leave those sentences to the workspace kernels'
@@ -509,6 +510,15 @@ struct KernelPlan {
 // sentence fused: 256 words 493 against 1,095 us in teams, 400 words 1,411
 // against about 1,530, 512 words 2,100 in teams).
 constexpr int kTileTeamCount = 16, kTileTeamLen = 400;
+// CKY alone, every sentence in LDS: tile charts when the longest has up to
+// this many words, a step per width past that.  A float64 tile's chain is as
+// long as its four width steps', so only the saved barriers of short charts
+// pay (us, a step per width and tiles): one sentence of 23 words 14.8 and
+// 13.3, 40 of 10 to 28 17.8 both, 300 of 10 to 32 20.95 and 21.2, 20 of 40 to
+// 60 36.3 and 38.1, 300 of up to 80 59.2 and 61.1, 8 of 110
+// to 130 104.2 and 112.1.  Beside the inside chain it is the other way round:
+// the fused and MBR launches stay on tiles.
+constexpr int kTileCkyLen = 28;
 // Bytes of a sentence's tile charts in the workspace: inside (alpha and O', each
 // also transposed) and CKY (chart and 16-bit splits).
 __host__ __device__ inline int64_t tile_ws_io_bytes(int m) { return 128 * (int64_t)m * (m + 1); }

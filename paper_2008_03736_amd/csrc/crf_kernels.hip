@@ -2194,14 +2194,14 @@ static hipError_t launch_cky_k(const KernelPlan &p, const float *scores, int32_t
                                hipStream_t stream, int32_t *labels) {
     const Schedule &q = p.cky;
     hipError_t e;
-    if (!LAB && p.tile_on) {
+    if (!LAB && p.tile_cky) {
         if ((e = launch_tile_cky(p, scores, spans, best, stream)) != hipSuccess) return e;
     } else if (q.n_bundles > 0) {
         hipLaunchKernelGGL((cky_kernel<false, LAB>), dim3(q.n_bundles), dim3(q.threads), (size_t)q.lds_bytes, stream, p,
                            scores, spans, best, labels);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (q.n_spill > 0 && !(p.tile_on && p.tile_long)) {
+    if (q.n_spill > 0 && !(p.tile_cky && p.tile_long)) {
         KernelPlan t = p;
         dim3 grid;
         if ((e = spill_launch_shape(t, q.n_spill, stream, &grid)) != hipSuccess) return e;

@@ -751,6 +751,8 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
         }
     }
 
+    kp.tile_cky = kp.tile_on && (max_len <= crf::kTileCkyLen || kp.tile_ws.n > 0 || !kp.tile_long);
+
     if ((e = upload(p, len, &kp.len)) != hipSuccess ||
         (e = upload(p, rec_in, &kp.inside.recs)) != hipSuccess ||
         (e = upload(p, si.spill, &kp.inside.order_spill)) != hipSuccess ||
