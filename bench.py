@@ -8,9 +8,10 @@ timing starts.  Prints one JSON line.
 
   python bench.py [--steps K] [--warmup W] [--workload mixed] [--no-cpu-baseline]
 
-Roofline: the hot path is one launch (parse_kernel: inside + marginal and CKY
-workgroups side by side).  It is bound by plain vector-ALU work and by the
-dependency chain of width steps, not by HBM and not by MFMA.  Algorithmic work
+Roofline: the hot path is one launch (tile_parse_kernel: inside + marginal and
+CKY workgroups side by side; sentences past LDS in a launch of their own,
+tile_ws_parse_kernel).  It is bound by plain vector-ALU work and by the
+dependency chain of stages, not by HBM and not by MFMA.  Algorithmic work
 per sentence of n words, with T(n) = (n+1)n(n-1)/6 split points and
 P(n) = n(n+1)/2 spans, in VALU issue slots, counting the marginals as a
 reverse-mode pass (the cheaper formulation; the kernel's outside pass does
@@ -52,14 +53,8 @@ HBM_PEAK = 8.0e12               # bytes per second
 # (else null).  `profile` names the committed
 # summary that holds the counters and the scaling.
 MEASURED_TRAFFIC = {
-    "mixed": {"bytes": 73.94e6, "source_sha16": "344d6a0b90f8641c",
-              "profile": "profiles/parse_kernel_mixed5000.txt"},
-    "longer": {"bytes": 32.44e6, "source_sha16": "344d6a0b90f8641c",
-               "profile": "profiles/parse_kernel_longer2000.txt"},
-    "labeled": {"bytes": 118.57e6, "source_sha16": "344d6a0b90f8641c",
-                "profile": "profiles/inside_kernel_labeled1000.txt"},
-    "stress": {"bytes": 4706.67e6, "source_sha16": "344d6a0b90f8641c",
-               "profile": "profiles/spill_kernels_stress64.txt"},
+    "mixed": {"bytes": 75.92e6, "source_sha16": "632dbc9c924a0723",
+              "profile": "profiles/tile_parse_kernel_mixed5000.txt"},
 }
 METRIC = "sentences/sec for inside fwd+bwd and CKY decode; % of binding roofline"
 
@@ -113,7 +108,7 @@ def source_sha16():
     import hashlib
 
     h = hashlib.sha256()
-    for name in ("crf_kernels.hip", "crf_internal.h", "crf_plan.cpp"):
+    for name in ("crf_kernels.hip", "crf_tile.hip", "crf_internal.h", "crf_plan.cpp"):
         with open(os.path.join(ROOT, "paper_2008_03736_amd", "csrc", name), encoding="utf-8") as f:
             h.update(strip_comments(f.read()).encode())
     return h.hexdigest()[:16]
@@ -426,7 +421,7 @@ def main():
     ach = slots / avg_s
     traffic, traffic_src = measured_traffic(batch.name)
     roof = {"bound": "alu",
-            "kernel": "parse_kernel (inside + marginals + CKY, one launch)" if decode
+            "kernel": "tile_parse_kernel (inside + marginals + CKY, one launch)" if decode
             else "inside_kernel (inside + marginals)",
             "achieved": round(ach / 1e12, 4), "peak": round(PEAK_SLOTS / 1e12, 3),
             "unit": "T VALU lane-slots/s", "frac": round(ach / PEAK_SLOTS, 5),

@@ -43,9 +43,11 @@
  *   257 KB area for the teams below; they are allocated by crf_plan_create
  *   and freed by crf_plan_destroy.  Compute calls allocate nothing.
  *
- *   Teams.  When a call has only a few workspace sentences (at most 32
- *   sentence passes in one launch), each pass runs on a team of 8 or 16
- *   workgroups of one XCD that wait for each other at every width step.
+ *   Teams.  When a call has only a few workspace sentences, each pass may run
+ *   on a team of 8 or 16 workgroups of one XCD that wait for each other at
+ *   every width step: unlabelled plans with at most 16 workspace sentences of
+ *   which one has more than 400 words, and calls of labelled plans with at
+ *   most 32 workspace sentence passes in one launch.
  *   Such a launch waits until all its workgroups are resident at once (it
  *   is sized to fit an otherwise idle device); work from other streams
  *   delays it.  A wait that lasts about 2^21 polls (a second or two) ends
@@ -296,8 +298,11 @@ int crf_biaffine_scores(const crf_plan *plan, const uint16_t *rl, const uint16_t
  * that clears the array's counter, then the launches of the fused call
  * (with one workgroup per workspace sentence pass: no teams).
  *   Returns CRF_EINVAL when the plan needs more workspace than the array
- *   holds (8 MiB less 256 bytes; crf_plan_info: workspace_bytes), e.g. a
- *   batch with many sentences longer than 142 words.
+ *   holds (8 MiB less 256 bytes), e.g. a batch with many sentences longer
+ *   than 142 words.  The need counted is that of the charts of single spans,
+ *   which can be less than crf_plan_info's workspace_bytes (that also covers
+ *   the charts in tiles of spans); a plan whose tile charts do not fit the
+ *   array runs on the charts of single spans.
  *   Every such call on one GPU shares that GPU's array, whatever the plan:
  *   calls of this entry point that overlap on one GPU race (issue them on
  *   one stream, or order them with events).
