@@ -443,6 +443,17 @@ __host__ __device__ inline int64_t tile_io_bytes(int m, int S, int pitch) {
 __host__ __device__ inline int64_t tile_ck_bytes(int m, int S) {
     return 144 * (int64_t)S * (m * (m + 1) / 2) + 8 * (int64_t)S;
 }
+// Row of tiles (byte offset from row 0) that a lane reads for a product of an
+// LDS tile: `off` the row of its it-th product, counted on past the last row,
+// `last` that of the tile's last product (a lane with none left reads that one
+// again: up to 15 rows on, it would leave the bundle's LDS), `lim` the bytes
+// of all rows.  Inside products end below the last row; outside ones wrap
+// round once (x - lim is huge, unsigned, where x needs no wrap).
+__host__ __device__ inline uint32_t tile_row_inside(uint32_t off, uint32_t last) { return off < last ? off : last; }
+__host__ __device__ inline uint32_t tile_row_outside(uint32_t off, uint32_t last, uint32_t lim) {
+    const uint32_t x = off < last ? off : last;
+    return x < x - lim ? x : x - lim;
+}
 struct TileSchedule {
     const int32_t *recs;
     int32_t n, lds_bytes;

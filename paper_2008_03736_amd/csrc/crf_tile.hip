@@ -346,7 +346,7 @@ __device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np,
         f4 x[4], y[4];
     } pr;
     const int bx = (OUT ? 0 : cx.qo) + gi * 64, by = (OUT ? cx.qo : 0) + gj * 64;
-    const int lim = m * cx.rpb, step = cx.rpb << lg;
+    const int lim = m * cx.rpb, step = cx.rpb << lg, last = ((OUT ? J : I) + np) * cx.rpb;
     int off = ((OUT ? J : I) + 1 + ls.q) * cx.rpb;
     auto load_at = [&](Pair &q, int ax, int rx, int ay, int ry) {
 #pragma unroll
@@ -355,7 +355,7 @@ __device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np,
             q.y[k] = ld4(sm, ay + ry * k);
         }
     };
-    auto load = [&](Pair &q, int it) {   // (a lane past its last product reads some tiles of the chart)
+    auto load = [&](Pair &q, int it) {   // (a lane past its last product reads the tile's last one again)
         if constexpr (CX::kGlob) {
             const int p = min(ls.q + (it << lg), np - 1);
             if constexpr (!OUT) {
@@ -370,7 +370,7 @@ __device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np,
                         cx.rs(right ? K - J : J - L));
             }
         } else {
-            const int o = off >= lim ? (OUT ? off - lim : 0) : off;
+            const int o = (int)(OUT ? tile_row_outside(off, last, lim) : tile_row_inside(off, last));
             load_at(q, bx + o, 16, by + o, 16);
             off += step;
         }

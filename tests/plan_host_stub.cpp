@@ -115,6 +115,52 @@ int main(int argc, char **argv) {
         std::printf("N %d %d\n", t.k, t.grid);
         return 0;
     }
+    if (std::strcmp(argv[1], "tilereads") == 0) {
+        // Every LDS read of the tile products, for every block count, bundle
+        // size and number of lanes per tile: X and Y tiles inside the two
+        // squares, and the row the product needs when the lane has one.
+        long reads = 0;
+        for (int m = 1; m <= crf::tile_blocks(crf::kTileMaxLen); ++m)
+            for (int S : {1, -1, 2, 3, 7, 64 / m + 1, crf::kTileThreads / m}) {   // (-1: one sentence, no padding)
+                if (S == 0) continue;
+                const int pitch = S < 0 ? m : crf::tile_pitch(m, S), rpb = 64 * pitch, qo = m * rpb;
+                S = S < 0 ? 1 : S;
+                for (int lg = 0; lg <= 4; ++lg)
+                    for (int t = 1; t < m; ++t)
+                        for (int out = 0; out <= 1; ++out) {
+                            const int D = out ? m - t : t, np = t - 1;
+                            for (int I = 0; I + D < m; ++I)
+                                for (int sb : {0, S - 1})
+                                    for (int q = 0; q < (1 << lg); ++q) {
+                                        const int J = I + D, first = (out ? J : I) + 1, iters = (np + (1 << lg) - 1) >> lg;
+                                        for (int it = 0; it < iters; ++it) {
+                                            const int p = q + (it << lg);
+                                            const uint32_t off = (uint32_t)((first + p) * rpb);
+                                            const uint32_t last = (uint32_t)((first + np - 1) * rpb);
+                                            const uint32_t o = out ? crf::tile_row_outside(off, last, (uint32_t)qo)
+                                                                   : crf::tile_row_inside(off, last);
+                                            const int gi = I * S + sb, gj = J * S + sb;
+                                            const long x = (out ? 0 : qo) + gi * 64 + (long)o;
+                                            const long y = (out ? qo : 0) + gj * 64 + (long)o;
+                                            ++reads;
+                                            if (x + 64 > 2L * qo || y + 64 > 2L * qo) {
+                                                std::printf("BAD m %d S %d lg %d stage %d out %d tile %d lane %d product %d of %d: "
+                                                            "byte %ld of %d\n", m, S, lg, t, out, I, q, p, np,
+                                                            std::max(x, y) + 63, 2 * qo);
+                                                return 1;
+                                            }
+                                            if (p < np && (long)o != (long)((first + p) % m) * rpb) {
+                                                std::printf("BAD row m %d S %d lg %d stage %d out %d product %d\n", m, S, lg, t,
+                                                            out, p);
+                                                return 1;
+                                            }
+                                        }
+                                    }
+                        }
+            }
+        std::printf("READS OK %ld\n", reads);
+        return 0;
+    }
     std::vector<int32_t> len;
     FILE *f = std::fopen(argv[1], "r");
     if (!f) return 2;

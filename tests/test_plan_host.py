@@ -186,6 +186,13 @@ def test_step_shape_runs(harness):
     assert res.returncode == 0 and res.stdout.strip() == "RUNS OK", res.stdout[-500:]
 
 
+def test_tile_products_read_inside_the_charts(harness):
+    # a lane that shares a tile and has no product left still loads: its
+    # reads, like those of real products, stay inside the bundle's two squares
+    res = subprocess.run([harness, "tilereads"], capture_output=True, text=True)
+    assert res.returncode == 0 and res.stdout.startswith("READS OK"), res.stdout[-500:]
+
+
 def test_team_launch_shapes(harness):
     # Every workspace launch shape: a team of k (a power of two in
     # [kTeamMinK, kTeamMaxK] = [8, 16]) per job, m = ceil(jobs / 8) teams per
