@@ -416,3 +416,33 @@ def test_fused_repeat_launches(torch, name):
     for lz, mu, sp, be in outs:
         assert torch.equal(lz, lz0) and torch.equal(mu, mu0)
         assert torch.equal(sp, sp0) and torch.equal(be, be0)
+
+
+# chart values reach some 2^9 (log2 units) where scores spread this far, and a
+# marginal's exponent takes about ten roundings of them: 10 * 2^-15 * ln 2
+LOG_DOMAIN_ATOL = 2.1e-4
+
+
+@pytest.mark.parametrize("labels,sd,lengths,seed,tol", [
+    (3, 7.0, [30, 40, 50, 60, 70, 80, 90, 100], 0, MARG_ATOL),
+    (2, 5.0, [30, 40, 50, 60, 70, 80, 90, 100], 3, MARG_ATOL),
+    (26, 10.0, [6, 25, 26, 40, 60, 75, 110, 130, 143, 160], 7, LOG_DOMAIN_ATOL),
+    # unlabelled, few long sentences and one past 400 words: teams
+    (1, 4.5, [402, 150, 180, 210, 240, 270, 300], 4, LOG_DOMAIN_ATOL),
+])
+def test_sums_lost_to_underflow(torch, labels, sd, lengths, seed, tol):
+    # scores spread so far that sums of the linear domain leave float32 below
+    # while every value and the root stay within its bounds: the log domain
+    # must take the bundle (without it, marginals are 0.01 to 110 off here)
+    b = W.custom(lengths, seed=seed, sd=sd, labels=labels)
+    out = gpu_run(torch, b, decode=False)
+    if labels > 1:
+        lz, mu = orc.labeled(b.scores, b.lengths, threads=ORACLE_THREADS)
+    else:
+        lz, mu = orc.marginals(b.scores, b.lengths, threads=ORACLE_THREADS)
+    check_logz(out["logZ"], lz)
+    check_logz(out["logZ_fwd"], lz)
+    v = W.valid_mask(b.lengths, b.n1)
+    if labels > 1:
+        v = np.broadcast_to(v[..., None], mu.shape)
+    assert np.max(np.abs(out["marg"][v] - mu[v])) <= tol
