@@ -593,29 +593,43 @@ __device__ __forceinline__ double row_sum(double v) {
 }
 
 // Growth of log2 alpha per node over a tile's spans (diagonal D >= 1): the
-// largest, the sum and the number of log2(x) / (w-1), spans of no value left
-// out.
+// largest, the sum and the number of log2(x) / (w-1).  Linear domain: spans of
+// no value left out.  Log domain: those more than kShiftBand below the tile's
+// largest, as growth_shift leaves out whole tiles: they hold near-forbidden
+// scores, whose share per node falls with the width (-1e4 in a span of 88
+// words is -166, and 5% of such spans moved the shift by 8 a node: marginals
+// of 350 words 1e-3 off, 1e-4 without them).
+constexpr float kShiftBand = 30.0f;
 struct Growth {
     float mx = NEG, sum = 0.f, cnt = 0.f;
 };
 template <bool LIN>
 __device__ __forceinline__ Growth tile_growth(const Tile &x, int D) {
     Growth g;
+    auto each = [&](auto &&f) {
 #pragma unroll
-    for (int j = -3; j <= 3; ++j) {
-        const int w = 4 * D + j;
-        const float inv = __builtin_amdgcn_rcpf((float)(w > 1 ? w - 1 : 1));
+        for (int j = -3; j <= 3; ++j) {
+            const int w = 4 * D + j;
+            const float inv = __builtin_amdgcn_rcpf((float)(w > 1 ? w - 1 : 1));
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int c = r + j;
-            if (c < 0 || c > 3) continue;
-            const float v = Dom<LIN>::log2(x.v[r][c]) * inv;
-            const bool in = v > -200.f && v < 200.f && w >= 2;
-            g.mx = in ? __builtin_fmaxf(g.mx, v) : g.mx;
-            g.sum += in ? v : 0.f;
-            g.cnt += in ? 1.f : 0.f;
+            for (int r = 0; r < 4; ++r) {
+                const int c = r + j;
+                if (c < 0 || c > 3) continue;
+                f(Dom<LIN>::log2(x.v[r][c]) * inv, w >= 2);
+            }
         }
+    };
+    float floor_v = -200.f;
+    if constexpr (!LIN) {
+        each([&](float v, bool ok) { g.mx = ok ? __builtin_fmaxf(g.mx, v) : g.mx; });
+        floor_v = g.mx - kShiftBand;
     }
+    each([&](float v, bool ok) {
+        const bool in = ok && v > floor_v && (!LIN || v < 200.f);
+        if constexpr (LIN) g.mx = in ? __builtin_fmaxf(g.mx, v) : g.mx;
+        g.sum += in ? v : 0.f;
+        g.cnt += in ? 1.f : 0.f;
+    });
     return g;
 }
 // The shift that a sentence's growth partials (part[I*S + sb], I < blocks)
@@ -627,13 +641,21 @@ __device__ __forceinline__ void growth_shift(const CX &cx, int blocks, int which
     const int gl = this_thread() & 15, S = cx.S;
     for (int sb = this_thread() >> 4; sb < S; sb += (int)blockDim.x >> 4) {
         float mx = NEG, sum = 0.f, c = 0.f;
+        if constexpr (!LIN) {
+            for (int I = gl; I < blocks; I += 16) mx = __builtin_fmaxf(mx, ld4(cx.tb, cx.part + 16 * (I * S + sb))[0]);
+            mx = row_max(mx);
+        }
         for (int I = gl; I < blocks; I += 16) {
             const f4 p = ld4(cx.tb, cx.part + 16 * (I * S + sb));
-            mx = __builtin_fmaxf(mx, p[0]);
+            if constexpr (!LIN) {
+                if (!(p[0] > mx - kShiftBand)) continue;   // a tile of near-forbidden spans
+            } else {
+                mx = __builtin_fmaxf(mx, p[0]);
+            }
             sum += p[1];
             c += p[2];
         }
-        mx = row_max(mx);
+        if constexpr (LIN) mx = row_max(mx);
         sum = row_sum(sum);
         c = row_sum(c);
         if (gl == 0)

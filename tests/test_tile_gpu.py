@@ -106,3 +106,22 @@ def test_tile_charts(name, flags):
     # MBR: the tree of the marginals that the call returned
     mum = np.where(valid, mum.cpu().numpy(), np.float32(np.nan))
     assert np.array_equal(spm.cpu().numpy(), orc.cky(mum, b.lengths, threads=16)[0])
+
+
+def test_log_domain_shift_near_forbidden():
+    # the log domain's shift comes from spans of a quarter of the sentence's
+    # width, of which those with a near-forbidden score must be left out
+    # however wide they are.  Chart values then reach some 2^9 (log2 units),
+    # and a marginal's exponent takes about ten roundings of them:
+    # 10 * 2^-15 * ln 2 (1e-3 off with those spans in the mean).
+    import torch
+
+    b = W.custom([350, 300, 350], seed=400, sd=5.0, forbid=0.05)
+    s = torch.from_numpy(b.scores).to("cuda:0")
+    lz_ref, mu_ref = orc.marginals(b.scores, b.lengths, threads=16)
+    with B.Plan(b.lengths, n1=b.n1, device=s.device) as plan:
+        lz, mu = plan.inside_fwd_bwd(s)
+        torch.cuda.synchronize()
+    assert np.all(np.abs(lz.cpu().numpy() - lz_ref) <= 1e-5 * np.abs(lz_ref))
+    valid = W.valid_mask(b.lengths, b.n1)
+    assert np.max(np.abs(mu.cpu().numpy() - mu_ref)[valid]) <= 2.1e-4
