@@ -124,7 +124,7 @@ __device__ __forceinline__ void st4(char *sm, int off, f4 v) { *reinterpret_cast
 // ---------------------------------------------------------------------------
 // The two domains.  LIN: the chart holds exp2 of the shifted, log2-scaled
 // values, sums are sums.  Otherwise it holds those values, and sums are
-// pairwise log-sum-exps (only bundles that leave float32's range come here).
+// log-sum-exps (only bundles that leave float32's range come here).
 template <bool LIN>
 struct Dom {
     static constexpr float zero = LIN ? 0.f : NEG, one = LIN ? 1.f : 0.f;
@@ -132,10 +132,6 @@ struct Dom {
         if constexpr (LIN) return a + b;
         const float m = __builtin_fmaxf(a, b);
         return m + fast_log2(fast_exp2(a - m) + fast_exp2(b - m));
-    }
-    __device__ static __forceinline__ float fma(float u, float x, float t) {
-        if constexpr (LIN) return __builtin_fmaf(u, x, t);
-        return add(t, u + x);
     }
     __device__ static __forceinline__ float mul(float a, float b) {
         if constexpr (LIN) return a * b;
@@ -151,36 +147,112 @@ struct Dom {
         if constexpr (LIN) return fast_log2(x);
         return x;
     }
-    // acc[r][c] += sum_k x[k][r] y[k][c]
-    __device__ static __forceinline__ void product(Tile &acc, const f4 (&x)[4], const f4 (&y)[4]) {
-        if constexpr (LIN) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) acc.v[r][c] = __builtin_fmaf(x[k][r], y[k][c], acc.v[r][c]);
-        } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    float m = acc.v[r][c];
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) m = __builtin_fmaxf(m, x[k][r] + y[k][c]);
-                    float s = fast_exp2(acc.v[r][c] - m);
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) s += fast_exp2(x[k][r] + y[k][c] - m);
-                    acc.v[r][c] = m + fast_log2(s);
-                }
-        }
-    }
-    template <int CTRL>
-    __device__ static __forceinline__ void combine(Tile &acc) {
+};
+
+// A tile's sums while its terms come in.  LIN: the sums.  Otherwise a pair per
+// span, its largest term and the sum of the terms relative to that (2^m s), so
+// that a span's sum is rounded at the chart's magnitude once, however many
+// products and lanes it takes (a log2 per product rounded it every time: sd 10,
+// 60 to 200 words, marginals XXX off instead of YYY, 2-norm).
+template <bool LIN>
+struct Acc {
+    Tile v;
+    __device__ __forceinline__ Acc() {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc.v[r][c] = add(acc.v[r][c], dpp_f<CTRL>(acc.v[r][c]));
+            for (int c = 0; c < 4; ++c) v.v[r][c] = 0.f;
+    }
+    // += sum_k x[k][r] y[k][c]
+    __device__ __forceinline__ void product(const f4 (&x)[4], const f4 (&y)[4]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v.v[r][c] = __builtin_fmaf(x[k][r], y[k][c], v.v[r][c]);
+    }
+    template <int CTRL>
+    __device__ __forceinline__ void combine() {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v.v[r][c] += dpp_f<CTRL>(v.v[r][c]);
+    }
+    __device__ __forceinline__ void set_one(int r, int c, bool yes) { v.v[r][c] = yes ? 1.f : v.v[r][c]; }
+};
+struct Log_pair {
+    float m = NEG, s = 1.f;
+    __device__ __forceinline__ void add(float x) {
+        const float n = __builtin_fmaxf(m, x);
+        s = s * fast_exp2(m - n) + fast_exp2(x - n);
+        m = n;
+    }
+    template <int CTRL>
+    __device__ __forceinline__ void combine() {
+        const float m2 = dpp_f<CTRL>(m), s2 = dpp_f<CTRL>(s), n = __builtin_fmaxf(m, m2);
+        s = s * fast_exp2(m - n) + s2 * fast_exp2(m2 - n);
+        m = n;
+    }
+    __device__ __forceinline__ float value() const { return m + fast_log2(s); }
+};
+template <>
+struct Acc<false> {
+    Log_pair v[4][4];
+    __device__ __forceinline__ void product(const f4 (&x)[4], const f4 (&y)[4]) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                Log_pair &p = v[r][c];
+                float n = p.m;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) n = __builtin_fmaxf(n, x[k][r] + y[k][c]);
+                float s = p.s * fast_exp2(p.m - n);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s += fast_exp2(x[k][r] + y[k][c] - n);
+                p.m = n;
+                p.s = s;
+            }
+    }
+    template <int CTRL>
+    __device__ __forceinline__ void combine() {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[r][c].template combine<CTRL>();
+    }
+    __device__ __forceinline__ void set_one(int r, int c, bool yes) {
+        v[r][c].m = yes ? 0.f : v[r][c].m;
+        v[r][c].s = yes ? 1.f : v[r][c].s;
+    }
+};
+
+// One span's sum: its accumulator and up to six further terms.
+template <bool LIN>
+struct Span_sum {
+    float t;
+    __device__ __forceinline__ Span_sum(const Acc<LIN> &a, int r, int c) : t(a.v.v[r][c]) {}
+    __device__ __forceinline__ void add(float x) { t += x; }
+    __device__ __forceinline__ void fma(float u, float x) { t = __builtin_fmaf(u, x, t); }
+    __device__ __forceinline__ float value() const { return t; }
+};
+template <>
+struct Span_sum<false> {
+    Log_pair p;
+    float term[6];
+    int n = 0;   // (known once the loops are unrolled)
+    __device__ __forceinline__ Span_sum(const Acc<false> &a, int r, int c) : p(a.v[r][c]) {}
+    __device__ __forceinline__ void add(float x) { term[n++] = x; }
+    __device__ __forceinline__ void fma(float u, float x) { term[n++] = u + x; }
+    __device__ __forceinline__ float value() const {
+        float m = p.m;
+#pragma unroll
+        for (int k = 0; k < 6; ++k) m = k < n ? __builtin_fmaxf(m, term[k]) : m;
+        float s = p.s * fast_exp2(p.m - m);
+#pragma unroll
+        for (int k = 0; k < 6; ++k) s += k < n ? fast_exp2(term[k] - m) : 0.f;
+        return m + fast_log2(s);
     }
 };
 
@@ -293,20 +365,21 @@ __device__ __forceinline__ Diag3 diag3(const char *sm, int at, int rot, int rs) 
 // blocks); sum: the bracket on the tile's diagonal.  word: the tile's lower
 // left span is a word (diagonal 1).
 template <bool LIN>
-__device__ __forceinline__ void finish_inside(Tile &x, float (&sum)[4], const Tile &acc, const Tile &e, const Diag3 &U,
+__device__ __forceinline__ void finish_inside(Tile &x, float (&sum)[4], const Acc<LIN> &acc, const Tile &e, const Diag3 &U,
                                               const Diag3 &V, bool word) {
     typedef Dom<LIN> Dm;
 #pragma unroll
     for (int c = 0; c < 4; ++c)
 #pragma unroll
         for (int r = 3; r >= 0; --r) {
-            float t = acc.v[r][c];
-            if (r < 3) t = Dm::add(t, x.v[r + 1][c]);
-            if (r < 2) t = Dm::fma(r == 0 ? U.d02 : U.d13, x.v[r + 2][c], t);
-            if (r < 1) t = Dm::fma(U.d03, x.v[3][c], t);
-            if (c > 0) t = Dm::add(t, x.v[r][c - 1]);
-            if (c > 1) t = Dm::fma(c == 2 ? V.d02 : V.d13, x.v[r][c - 2], t);
-            if (c > 2) t = Dm::fma(V.d03, x.v[r][0], t);
+            Span_sum<LIN> q(acc, r, c);
+            if (r < 3) q.add(x.v[r + 1][c]);
+            if (r < 2) q.fma(r == 0 ? U.d02 : U.d13, x.v[r + 2][c]);
+            if (r < 1) q.fma(U.d03, x.v[3][c]);
+            if (c > 0) q.add(x.v[r][c - 1]);
+            if (c > 1) q.fma(c == 2 ? V.d02 : V.d13, x.v[r][c - 2]);
+            if (c > 2) q.fma(V.d03, x.v[r][0]);
+            const float t = q.value();
             if (r == c) sum[r] = t;
             x.v[r][c] = Dm::mul(e.v[r][c], t);
             if (r == 3 && c == 0) x.v[3][0] = word ? Dm::one : x.v[3][0];   // a word
@@ -376,48 +449,42 @@ __device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np,
         }
     };
     if (iters > 0) load(pr, 0);
-    Tile acc, e;
+    Acc<LIN> acc;
+    Tile e;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            acc.v[r][c] = Dm::zero;
-            e.v[r][c] = Dm::own(raw[r][c], d);
-        }
-    auto run = [&](Tile &sum, int i0, int i1) {
+        for (int c = 0; c < 4; ++c) e.v[r][c] = Dm::own(raw[r][c], d);
+    auto run = [&](Acc<LIN> &sum, int i0, int i1) {
 #pragma unroll 1
         for (int it = i0; it < i1; ++it) {
             if (it > 0) load(pr, it);
-            if (ls.q + (it << lg) < np) Dm::product(sum, pr.x, pr.y);
+            if (ls.q + (it << lg) < np) sum.product(pr.x, pr.y);
         }
     };
     if constexpr (CX::kGlob && LIN) {
 #pragma unroll 1
         for (int i0 = 0; i0 < iters; i0 += kSum) {
-            Tile part;
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) part.v[r][c] = 0.f;
+            Acc<LIN> part;
             run(part, i0, min(iters, i0 + kSum));
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc.v[r][c] += part.v[r][c];
+                for (int c = 0; c < 4; ++c) acc.v.v[r][c] += part.v.v[r][c];
         }
     } else {
         run(acc, 0, iters);
     }
-    if (lg >= 1) Dm::template combine<kRor8>(acc);
-    if (lg >= 2) Dm::template combine<kRor4>(acc);
-    if (lg >= 3) Dm::template combine<kRor2>(acc);
-    if (lg >= 4) Dm::template combine<kRor1>(acc);
+    if (lg >= 1) acc.template combine<kRor8>();
+    if (lg >= 2) acc.template combine<kRor4>();
+    if (lg >= 3) acc.template combine<kRor2>();
+    if (lg >= 4) acc.template combine<kRor1>();
     if (D == m - 1) {   // the root (0, n): own term 1; outside score 1
         const int rc = tab<int>(cx, kTabN, sb) - 4 * (m - 1);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             e.v[0][c] = I == 0 && c == rc ? Dm::one : e.v[0][c];
-            if constexpr (OUT) acc.v[0][c] = I == 0 && c == rc ? Dm::one : acc.v[0][c];
+            if constexpr (OUT) acc.set_one(0, c, I == 0 && c == rc);
         }
     }
 
@@ -436,14 +503,14 @@ __device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np,
         for (int r = 0; r < 4; ++r)
 #pragma unroll
             for (int c = 3; c >= 0; --c) {
-                float v = acc.v[r][c];
-                if (r > 0) v = Dm::add(v, t.v[r - 1][c]);
-                if (r > 1) v = Dm::fma(r == 2 ? U.d02 : U.d13, t.v[r - 2][c], v);
-                if (r > 2) v = Dm::fma(U.d03, t.v[0][c], v);
-                if (c < 3) v = Dm::add(v, t.v[r][c + 1]);
-                if (c < 2) v = Dm::fma(c == 1 ? V.d13 : V.d02, t.v[r][c + 2], v);
-                if (c < 1) v = Dm::fma(V.d03, t.v[r][3], v);
-                t.v[r][c] = Dm::mul(e.v[r][c], v);
+                Span_sum<LIN> q(acc, r, c);
+                if (r > 0) q.add(t.v[r - 1][c]);
+                if (r > 1) q.fma(r == 2 ? U.d02 : U.d13, t.v[r - 2][c]);
+                if (r > 2) q.fma(U.d03, t.v[0][c]);
+                if (c < 3) q.add(t.v[r][c + 1]);
+                if (c < 2) q.fma(c == 1 ? V.d13 : V.d02, t.v[r][c + 2]);
+                if (c < 1) q.fma(V.d03, t.v[r][3]);
+                t.v[r][c] = Dm::mul(e.v[r][c], q.value());
                 if (r == 3 && c == 0) t.v[3][0] = D == 1 ? Dm::zero : t.v[3][0];   // a word: no term of any product
             }
     }
@@ -505,7 +572,11 @@ __device__ __forceinline__ void outside_diagonal(const CX &cx, char *sm, int w, 
     const f4 r0 = ld4(sm, at + ri * rs), r1 = ld4(sm, at + ((1 + ri) & 3) * rs);
     const float d = tab<float>(cx, kTabD, sb);
     const int n = tab<int>(cx, kTabN, sb);
-    float a02 = Dm::zero, a13 = Dm::zero, a03 = Dm::zero;
+    typename std::conditional<LIN, float, Log_pair>::type s02{}, s13{}, s03{};
+    auto term = [](auto &a, float x, float y) {
+        if constexpr (LIN) a = __builtin_fmaf(x, y, a);
+        else a.add(x + y);
+    };
     const int bx = f * 64, by = cx.qo + f * 64, lim = m * cx.rpb, step = cx.rpb << lg;
     int off = (I + 1 + ls.q) * cx.rpb;
     typedef float f2 __attribute__((ext_vector_type(2)));
@@ -523,21 +594,25 @@ __device__ __forceinline__ void outside_diagonal(const CX &cx, char *sm, int w, 
         for (int k = 0; k < 4; ++k) {   // columns 0, 1 of X and 2, 3 of Y
             const f2 x = *reinterpret_cast<const f2 *>(sm + (uint32_t)(ax + rx * k));
             const f2 y = *reinterpret_cast<const f2 *>(sm + (uint32_t)(ay + ry * k + 8));
-            a02 = Dm::fma(x[0], y[0], a02);
-            a13 = Dm::fma(x[1], y[1], a13);
-            a03 = Dm::fma(x[0], y[1], a03);
+            term(s02, x[0], y[0]);
+            term(s13, x[1], y[1]);
+            term(s03, x[0], y[1]);
         }
         off += step;
     }
-    auto combine = [&](float &a) {
-        if (lg >= 1) a = Dm::add(a, dpp_f<kRor8>(a));
-        if (lg >= 2) a = Dm::add(a, dpp_f<kRor4>(a));
-        if (lg >= 3) a = Dm::add(a, dpp_f<kRor2>(a));
-        if (lg >= 4) a = Dm::add(a, dpp_f<kRor1>(a));
+    auto level = [&](auto &a, auto ctrl) {
+        if constexpr (LIN) a += dpp_f<decltype(ctrl)::value>(a);
+        else a.template combine<decltype(ctrl)::value>();
     };
-    combine(a02);
-    combine(a13);
-    combine(a03);
+    auto combine = [&](auto &a) -> float {
+        if (lg >= 1) level(a, std::integral_constant<int, kRor8>{});
+        if (lg >= 2) level(a, std::integral_constant<int, kRor4>{});
+        if (lg >= 3) level(a, std::integral_constant<int, kRor2>{});
+        if (lg >= 4) level(a, std::integral_constant<int, kRor1>{});
+        if constexpr (LIN) return a;
+        else return a.value();
+    };
+    float a02 = combine(s02), a13 = combine(s13), a03 = combine(s03);
     float e02 = Dm::own(r0[2], d), e13 = Dm::own(r1[3], d), e03 = Dm::own(r0[3], d);
     if (m == 1) {
         a02 = n == 2 ? Dm::one : a02;

@@ -125,3 +125,21 @@ def test_log_domain_shift_near_forbidden():
     assert np.all(np.abs(lz.cpu().numpy() - lz_ref) <= 1e-5 * np.abs(lz_ref))
     valid = W.valid_mask(b.lengths, b.n1)
     assert np.max(np.abs(mu.cpu().numpy() - mu_ref)[valid]) <= 2.1e-4
+
+
+def test_log_domain_rounds_a_sum_once():
+    # a span's log-sum-exp is rounded at the chart's magnitude once, not once
+    # per product of tiles and lane: 2-norm of the marginals' error 7.4e-6 of
+    # their own (9.6e-6 with a log2 per product, 9.8e-6 on charts that take a
+    # width a step; same inputs, same arithmetic, same bits every time)
+    import torch
+
+    b = W.custom([60] * 40, seed=140, sd=8.0)
+    s = torch.from_numpy(b.scores).to("cuda:0")
+    _, mu_ref = orc.marginals(b.scores, b.lengths, threads=16)
+    with B.Plan(b.lengths, n1=b.n1, device=s.device) as plan:
+        _, mu = plan.inside_fwd_bwd(s)
+        torch.cuda.synchronize()
+    valid = W.valid_mask(b.lengths, b.n1)
+    err = (mu.cpu().numpy() - mu_ref)[valid]
+    assert np.linalg.norm(err) <= 8.5e-6 * np.linalg.norm(mu_ref[valid])
