@@ -422,7 +422,7 @@ constexpr int kTileMaxLen = 139;      // 35 blocks: the longest whose two inside
 constexpr int kTileThreads = 256;      // two workgroups per CU
 constexpr int kTileThreadsMax = 512;  // one workgroup per CU (bundles past half the LDS)
 constexpr int kTileThreadsWs = 512;  // workspace charts: a sentence and pass per workgroup
-constexpr int kTileTabWords = 6;
+constexpr int kTileTabWords = 8;
 // An inside bundle's score rows in 16-byte pieces (tiles are walked in folded
 // rows of m + 1), of which a thread keeps at most kTilePieces.
 constexpr int kTilePieces = 6;

@@ -65,14 +65,22 @@ constexpr double LN2_D = 0.69314718055994530942;
 // value, and finite, so that sums and differences of two stay finite.
 constexpr float NEG = -1.0e30f;
 // Linear-domain range (see inside_block_impl): a larger value, or a root
-// outside [2^-100, 2^100], sends the bundle to the log domain.  So does a sum
-// over a span's splits below 2^-100 that is not zero (looked at on a quarter
-// of the spans, the tiles' diagonals): the scores then spread so far that
-// other sums have lost their digits, or themselves, to underflow.  (Zero is
-// what spans get whose every tree holds a near-forbidden score.)
+// outside [2^-100, 2^100], sends the bundle to the log domain.  So do sums
+// that lost their digits, or themselves, to underflow where that matters.  A
+// sum below 2^-100 that is not zero is a sign of it (zero is what spans get
+// whose every tree holds a near-forbidden score); it is off by some 2^-142 (of
+// at most 2^8 terms, 2^-150 each), times 2^R by the rescales that follow, and
+// log Z and the marginals by that times the span's outside over Z (a lost
+// outside sum: times its inside).  So the bundle is redone when a sentence
+// has a low sum and its largest value or sum, times 2^R, exceeds
+// 2^kHarmLog2 Z: 2^-42 a span, which leaves some 2^20 for the number of spans
+// and for sums being looked at on a quarter of the spans only (the tiles'
+// diagonals).  Calls without the outside redo any bundle with a low sum.
 constexpr uint32_t kLinLowBits = 0x0D800000u;   // 2^-100
 constexpr uint32_t kLinMaxBits = 0x71800000u;   // 2^100; infinities and NaN compare above it
 constexpr float kLinMin = 0x1p-100f, kLinMax = 0x1p+100f;
+constexpr uint32_t kLinTopBits = 0x4F800000u;   // 2^32: larger values and sums are noted
+constexpr float kLinTopLog2 = 32.f, kHarmLog2 = 100.f;
 constexpr int kGoldMark = 0x7FBADBAD;           // a NaN bit pattern: no finite chart value has it
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -303,7 +311,11 @@ __device__ __forceinline__ Io_ctx<GLOB> io_ctx(const int32_t *rec, char *lds) {
     return c;
 }
 // per-sentence tables: word `which` of sentence sb
-enum { kTabD = 0, kTabDl, kTabG, kTabLz, kTabId, kTabN, kTabWords };
+// (kTabTop: the bits of the largest value or sum noted; kTabR: log2 of what
+// rescales may have added to an early sum's error)
+enum { kTabD = 0, kTabDl, kTabG, kTabLz, kTabId, kTabN, kTabTop, kTabR, kTabWords };
+// a bundle's flags: out of range, and a low sum
+enum { kFlagOut = 0, kFlagLow, kFlags };
 template <typename T, typename CX>
 __device__ __forceinline__ T &tab(const CX &c, int which, int sb) {
     return *reinterpret_cast<T *>(c.tb + c.tab + 4 * (which * c.S + sb));
@@ -390,7 +402,7 @@ __device__ __forceinline__ void finish_inside(Tile &x, float (&sum)[4], const Ac
 // D (OUT = false) or outside of diagonal D; D >= 1 for the inside (diagonal 0
 // is inside_diagonal).  cnt tiles, np products each.
 template <bool LIN, bool OUT, typename CX>
-__device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np, int cnt, int w, int lg, int *ovf) {
+__device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np, int cnt, int w, int lg, int *flags) {
     typedef Dom<LIN> Dm;
     const int m = cx.m, S = cx.S;
     const Lane_share ls = lane_share(here(w), here(lg));
@@ -489,15 +501,9 @@ __device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np,
     }
 
     Tile t;
+    float sum[4];   // on the tile's diagonal
     if constexpr (!OUT) {
-        float sum[4];
         finish_inside<LIN>(t, sum, acc, e, U, V, D == 1);
-        if constexpr (LIN) {   // (zero wraps round to the largest)
-            uint32_t low = 0xFFFFFFFFu;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) low = min(low, __builtin_bit_cast(uint32_t, sum[r]) - 1u);
-            if (low < kLinLowBits) *ovf = 1;
-        }
     } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -510,15 +516,29 @@ __device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np,
                 if (c < 3) q.add(t.v[r][c + 1]);
                 if (c < 2) q.fma(c == 1 ? V.d13 : V.d02, t.v[r][c + 2]);
                 if (c < 1) q.fma(V.d03, t.v[r][3]);
-                t.v[r][c] = Dm::mul(e.v[r][c], q.value());
+                const float v = q.value();
+                if (r == c) sum[r] = v;
+                t.v[r][c] = Dm::mul(e.v[r][c], v);
                 if (r == 3 && c == 0) t.v[3][0] = D == 1 ? Dm::zero : t.v[3][0];   // a word: no term of any product
             }
     }
-    if constexpr (LIN) {   // every value is >= 0, so the sum shows an infinity, a NaN or a value past the range
+    if constexpr (LIN) {   // every value is >= 0, so their sum shows an infinity, a NaN or a value past the range
         float s = 0.f;
 #pragma unroll
         for (int r = 0; r < 4; ++r) s += (t.v[r][0] + t.v[r][1]) + (t.v[r][2] + t.v[r][3]);
-        if (__builtin_bit_cast(uint32_t, s) > kLinMaxBits) *ovf = 1;
+        const uint32_t sb_bits = __builtin_bit_cast(uint32_t, s);
+        uint32_t low = 0xFFFFFFFFu, top = sb_bits;   // (zero wraps round to the largest)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t b = __builtin_bit_cast(uint32_t, sum[r]);
+            low = min(low, b - 1u);
+            top = max(top, b);
+        }
+        if (low < kLinLowBits || top > kLinTopBits) {
+            if (sb_bits > kLinMaxBits) flags[kFlagOut] = 1;
+            if (low < kLinLowBits) flags[kFlagLow] = 1;
+            atomicMax(&tab<uint32_t>(cx, kTabTop, sb), top);
+        }
     }
     if (act) {
         const int up = OUT ? cx.o(I, J, sb) : cx.a(I, J, sb), lo = OUT ? cx.ot(I, J, sb) : cx.at(I, J, sb);
@@ -533,7 +553,7 @@ __device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np,
 // Inside of tile diagonal 0: the spans of up to three words inside a block.
 // A lane per tile.
 template <bool LIN, typename CX>
-__device__ __forceinline__ void inside_diagonal(const CX &cx, char *sm, int *ovf) {
+__device__ __forceinline__ void inside_diagonal(const CX &cx, char *sm, int *flags) {
     typedef Dom<LIN> Dm;
     const int cnt = cx.m * cx.S;
     for (int f = this_thread(); f < cnt; f += (int)blockDim.x) {
@@ -549,7 +569,7 @@ __device__ __forceinline__ void inside_diagonal(const CX &cx, char *sm, int *ovf
         }
         const float x03 = Dm::mul(e03, Dm::add(e13, e02));
         if constexpr (LIN)
-            if (__builtin_bit_cast(uint32_t, e02 + e13 + x03) > kLinMaxBits) *ovf = 1;
+            if (__builtin_bit_cast(uint32_t, e02 + e13 + x03) > kLinMaxBits) flags[kFlagOut] = 1;
         const float z = Dm::zero, o = Dm::one;
         st4(sm, at + ri * rs, f4{z, o, e02, x03});
         st4(sm, at + ((1 + ri) & 3) * rs, f4{z, z, o, e13});
@@ -561,7 +581,7 @@ __device__ __forceinline__ void inside_diagonal(const CX &cx, char *sm, int *ovf
 // Outside of tile diagonal 0 (stage m): the products run over every other
 // block, the finish over the three spans of two and three words.
 template <bool LIN, typename CX>
-__device__ __forceinline__ void outside_diagonal(const CX &cx, char *sm, int w, int lg, int *ovf) {
+__device__ __forceinline__ void outside_diagonal(const CX &cx, char *sm, int w, int lg, int *flags) {
     typedef Dom<LIN> Dm;
     const int m = cx.m, S = cx.S, cnt = m * S, np = m - 1;
     const Lane_share ls = lane_share(w, lg);
@@ -621,9 +641,18 @@ __device__ __forceinline__ void outside_diagonal(const CX &cx, char *sm, int w, 
         e03 = n == 3 ? Dm::one : e03;
     }
     const float o03 = Dm::mul(e03, a03);
-    const float o02 = Dm::mul(e02, Dm::add(a02, o03)), o13 = Dm::mul(e13, Dm::add(a13, o03));
-    if constexpr (LIN)
-        if (__builtin_bit_cast(uint32_t, o02 + o13 + o03) > kLinMaxBits) *ovf = 1;
+    a02 = Dm::add(a02, o03);
+    a13 = Dm::add(a13, o03);
+    const float o02 = Dm::mul(e02, a02), o13 = Dm::mul(e13, a13);
+    if constexpr (LIN) {
+        const uint32_t s = __builtin_bit_cast(uint32_t, o02 + o13 + o03);
+        const uint32_t top = max(max(s, __builtin_bit_cast(uint32_t, a03)),
+                                 max(__builtin_bit_cast(uint32_t, a02), __builtin_bit_cast(uint32_t, a13)));
+        if (top > kLinTopBits) {
+            if (s > kLinMaxBits) flags[kFlagOut] = 1;
+            atomicMax(&tab<uint32_t>(cx, kTabTop, sb), top);
+        }
+    }
     if (act) {
         st4(sm, at + ri * rs, f4{Dm::zero, Dm::zero, o02, o03});
         st4(sm, at + ((1 + ri) & 3) * rs, f4{Dm::zero, Dm::zero, Dm::zero, o13});
@@ -805,7 +834,11 @@ __device__ void tile_rescale(const CX &cx, char *sm, int t0) {
                           (float)(n - 4 * D), -1.f);
             }
         }
-    for (int sb = tid; sb < S; sb += NT) tab<float>(cx, kTabD, sb) += tab<float>(cx, kTabDl, sb);
+    for (int sb = tid; sb < S; sb += NT) {
+        const float dl = tab<float>(cx, kTabDl, sb);
+        tab<float>(cx, kTabD, sb) += dl;
+        tab<float>(cx, kTabR, sb) += __builtin_fmaxf(dl, 0.f) * (float)(4 * t0 + 2);   // the widest span moved
+    }
     __syncthreads();
 }
 
@@ -912,7 +945,7 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
                                                  float *__restrict__ logZ, float *__restrict__ marg,
                                                  const int32_t *__restrict__ gold, float *__restrict__ loss) {
     typedef Dom<LIN> Dm;
-    __shared__ int ovf;
+    __shared__ int flags[kFlags];
     const int tid = this_thread(), NT = (int)blockDim.x, N1 = p.n1;
     const Io_ctx<GLOB> cx = io_ctx<GLOB>(rec, lds);
     const int m = cx.m, S = cx.S;
@@ -921,8 +954,10 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
         tab<int>(cx, kTabId, sb) = id;
         tab<int>(cx, kTabN, sb) = rec[kTrHeader + 2 * sb + 1];
         tab<float>(cx, kTabG, sb) = grad ? grad[id] : 1.0f;
+        tab<uint32_t>(cx, kTabTop, sb) = 0u;
+        tab<float>(cx, kTabR, sb) = 0.f;
     }
-    if (tid == 0) ovf = 0;
+    if (tid < kFlags) flags[tid] = 0;
     __syncthreads();
 
     // Prologue: the score rows into P and Q, at most kTilePieces pieces a
@@ -960,7 +995,7 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
     // The stages.
     const int nw = NT >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int most = lanes_lg(m * S, nw);
-    inside_diagonal<LIN>(cx, sm, &ovf);
+    inside_diagonal<LIN>(cx, sm, flags);
     __syncthreads();
     int tr = tile_rescale_after<LIN>(1, m);
     for (int t = 1; t < (REV ? m + 1 : m); ++t) {
@@ -969,11 +1004,11 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
         const int win = ((cin << lg) + 63) >> 6, wout = ((cout << lg) + 63) >> 6;
         for (int w = wave; w < win + wout; w += nw) {
             if (w < win)
-                tile_task<LIN, false>(cx, sm, t, t - 1, cin, w, lg, &ovf);
+                tile_task<LIN, false>(cx, sm, t, t - 1, cin, w, lg, flags);
             else if (REV && t < m)
-                tile_task<LIN, true>(cx, sm, m - t, t - 1, cout, w - win, lg, &ovf);
+                tile_task<LIN, true>(cx, sm, m - t, t - 1, cout, w - win, lg, flags);
             else if (REV)
-                outside_diagonal<LIN>(cx, sm, w - win, lg, &ovf);
+                outside_diagonal<LIN>(cx, sm, w - win, lg, flags);
         }
         __syncthreads();
         if (t == tr) {
@@ -993,13 +1028,20 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
     };
     for (int sb = tid; sb < S; sb += NT) {
         const float r = root_of(sb);
-        if constexpr (LIN)
-            if (!(r >= kLinMin) || !(r <= kLinMax)) ovf = 1;
-        tab<float>(cx, kTabLz, sb) = Dm::log2(r);
+        const float lz = Dm::log2(r);
+        if constexpr (LIN) {
+            bool bad = !(r >= kLinMin) || !(r <= kLinMax);
+            if (flags[kFlagLow] != 0) {
+                const float top = __builtin_fmaxf(kLinTopLog2, fast_log2(tab<float>(cx, kTabTop, sb)));
+                bad = bad || !REV || top + tab<float>(cx, kTabR, sb) > lz + kHarmLog2;
+            }
+            if (bad) flags[kFlagOut] = 1;
+        }
+        tab<float>(cx, kTabLz, sb) = lz;
     }
     __syncthreads();
     if constexpr (LIN)
-        if (ovf) return false;
+        if (flags[kFlagOut] != 0) return false;
     auto log_z = [&](int sb) {
         const int n = tab<int>(cx, kTabN, sb);
         const float r = root_of(sb);

@@ -143,3 +143,21 @@ def test_log_domain_rounds_a_sum_once():
     valid = W.valid_mask(b.lengths, b.n1)
     err = (mu.cpu().numpy() - mu_ref)[valid]
     assert np.linalg.norm(err) <= 8.5e-6 * np.linalg.norm(mu_ref[valid])
+
+
+@pytest.mark.parametrize("length,count,sd,seed", [(30, 60, 8.0, 110)])
+def test_sums_lost_to_underflow(length, count, sd, seed):
+    # sums that underflow on few spans, none of them on an inside tile's
+    # diagonal: without the outside sums the bundle of one sentence here keeps
+    # the linear domain, 8e-2 off
+    import torch
+
+    b = W.custom([length] * count, seed=seed, sd=sd)
+    s = torch.from_numpy(b.scores).to("cuda:0")
+    lz_ref, mu_ref = orc.marginals(b.scores, b.lengths, threads=16)
+    with B.Plan(b.lengths, n1=b.n1, device=s.device) as plan:
+        lz, mu = plan.inside_fwd_bwd(s)
+        torch.cuda.synchronize()
+    assert np.all(np.abs(lz.cpu().numpy() - lz_ref) <= 1e-5 * np.maximum(1.0, np.abs(lz_ref)))
+    valid = W.valid_mask(b.lengths, b.n1)
+    assert np.max(np.abs(mu.cpu().numpy() - mu_ref)[valid]) <= 1e-4
