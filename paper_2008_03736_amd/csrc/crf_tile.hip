@@ -314,8 +314,8 @@ __device__ __forceinline__ Io_ctx<GLOB> io_ctx(const int32_t *rec, char *lds) {
 // (kTabTop: the bits of the largest value or sum noted; kTabR: log2 of what
 // rescales may have added to an early sum's error)
 enum { kTabD = 0, kTabDl, kTabG, kTabLz, kTabId, kTabN, kTabTop, kTabR, kTabWords };
-// a bundle's flags: out of range, and a low sum
-enum { kFlagOut = 0, kFlagLow, kFlags };
+// a bundle's flags: out of range, a low sum, and early values far from 1
+enum { kFlagOut = 0, kFlagLow, kFlagWide, kFlags };
 template <typename T, typename CX>
 __device__ __forceinline__ T &tab(const CX &c, int which, int sb) {
     return *reinterpret_cast<T *>(c.tb + c.tab + 4 * (which * c.S + sb));
@@ -400,9 +400,11 @@ __device__ __forceinline__ void finish_inside(Tile &x, float (&sum)[4], const Ac
 
 // One wavefront's share of a stage's tiles of one kind: inside of diagonal
 // D (OUT = false) or outside of diagonal D; D >= 1 for the inside (diagonal 0
-// is inside_diagonal).  cnt tiles, np products each.
+// is inside_diagonal).  cnt tiles, np products each.  mark: sums below it set
+// the flags.
 template <bool LIN, bool OUT, typename CX>
-__device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np, int cnt, int w, int lg, int *flags) {
+__device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np, int cnt, int w, int lg, uint32_t mark,
+                                          int *flags) {
     typedef Dom<LIN> Dm;
     const int m = cx.m, S = cx.S;
     const Lane_share ls = lane_share(here(w), here(lg));
@@ -534,9 +536,10 @@ __device__ __forceinline__ void tile_task(const CX &cx, char *sm, int D, int np,
             low = min(low, b - 1u);
             top = max(top, b);
         }
-        if (low < kLinLowBits || top > kLinTopBits) {
+        if (low < mark || top > kLinTopBits) {
             if (sb_bits > kLinMaxBits) flags[kFlagOut] = 1;
             if (low < kLinLowBits) flags[kFlagLow] = 1;
+            if (mark != kLinLowBits) flags[kFlagWide] = 1;   // (written before the stage that reads it only)
             atomicMax(&tab<uint32_t>(cx, kTabTop, sb), top);
         }
     }
@@ -663,13 +666,21 @@ __device__ __forceinline__ void outside_diagonal(const CX &cx, char *sm, int w, 
 }
 
 // Stages after which the chart is rescaled, the first >= lo, or 0.  The seed
-// (tile_seed) comes from the scores alone; sentences of fewer than 44 words
-// stay in range on it.  The log domain, which never leaves the range, rescales
-// once, a quarter of the way, to keep the values and so their rounding small.
+// (tile_seed) comes from the scores alone: independent scores grow less than
+// it says, by 0.4 log2 units a node at deviation 1 and 3 at 5 (30 words), so
+// that sentences of 16 to 43 words, whose range holds at deviation 2, need one
+// rescale where the scores spread further.  They take it only when a value or
+// sum of the stages before lies outside [2^-36, 2^32] (kFlagWide): it costs 3 us
+// (40 words: 38 and 41), a redo in the log domain 40 (deviation 3, 76 us).
+// The log domain, which never leaves the range, rescales once, a quarter of the
+// way, to keep the values and so their rounding small.
+constexpr int kWideBlocks = 12;   // fewer blocks: only if flagged
+constexpr uint32_t kLinWideBits = 0x2D800000u;   // 2^-36
 template <bool LIN>
 __device__ __forceinline__ int tile_rescale_after(int lo, int m) {
     if (!LIN) return m >= 5 && m / 4 >= lo ? m / 4 : 0;
-    if (m >= 12 && lo <= 4) return 4;
+    if (m >= kWideBlocks && lo <= 4) return 4;
+    if (m >= 5 && m < kWideBlocks && lo <= 2) return m >= 7 ? 3 : 2;
     if (m > 32 && lo <= 12) return 12;
     if (m > 64 && m / 4 >= lo) return m / 4;
     if (m > 24 && m / 2 >= lo) return m / 2;
@@ -1002,17 +1013,19 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
         const int cin = (m - t) * S, cout = REV ? t * S : 0;
         const int lg = stage_lg(t - 1, cin, cout, nw, most);
         const int win = ((cin << lg) + 63) >> 6, wout = ((cout << lg) + 63) >> 6;
+        const uint32_t mark = LIN && m < kWideBlocks && t <= tr ? kLinWideBits : kLinLowBits;
         for (int w = wave; w < win + wout; w += nw) {
             if (w < win)
-                tile_task<LIN, false>(cx, sm, t, t - 1, cin, w, lg, flags);
+                tile_task<LIN, false>(cx, sm, t, t - 1, cin, w, lg, mark, flags);
             else if (REV && t < m)
-                tile_task<LIN, true>(cx, sm, m - t, t - 1, cout, w - win, lg, flags);
+                tile_task<LIN, true>(cx, sm, m - t, t - 1, cout, w - win, lg, mark, flags);
             else if (REV)
                 outside_diagonal<LIN>(cx, sm, w - win, lg, flags);
         }
         __syncthreads();
         if (t == tr) {
-            tile_rescale<LIN, REV>(cx, sm, t);
+            // (the flag is uniform: no later stage writes it)
+            if (!LIN || m >= kWideBlocks || flags[kFlagWide] != 0) tile_rescale<LIN, REV>(cx, sm, t);
             tr = tile_rescale_after<LIN>(t + 1, m);
         }
     }

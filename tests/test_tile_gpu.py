@@ -161,3 +161,22 @@ def test_sums_lost_to_underflow(length, count, sd, seed):
     assert np.all(np.abs(lz.cpu().numpy() - lz_ref) <= 1e-5 * np.maximum(1.0, np.abs(lz_ref)))
     valid = W.valid_mask(b.lengths, b.n1)
     assert np.max(np.abs(mu.cpu().numpy() - mu_ref)[valid]) <= 1e-4
+
+
+@pytest.mark.parametrize("length,sd,tol", [(20, 5.0, 8e-7), (30, 4.0, 8e-7), (40, 3.0, 7.3e-7), (40, 5.0, 1.2e-6)])
+def test_short_sentences_of_wide_spread_stay_linear(length, sd, tol):
+    # 16 to 43 words whose scores spread further than the seed of the shift
+    # allows for are rescaled, not sent to the log domain: 2-norm of the
+    # marginals' error relative to their own 4.5e-7 to 7.1e-7 (in the log
+    # domain 7.8e-7 to 2.4e-6)
+    import torch
+
+    b = W.custom([length] * (2000 // length - 10), seed=length + int(10 * sd), sd=sd)
+    s = torch.from_numpy(b.scores).to("cuda:0")
+    _, mu_ref = orc.marginals(b.scores, b.lengths, threads=16)
+    with B.Plan(b.lengths, n1=b.n1, device=s.device) as plan:
+        _, mu = plan.inside_fwd_bwd(s)
+        torch.cuda.synchronize()
+    valid = W.valid_mask(b.lengths, b.n1)
+    err = (mu.cpu().numpy() - mu_ref)[valid]
+    assert np.linalg.norm(err) <= tol * np.linalg.norm(mu_ref[valid])
