@@ -180,3 +180,21 @@ def test_short_sentences_of_wide_spread_stay_linear(length, sd, tol):
     valid = W.valid_mask(b.lengths, b.n1)
     err = (mu.cpu().numpy() - mu_ref)[valid]
     assert np.linalg.norm(err) <= tol * np.linalg.norm(mu_ref[valid])
+
+
+@pytest.mark.parametrize("length", [10, 20, 30, 40])
+def test_marginals_of_short_sentences_keep_float32s_digits(length):
+    # marginals are products of the chart's own values: 2-norm of the error
+    # 0.7 to 1.1e-7 of their own at deviation 2, a few float32 roundings (1.9
+    # to 3.6e-7 through the values' logarithms)
+    import torch
+
+    b = W.custom([length] * (2000 // length), seed=length + 20, sd=2.0)
+    s = torch.from_numpy(b.scores).to("cuda:0")
+    _, mu_ref = orc.marginals(b.scores, b.lengths, threads=16)
+    with B.Plan(b.lengths, n1=b.n1, device=s.device) as plan:
+        _, mu = plan.inside_fwd_bwd(s)
+        torch.cuda.synchronize()
+    valid = W.valid_mask(b.lengths, b.n1)
+    err = (mu.cpu().numpy() - mu_ref)[valid]
+    assert np.linalg.norm(err) <= 1.5e-7 * np.linalg.norm(mu_ref[valid])
