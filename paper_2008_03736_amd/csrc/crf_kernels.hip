@@ -513,17 +513,21 @@ __device__ __forceinline__ float span_dot(const T *a, const T *b, int kl, const 
     return e * sum;
 }
 
-// Bound of a stored linear-domain value: anything above it (infinity, NaN
-// or a value whose products could overflow) sends the bundle to the
-// log-domain sweep.
-constexpr float kLinMax = 0x1p+100f;
-// So does an inside sum below 2^-100 that is not zero: the scores then spread
+// Linear domain: a span's sum outside [2^-100, 2^100] that is not zero sends
+// the bundle to the log-domain sweep.  Above: sums and values on their way out
+// of float32's range (an infinity or NaN among them).  Below: the scores spread
 // so far that other sums have lost their digits, or themselves, to underflow
-// (labelled scores of deviation 10, 26 labels, 143 words: marginals 0.23 off
-// without this).  Zero is what spans get whose every tree holds a
-// near-forbidden score.
-constexpr uint32_t kLinLowBits = 0x0D800000u;   // 2^-100
-__device__ __forceinline__ bool low_sum(float x) { return __builtin_bit_cast(uint32_t, x) - 1u < kLinLowBits; }
+// (labelled scores of deviation 7, 3 labels, 50 words: marginals 45 off without
+// this; 8 words at deviation 10, whose outside sums are the first to go: 4e-2).
+// Zero is what spans get whose every tree holds a near-forbidden score.  Both
+// bounds in one unsigned comparison, which a zero also passes.
+constexpr float kLinMin = 0x1p-100f, kLinMax = 0x1p+100f;
+constexpr uint32_t kLinMinBits = 0x0D800000u, kLinMaxBits = 0x71800000u;
+__device__ __forceinline__ void check_sum(float sum, int *ovf) {
+    const uint32_t b = __builtin_bit_cast(uint32_t, sum);
+    if (b - kLinMinBits > kLinMaxBits - kLinMinBits)
+        if (b != 0u) *ovf = 1;
+}
 
 // One span of a width-w inside step (K = w - 1 splits):
 // alpha(i,j) = s(i,j) + d + log2 sum_k exp2(alpha(i,k) + alpha(k,j)), d the
@@ -552,7 +556,7 @@ __device__ __forceinline__ void inside_span(const Bundle_ctx<T> &bx, int w, int 
         pq[pa] = v;
         pq[qa] = v;
         if constexpr (LIN)
-            if (!(v <= kLinMax) || low_sum(sum)) *bx.ovf = 1;
+            check_sum(sum, bx.ovf);
     }
 }
 
@@ -568,7 +572,7 @@ __device__ __forceinline__ void outside_span(const Bundle_ctx<T> &bx, int v, int
     const int rp = (int)__umul24((uint32_t)(i + v), (uint32_t)ld);    // P row j
     const int rq = (int)__umul24((uint32_t)(i + ld), (uint32_t)ld);   // Q row i
     const int po = rp + n - v, qo = rq + v;                          // O'(i,j) cells
-    float o, sum;
+    float o, sum = 0.f;
     if constexpr (LIN)
         o = span_dot<G, C, MF, TEAM>(pq + rp + l, pq + rq + v + 1 + l, K - l, pq + po, dsh + at.sb, true, sum);
     else
@@ -578,7 +582,7 @@ __device__ __forceinline__ void outside_span(const Bundle_ctx<T> &bx, int v, int
         pq[qo] = o;
         pq[po] = o;
         if constexpr (LIN)
-            if (!(o <= kLinMax)) *bx.ovf = 1;
+            check_sum(sum, bx.ovf);
     }
 }
 
@@ -1081,11 +1085,10 @@ constexpr int kGoldMark = 0x7FBADBAD;   // a NaN bit pattern: no finite chart va
 // LIN: the sweeps run in the linear domain -- the chart holds exp2 of the
 // (shifted, log2-scaled) inside and outside values, a span's sum over its
 // splits is a dot product (span_dot), and rescales at doubling steps keep the
-// values near 1.  A value that leaves float32's range (or a root below
-// kLinMin) sets the bundle's overflow flag, and the bundle returns false
+// values near 1.  A sum that leaves float32's range (check_sum) or a root that
+// does sets the bundle's overflow flag, and the bundle returns false
 // before it has written any output: the caller then runs it again in the log
 // domain (LIN = false, max-shifted log-sum-exp per span).
-constexpr float kLinMin = 0x1p-100f;
 template <bool LIN, bool REV, bool SPILL, bool GOLD, bool LAB>
 __device__ __forceinline__ bool inside_block_impl(const KernelPlan &p, int block, const int32_t *rec, char *smem_raw,
                                                   const float *__restrict__ scores,

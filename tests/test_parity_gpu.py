@@ -427,6 +427,9 @@ LOG_DOMAIN_ATOL = 2.1e-4
     (3, 7.0, [30, 40, 50, 60, 70, 80, 90, 100], 0, MARG_ATOL),
     (2, 5.0, [30, 40, 50, 60, 70, 80, 90, 100], 3, MARG_ATOL),
     (26, 10.0, [6, 25, 26, 40, 60, 75, 110, 130, 143, 160], 7, LOG_DOMAIN_ATOL),
+    # short sentences, whose outside sums are the first to go
+    (2, 10.0, [8] * 300, 1108, MARG_ATOL),
+    (3, 10.0, [12] * 300, 1112, MARG_ATOL),
     # unlabelled, few long sentences and one past 400 words: teams
     (1, 4.5, [402, 150, 180, 210, 240, 270, 300], 4, LOG_DOMAIN_ATOL),
 ])
