@@ -1214,7 +1214,11 @@ __device__ __forceinline__ bool inside_block_impl(const KernelPlan &p, int block
     // expected tree weight grows by 4 (Catalan) times E[exp2(s)] =
     // exp2(m + v ln2 / 2) per node, so d = -(m + v ln2 / 2 + 2), from the
     // non-forced spans of widths 2..9 (near-forbidden scores left out); the
-    // rescales then correct it from the chart itself.
+    // rescales then correct it from the chart itself.  The variance's term
+    // stops at 20: past that (deviation 5) it runs far ahead of what a tree's
+    // few spans can reach, and values of two or three words would vanish
+    // before the first rescale (8 words at deviation 10: shift -84 a node,
+    // growth 36, log Z 0.04 off).
     by_sentence_groups(n, nb, [&](auto gs, int sb, int gl, bool valid) {
         constexpr int GS = decltype(gs)::value;
         const float *P = chart0 + (size_t)sb * cstride;
@@ -1240,7 +1244,7 @@ __device__ __forceinline__ bool inside_block_impl(const KernelPlan &p, int block
             c = grp_sum<GS>(c);
             if (valid && gl == 0 && c > 0.f) {
                 const float mean = s1 / c, var = fmaxf(s2 / c - mean * mean, 0.f);
-                dsh[sb] = -(mean + 0.5f * (float)LN2_D * var + 2.0f);
+                dsh[sb] = -(mean + fminf(0.5f * (float)LN2_D * var, 20.0f) + 2.0f);
             }
         }
     });
