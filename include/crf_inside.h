@@ -62,7 +62,7 @@
  *   calls only enqueue work and never synchronise.  Calls on one plan must
  *   not overlap on the device: issue them on one stream, or order them with
  *   events.  A plan owns device state that its calls use while they run --
- *   the fused launches' work counter, the workspace that holds the charts
+ *   the workspace that holds the charts
  *   and CKY split tables of sentences too long for LDS (crf_plan_info:
  *   workspace_users) and the team area -- and two overlapping calls would
  *   share it.  Different
@@ -109,17 +109,18 @@ typedef struct {
     int32_t lds_count;       /* sentences whose inside chart lives in LDS */
     int32_t spill_count;     /* sentences whose inside chart lives in the workspace */
     int64_t workspace_bytes; /* device workspace owned by the plan */
-    int32_t lds_bytes_inside;/* dynamic LDS per workgroup, inside kernels */
+    int32_t lds_bytes_inside;/* dynamic LDS per workgroup, inside kernels (the
+                                sentences whose chart lives in LDS) */
     int32_t lds_bytes_cky;   /* dynamic LDS per workgroup, CKY kernel */
     int32_t cky_spill_count; /* sentences whose CKY chart lives in the workspace */
     int32_t split_ws_count;  /* sentences whose CKY chart is in LDS but whose
                                 split table is in the workspace */
     int32_t workspace_users; /* sentences that use the workspace in some call
                                 (any of the three above) */
-    int32_t fused_queue;     /* 1 if the fused launches pull work from the
-                                plan's counter */
-    int32_t mbr_fused;       /* 1 if crf_mbr_decode runs as one launch per
-                                bundle queue (else as separate launches) */
+    int32_t fused_queue;     /* 0: no launch pulls work from a counter of the
+                                plan's any more */
+    int32_t mbr_fused;       /* 1 if crf_mbr_decode runs the sentences whose
+                                charts live in LDS in one launch (0: none do) */
 } crf_plan_stats;
 
 /*
@@ -291,8 +292,8 @@ int crf_biaffine_scores(const crf_plan *plan, const uint16_t *rl, const uint16_t
  * cannot allocate device memory or must not touch the plan's device state
  * while they run (code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation).  Same arguments and results as
- * crf_inside_fwd_bwd_cky; the plan's workspace and work counter are not
- * used: the call takes them from a static scratch array of the library,
+ * crf_inside_fwd_bwd_cky; the plan's workspace is not used: the call takes
+ * one (and a work counter) from a static scratch array of the library,
  * 8 MiB per GPU, held from the library's first use on a device until the
  * process ends.  It calls no allocation routine; it enqueues a small kernel
  * that clears the array's counter, then the launches of the fused call

@@ -385,18 +385,17 @@ struct Bundle {
 };
 
 // What a bundle's workgroup reads first: one record of rec_stride ints --
-// n, count, split_ws (CKY; -1 for inside), kind (kKindInside, kKindCky or
-// kKindMbr), then its chart layout (inside_layout or cky_layout, as the plan
-// chose it: e, ld, cs) and div_magic(count), then a second layout (the CKY
-// chart of an MBR bundle, whose first layout is its inside chart), then the
-// count sentence ids -- so that its sentence ids arrive with its shape, one
+// n, count, split_ws (CKY; -1 for inside), kind (kKindInside or kKindCky),
+// then its chart layout (inside_layout or cky_layout, as the plan
+// chose it: e, ld, cs) and div_magic(count), then (labelled inside) whether it
+// does its own label I/O, then the count sentence ids -- so that its sentence ids arrive with its shape, one
 // memory round trip before its scores, and the workgroup computes none of it.
-constexpr int kRecHeader = 12;
+constexpr int kRecHeader = 9;
 enum RecField {
-    kRecN = 0, kRecCount, kRecSplitWs, kRecKind, kRecE, kRecLd, kRecCs, kRecMagic, kRecE2, kRecLd2, kRecCs2,
+    kRecN = 0, kRecCount, kRecSplitWs, kRecKind, kRecE, kRecLd, kRecCs, kRecMagic,
     kRecLab   // labelled inside bundles: 1 when the bundle reads and writes its own label scores
 };
-enum RecKind { kKindCky = 0, kKindInside = 1, kKindMbr = 2 };
+enum RecKind { kKindCky = 0, kKindInside = 1 };
 // g / S by multiply-high: 2^32 / S + 1, exact for g < 2^18, 2 <= S <= 1024;
 // 0 for S = 1 (the caller takes g itself).
 __host__ __device__ inline uint32_t div_magic(int S) { return S > 1 ? 0xFFFFFFFFu / (uint32_t)S + 1u : 0u; }
@@ -470,11 +469,7 @@ struct KernelPlan {
     const int32_t *mix;          // [n_mix] records, or NULL when the fused kernel is not used
     int32_t n_mix;
     int32_t fused_grid;          // workgroups of the fused kernel (<= n_mix)
-    // MBR decoding: records of bundles that run inside + marginals and then
-    // CKY over the marginals, or NULL (then the two run as separate launches)
-    const int32_t *mbr;
-    int32_t n_mbr, mbr_grid, mbr_lds;
-    int32_t *counter;            // the fused kernels' bundle claims; zero between launches
+    int32_t *counter;            // the fused kernel's bundle claims (in the no-allocation scratch)
     // labelled plans: chunks of kLabelRowChunk floats of the label blocks of
     // the rows of the sentences whose label passes run chip-wide, (sentence,
     // row, first float, 0), and the workspace offsets of their label
@@ -520,6 +515,9 @@ struct KernelPlan {
 // teams: one workgroup a sentence (tile charts) loses to 16 there (a lone
 // sentence fused: 256 words 493 against 1,095 us in teams, 400 words 1,411
 // against about 1,530, 512 words 2,100 in teams).
+// A plan with CRF_NO_TEAMS, a device without room for teams and the
+// no-allocation call run the same kernels with a workgroup a pass, slower: the
+// flag then changes no bit of a result.
 constexpr int kTileTeamCount = 16, kTileTeamLen = 400;
 // CKY alone, every sentence in LDS: tile charts when the longest has up to
 // this many words, a step per width past that.  A float64 tile's chain is as

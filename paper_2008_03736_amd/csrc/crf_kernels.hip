@@ -1637,8 +1637,7 @@ template <bool SPILL, bool LAB = false>
 __device__ __forceinline__ void cky_block(const KernelPlan &p, int block, const int32_t *rec, char *smem_raw,
                                           const float *__restrict__ scores,
                                           int32_t *__restrict__ spans, float *__restrict__ best,
-                                          int32_t *__restrict__ labels = nullptr, bool second = false,
-                                          const Team &tm = Team{}) {
+                                          int32_t *__restrict__ labels = nullptr, const Team &tm = Team{}) {
     __shared__ int spill_id[1];
     const int NT = blockDim.x;
     const int tid = threadIdx.x;
@@ -1668,7 +1667,7 @@ __device__ __forceinline__ void cky_block(const KernelPlan &p, int block, const 
         nb = rec[kRecCount];
         const int split_ws = rec[kRecSplitWs];
         split_lds = split_ws < 0;
-        lay = second ? CkyLayout{rec[kRecLd2], rec[kRecCs2], rec[kRecE2]} : CkyLayout{rec[kRecLd], rec[kRecCs], rec[kRecE]};
+        lay = CkyLayout{rec[kRecLd], rec[kRecCs], rec[kRecE]};
         mnb = (uint32_t)rec[kRecMagic];
         chart0 = smem_raw;
         cstride = lay.cs;
@@ -1864,16 +1863,17 @@ __global__ __launch_bounds__(kLabelChunk) void label_expand_kernel(KernelPlan p,
 
 // The gold-tree loss: the inside kernel with marginals, minus the gold
 // indicator (inside_block, GOLD).
-template <bool SPILL, bool TEAM = false>
+// (sentences in LDS: tile_loss_kernel)
+template <bool TEAM>
 __global__ __launch_bounds__(kThreadsMax) void loss_kernel(KernelPlan p, const float *__restrict__ scores,
                                                            const int32_t *__restrict__ gold,
                                                            const float *__restrict__ grad,
                                                            float *__restrict__ loss,
                                                            float *__restrict__ marg) {
     extern __shared__ __align__(16) char smem_raw[];
-    if constexpr (SPILL && !TEAM) {
+    if constexpr (!TEAM) {
         inside_block<true, true, true>(p, blockIdx.x, nullptr, smem_raw, scores, grad, nullptr, marg, gold, loss);
-    } else if constexpr (SPILL) {
+    } else {
         Team tm;
         int job, stride;
         if (!spill_jobs(p, tm, job, stride)) return;
@@ -1881,9 +1881,7 @@ __global__ __launch_bounds__(kThreadsMax) void loss_kernel(KernelPlan p, const f
             inside_block<true, true, true>(p, job, nullptr, smem_raw, scores, grad, nullptr, marg, gold, loss, tm);
             __syncthreads();
         }
-    } else
-        inside_block<true, false, true>(p, blockIdx.x, p.inside.recs + (size_t)blockIdx.x * p.rec_stride, smem_raw,
-                                        scores, grad, nullptr, marg, gold, loss);
+    }
 }
 
 template <bool SPILL, bool LAB, bool TEAM = false>
@@ -1899,7 +1897,7 @@ __global__ __launch_bounds__(kThreadsMax) void cky_kernel(KernelPlan p, const fl
         int job, stride;
         if (!spill_jobs(p, tm, job, stride)) return;
         for (; job < p.cky.n_spill; job += stride, ++tm.job) {
-            cky_block<true, LAB>(p, job, nullptr, smem_raw, scores, spans, best, labels, false, tm);
+            cky_block<true, LAB>(p, job, nullptr, smem_raw, scores, spans, best, labels, tm);
             __syncthreads();
         }
     } else
@@ -1946,32 +1944,8 @@ __global__ __launch_bounds__(kThreadsMax) void spill_parse_kernel(KernelPlan p, 
         if (job < p.inside.n_spill)
             inside_block<true, true>(p, job, nullptr, smem_raw, scores, grad, logZ, marg, nullptr, nullptr, tm);
         else
-            cky_block<true>(p, job - p.inside.n_spill, nullptr, smem_raw, scores, spans, best, nullptr, false, tm);
+            cky_block<true>(p, job - p.inside.n_spill, nullptr, smem_raw, scores, spans, best, nullptr, tm);
         __syncthreads();
-    }
-}
-
-// MBR decoding (Sec. 3.3) in one launch: each bundle runs the inside sweep
-// with the outside and writes the marginals, then CKY with the marginals in
-// place of the scores, in the same workgroup.  The CKY prologue reads back
-// exactly the cells this thread wrote (the same cell walk over the same
-// bundle), so the marginals come from this CU's cache, and the LDS charts are
-// reused.  Persistent, bundles claimed as in parse_kernel.
-__global__ __launch_bounds__(kThreadsMax) void mbr_kernel(KernelPlan p, const float *__restrict__ scores,
-                                                          float *__restrict__ logZ, float *marg,
-                                                          int32_t *__restrict__ spans,
-                                                          float *__restrict__ best) {
-    extern __shared__ __align__(16) char smem_raw[];
-    __shared__ int slot;
-    int cur = blockIdx.x;
-    for (;;) {
-        const int32_t *rec = p.mbr + (size_t)cur * p.rec_stride;
-        inside_block<true, false>(p, 0, rec, smem_raw, scores, nullptr, logZ, marg);
-        __syncthreads();   // the marginals are written and the inside charts are free
-        cky_block<false>(p, 0, rec, smem_raw, marg, spans, best, nullptr, true);
-        if ((int)gridDim.x >= p.n_mbr) break;
-        cur = claim_next(p.counter, p.n_mbr, &slot);
-        if (cur >= p.n_mbr) break;
     }
 }
 
@@ -2093,7 +2067,7 @@ int spill_blocks_per_cu() {
     const void *fns[] = {
         (const void *)inside_kernel<false, true, false, true>, (const void *)inside_kernel<true, true, false, true>,
         (const void *)cky_kernel<true, false, true>,           (const void *)cky_kernel<true, true, true>,
-        (const void *)loss_kernel<true, true>,                 (const void *)spill_parse_kernel<true>,
+        (const void *)loss_kernel<true>,                       (const void *)spill_parse_kernel<true>,
     };
     int least = 1 << 30;
     for (const void *f : fns) {
@@ -2109,11 +2083,9 @@ int spill_blocks_per_cu() {
 
 hipError_t set_kernel_attributes(int max_lds_bytes) {
     const void *fns[] = {
-        (const void *)inside_kernel<false, false>,        (const void *)inside_kernel<true, false>,
         (const void *)inside_kernel<false, false, true>,  (const void *)inside_kernel<true, false, true>,
         (const void *)cky_kernel<false, false>,           (const void *)cky_kernel<false, true>,
-        (const void *)loss_kernel<false>,                 (const void *)parse_kernel,
-        (const void *)mbr_kernel,
+        (const void *)parse_kernel,
     };
     for (const void *f : fns) {
         hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds_bytes);
@@ -2154,10 +2126,10 @@ static hipError_t launch_inside_sweeps(const KernelPlan &p, const float *scores,
                                        float *marg, hipStream_t stream) {
     const Schedule &q = p.inside;
     hipError_t e;
-    if (!LAB && p.tile_on) {
+    if constexpr (!LAB) {
         if ((e = launch_tile_inside(p, scores, grad, logZ, marg, stream)) != hipSuccess) return e;
     } else if (q.n_bundles > 0) {
-        launch_inside_k<false, LAB>(p, dim3(q.n_bundles), q.threads, q.lds_bytes, stream, scores, grad, logZ, marg);
+        launch_inside_k<false, true>(p, dim3(q.n_bundles), q.threads, q.lds_bytes, stream, scores, grad, logZ, marg);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (q.n_spill > 0 && !(p.tile_on && p.tile_long)) {
@@ -2238,26 +2210,11 @@ hipError_t launch_cky(const KernelPlan &p, const float *scores, int32_t *spans, 
 
 hipError_t launch_mbr(const KernelPlan &p, const float *scores, float *logZ, float *marg, int32_t *spans,
                       float *best, hipStream_t stream) {
-    if (!p.tile_on && (p.mbr == nullptr || p.counter == nullptr || p.mbr_grid < 1)) {
-        // separate launches, in stream order: inside + marginals, then CKY
-        // over the marginals
-        hipError_t e = launch_inside(p, scores, nullptr, logZ, marg, stream);
-        if (e != hipSuccess) return e;
-        return launch_cky(p, marg, spans, best, stream);
-    }
-    hipError_t e;
-    if (p.tile_on) {
-        e = launch_tile_mbr(p, scores, logZ, marg, spans, best, stream);
-    } else {
-        hipLaunchKernelGGL(mbr_kernel, dim3(p.mbr_grid), dim3(p.inside.threads), (size_t)p.mbr_lds, stream, p, scores,
-                           logZ, marg, spans, best);
-        e = hipGetLastError();
-    }
+    hipError_t e = launch_tile_mbr(p, scores, logZ, marg, spans, best, stream);
     if (e != hipSuccess) return e;
-    // sentences too long for LDS (the plan has checked that the inside and
-    // CKY workspace lists hold the same sentences): their marginals, then
-    // CKY over them
-    if (p.inside.n_spill > 0 && !(p.tile_on && p.tile_long)) {
+    // sentences left to the workspace kernels (the same in the inside and the
+    // CKY list): their marginals, then CKY over them
+    if (p.inside.n_spill > 0 && !p.tile_long) {
         KernelPlan t = p;
         dim3 grid;
         if ((e = spill_launch_shape(t, p.inside.n_spill, stream, &grid)) != hipSuccess) return e;
@@ -2279,22 +2236,16 @@ hipError_t launch_loss(const KernelPlan &p, const float *scores, const int32_t *
                        float *loss, float *grad_scores, hipStream_t stream) {
     const Schedule &q = p.inside;
     hipError_t e;
-    if (p.tile_on) {
-        if ((e = launch_tile_loss(p, scores, gold, grad, loss, grad_scores, stream)) != hipSuccess) return e;
-    } else if (q.n_bundles > 0) {
-        hipLaunchKernelGGL((loss_kernel<false>), dim3(q.n_bundles), dim3(q.threads), (size_t)q.lds_bytes, stream, p,
-                           scores, gold, grad, loss, grad_scores);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (q.n_spill > 0 && !(p.tile_on && p.tile_long)) {
+    if ((e = launch_tile_loss(p, scores, gold, grad, loss, grad_scores, stream)) != hipSuccess) return e;
+    if (q.n_spill > 0 && !p.tile_long) {
         KernelPlan t = p;
         dim3 grid;
         if ((e = spill_launch_shape(t, q.n_spill, stream, &grid)) != hipSuccess) return e;
         if (t.team_k > 1)
-            hipLaunchKernelGGL((loss_kernel<true, true>), grid, dim3(kThreadsMax), 0, stream, t, scores, gold, grad, loss,
+            hipLaunchKernelGGL(loss_kernel<true>, grid, dim3(kThreadsMax), 0, stream, t, scores, gold, grad, loss,
                                grad_scores);
         else
-            hipLaunchKernelGGL((loss_kernel<true>), grid, dim3(kThreadsMax), 0, stream, t, scores, gold, grad, loss,
+            hipLaunchKernelGGL(loss_kernel<false>, grid, dim3(kThreadsMax), 0, stream, t, scores, gold, grad, loss,
                                grad_scores);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -2316,22 +2267,12 @@ hipError_t launch_parse(const KernelPlan &p, const float *scores, const float *g
     hipError_t e;
     if (p.tile_on) {
         if ((e = launch_tile_parse(p, scores, grad, logZ, marg, spans, best, stream)) != hipSuccess) return e;
-    } else if (p.mix != nullptr && p.counter != nullptr && p.fused_grid >= 1 && p.n_mix == qi.n_bundles + qc.n_bundles) {
+    } else if (qi.n_bundles > 0) {   // the no-allocation call (launch_parse_scratch): the plan then has a mix
+        if (p.n_mix != qi.n_bundles + qc.n_bundles || qi.threads != qc.threads) return hipErrorInvalidValue;
         const size_t lds = (size_t)(qi.lds_bytes > qc.lds_bytes ? qi.lds_bytes : qc.lds_bytes);
         hipLaunchKernelGGL(parse_kernel, dim3(p.fused_grid), dim3(qi.threads), lds, stream, p,
                            scores, grad, logZ, marg, spans, best);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-    } else {
-        // the LDS bundles of each pass as its own launch
-        if (qi.n_bundles > 0) {
-            launch_inside_k<false>(p, dim3(qi.n_bundles), qi.threads, qi.lds_bytes, stream, scores, grad, logZ, marg);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
-        if (qc.n_bundles > 0) {
-            hipLaunchKernelGGL((cky_kernel<false, false>), dim3(qc.n_bundles), dim3(qc.threads), (size_t)qc.lds_bytes,
-                               stream, p, scores, spans, best, nullptr);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
     }
     if (qi.n_spill + qc.n_spill > 0 && !(p.tile_on && p.tile_long)) {
         KernelPlan t = p;

@@ -461,33 +461,6 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
     }
     sc.ws_bytes = split_cursor - si.ws_bytes;
 
-    // MBR decoding (unlabelled plans): bundles whose workgroup holds the
-    // inside chart and then, in the same LDS, the CKY chart over the
-    // marginals, so a bundle's LDS is the larger of the two.  Sentences past
-    // LDS run on the inside and CKY workspace kernels, which must then list
-    // the same sentences; if they do not, or no bundle is left, MBR decoding
-    // runs as separate launches.
-    HostSchedule sm;
-    bool mbr_fused = num_labels == 1;
-    if (mbr_fused) {
-        auto mbr_bytes = [=](int n, int64_t count) {
-            return std::max(inside_bundle_bytes(n, count), cky_bundle_bytes(n, count));
-        };
-        sm = make_schedule(order, lengths_host, lds_cap, force, 0, mbr_bytes, [](int) { return (int64_t)0; },
-                           kCkyTargetScale);
-        auto sorted = [](std::vector<int32_t> v) {
-            std::sort(v.begin(), v.end());
-            return v;
-        };
-        const std::vector<int32_t> ms = sorted(sm.spill);
-        mbr_fused = !sm.bundles.empty() && ms == sorted(si.spill) && ms == sorted(sc.spill);
-        if (mbr_fused)
-            for (crf::Bundle &bd : sm.bundles) {
-                if (split_in_lds(bd.n)) continue;
-                bd.split_ws = (int32_t)(split_cursor / 256);
-                split_cursor += (bd.count * crf::cky_split_count(bd.n) + 255) / 256 * 256;
-            }
-    }
     // Labelled plans: the label log-sum-exps and their marginals, [B][N1][N1]
     // float32 each, and the chunks of the label passes.
     std::vector<int32_t> lab_rows;
@@ -588,23 +561,13 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
     int max_count = 1;
     for (const crf::Bundle &bd : si.bundles) max_count = std::max(max_count, (int)bd.count);
     for (const crf::Bundle &bd : sc.bundles) max_count = std::max(max_count, (int)bd.count);
-    if (mbr_fused)
-        for (const crf::Bundle &bd : sm.bundles) max_count = std::max(max_count, (int)bd.count);
     const int stride = crf::kRecHeader + max_count;
     kp.rec_stride = stride;
-    auto put_inside_layout = [&](int32_t *q, int n, int count, int off) {
-        const crf::InsideLayout l = crf::inside_layout(n, count, inside_strict(n, count));
-        q[crf::kRecE + off] = l.e;
-        q[crf::kRecLd + off] = l.ld;
-        q[crf::kRecCs + off] = l.cs;
+    auto put_layout = [](int32_t *q, const auto &l) {
+        q[crf::kRecE] = l.e;
+        q[crf::kRecLd] = l.ld;
+        q[crf::kRecCs] = l.cs;
     };
-    auto put_cky_layout = [&](int32_t *q, int n, int count, int off) {
-        const crf::CkyLayout l = crf::cky_layout(n, count, split_in_lds(n) ? 1 : 0, cky_strict(n, count));
-        q[crf::kRecE + off] = l.e;
-        q[crf::kRecLd + off] = l.ld;
-        q[crf::kRecCs + off] = l.cs;
-    };
-    constexpr int kSecond = crf::kRecE2 - crf::kRecE;   // offset of the second layout's fields
     auto records = [&](const HostSchedule &h, int kind) {
         std::vector<int32_t> r((size_t)h.bundles.size() * stride, 0);
         for (size_t b = 0; b < h.bundles.size(); ++b) {
@@ -615,33 +578,20 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
             q[crf::kRecSplitWs] = kind == crf::kKindInside ? -1 : bd.split_ws;
             q[crf::kRecKind] = kind;
             q[crf::kRecLab] = kind == crf::kKindInside && num_labels > 1 && bd.n <= crf::kLabInBundleMaxN;
-            if (kind == crf::kKindCky) {
-                put_cky_layout(q, bd.n, bd.count, 0);
-            } else {
-                put_inside_layout(q, bd.n, bd.count, 0);
-                if (kind == crf::kKindMbr) put_cky_layout(q, bd.n, bd.count, kSecond);
-            }
+            if (kind == crf::kKindCky)
+                put_layout(q, crf::cky_layout(bd.n, bd.count, split_in_lds(bd.n) ? 1 : 0, cky_strict(bd.n, bd.count)));
+            else
+                put_layout(q, crf::inside_layout(bd.n, bd.count, inside_strict(bd.n, bd.count)));
             q[crf::kRecMagic] = (int32_t)crf::div_magic(bd.count);
             for (int t = 0; t < bd.count; ++t) q[crf::kRecHeader + t] = h.order[bd.first + t];
         }
         return r;
     };
     const std::vector<int32_t> rec_in = records(si, crf::kKindInside), rec_ck = records(sc, crf::kKindCky);
-    const std::vector<int32_t> rec_mbr = mbr_fused ? records(sm, crf::kKindMbr) : std::vector<int32_t>();
     kp.n_lab_rows = (int32_t)(lab_rows.size() / 4);
     kp.n_bia_tiles = (int32_t)(bia.size() / (crf::kBiaRows + crf::kBiaCols));
     kp.lab_sp_off = lab_sp_off;
     kp.lab_mu_off = lab_mu_off;
-    kp.n_mbr = mbr_fused ? (int32_t)sm.bundles.size() : 0;
-    kp.mbr_lds = mbr_fused ? sm.lds_bytes : 0;
-    kp.mbr_grid = 0;
-    if (mbr_fused) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, p->device) != hipSuccess || cus < 1)
-            cus = 256;
-        const int per_cu = std::min(4, std::max(1, (int)(lds_cap / std::max(1, sm.lds_bytes))));
-        kp.mbr_grid = std::min<int32_t>(kp.n_mbr, cus * per_cu);
-    }
     std::vector<int32_t> rec_mix;
     rec_mix.reserve(mix.size() * stride);
     for (int32_t e : mix) {
@@ -761,7 +711,6 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
         (e = upload(p, sc.spill, &kp.cky.order_spill)) != hipSuccess ||
         (e = upload(p, sc.off, &kp.cky.ws_off)) != hipSuccess ||
         (e = upload(p, rec_mix, &kp.mix)) != hipSuccess ||
-        (e = upload(p, rec_mbr, &kp.mbr)) != hipSuccess ||
         (e = upload(p, lab_rows, &kp.lab_rows)) != hipSuccess ||
         (e = upload(p, bia, &kp.bia_tiles)) != hipSuccess ||
         (e = upload(p, tile_recs, &kp.tile_io.recs)) != hipSuccess ||
@@ -776,17 +725,7 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
         kp.tile_ck.recs = kp.tile_io.recs + (size_t)kp.tile_io.n * kp.tile_stride;
         kp.tile_mix.recs = kp.tile_ck.recs + (size_t)kp.tile_ck.n * kp.tile_stride;
     }
-    kp.counter = nullptr;
-    if (kp.fused_grid > 0 || kp.mbr_grid > 0) {
-        void *c = nullptr;
-        if ((e = hipMalloc(&c, 256)) != hipSuccess || (p->allocations.push_back(c), false) ||
-            (e = hipMemset(c, 0, 256)) != hipSuccess) {
-            release(p);
-            delete p;
-            return hip_fail(e, "claim counter");
-        }
-        kp.counter = static_cast<int32_t *>(c);
-    }
+    kp.counter = nullptr;   // (the no-allocation call's, in its scratch)
     // Teams for the workspace sentences: the workgroups the device holds at
     // once, and the team area (none when no team of two fits).
     kp.team_area = nullptr;
@@ -822,7 +761,7 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
     }
     // Best effort: ROCm launches with any dynamic LDS up to the per-block
     // limit without this attribute; a real shortfall surfaces as a launch error.
-    if (crf::set_kernel_attributes(std::max(std::max(std::max(si.lds_bytes, sc.lds_bytes), kp.mbr_lds), kp.tile_mix.lds_bytes)) != hipSuccess)
+    if (crf::set_kernel_attributes(std::max(std::max(si.lds_bytes, sc.lds_bytes), kp.tile_mix.lds_bytes)) != hipSuccess)
         (void)hipGetLastError();
     if (crf::set_biaffine_attributes() != hipSuccess) (void)hipGetLastError();
     // Resolve this device's scratch address for the no-allocation entry
@@ -852,16 +791,21 @@ int crf_plan_info(const crf_plan *plan, crf_plan_stats *out) {
     out->n1 = plan->n1;
     out->num_labels = plan->L;
     out->max_len = plan->max_len;
-    out->lds_count = plan->B - plan->kp.inside.n_spill;
-    out->spill_count = plan->kp.inside.n_spill;
+    const crf::KernelPlan &kp = plan->kp;
+    // Unlabelled plans run on tile charts, in LDS or in the workspace, but for
+    // what tile_long and tile_cky leave to the charts of single spans; every
+    // sentence is on the same side for the inside and for CKY.
+    const int32_t ws = kp.tile_ws.n + (kp.tile_long ? 0 : kp.inside.n_spill);
+    out->spill_count = kp.tile_on ? ws : kp.inside.n_spill;
+    out->lds_count = plan->B - out->spill_count;
     out->workspace_bytes = plan->ws_bytes;
-    out->lds_bytes_inside = plan->kp.inside.lds_bytes;
-    out->lds_bytes_cky = plan->kp.cky.lds_bytes;
-    out->cky_spill_count = plan->kp.cky.n_spill;
-    out->split_ws_count = plan->split_ws_count;
-    out->workspace_users = plan->workspace_users;
-    out->fused_queue = plan->kp.counter != nullptr ? 1 : 0;
-    out->mbr_fused = plan->kp.mbr != nullptr ? 1 : 0;
+    out->lds_bytes_inside = kp.tile_on ? kp.tile_io.lds_bytes : kp.inside.lds_bytes;
+    out->lds_bytes_cky = kp.tile_cky ? kp.tile_ck.lds_bytes : kp.cky.lds_bytes;
+    out->cky_spill_count = kp.tile_on ? ws : kp.cky.n_spill;
+    out->split_ws_count = kp.tile_cky ? 0 : plan->split_ws_count;
+    out->workspace_users = kp.tile_on ? ws + out->split_ws_count : plan->workspace_users;
+    out->fused_queue = 0;
+    out->mbr_fused = kp.tile_io.n > 0 ? 1 : 0;
     return ok();
 }
 

@@ -4,8 +4,9 @@
 //   P n_mix fused_grid lds_inside lds_cky half_cu
 //   W spill cky_spill split_ws workspace_users workspace_bytes fused_queue
 //   R kind n count split_ws strict ld cs e bytes id...
-// one R line per record of the fused queue, in queue order; M lines for the
-// MBR bundles, I lines for labelled plans' inside bundles, T lines for the
+// one R line per record of the fused queue, in queue order; G, B and X lines
+// for the tile charts and V lines for workspace charts of single spans (see
+// below), I lines for labelled plans' inside bundles, T lines for the
 // biaffine scorer's tiles.  Arguments: a file
 // of sentence lengths, and optionally the number of labels.
 #include <cstdio>
@@ -211,24 +212,39 @@ int main(int argc, char **argv) {
         for (int t = 0; t < count; ++t) std::printf(" %d", r[crf::kRecHeader + t]);
         std::printf("\n");
     }
-    // MBR bundles, as
-    //   M n count split_ws inside_strict cky_strict mbr_grid mbr_lds id...
-    for (int b = 0; b < kp.n_mbr; ++b) {
-        const int32_t *r = kp.mbr + (size_t)b * kp.rec_stride;
-        const int n = r[crf::kRecN], count = r[crf::kRecCount];
-        const crf::InsideLayout li = crf::inside_layout(n, count, true);
-        const crf::CkyLayout lc = crf::cky_layout(n, count, r[crf::kRecSplitWs] < 0 ? 1 : 0, true);
-        const int si = li.ld == r[crf::kRecLd] && li.cs == r[crf::kRecCs] && li.e == r[crf::kRecE];
-        const int sc = lc.ld == r[crf::kRecLd2] && lc.cs == r[crf::kRecCs2] && lc.e == r[crf::kRecE2];
-        if (r[crf::kRecKind] != crf::kKindMbr) {
-            std::printf("E kind\n");
-            return 1;
+    // Tile charts, as
+    //   G tile_on tile_long tile_scratch tile_cky tile_threads scratch_bytes mbr_fused lds_inside lds_cky
+    //   B launch kind m count pitch lds_bytes used_bytes pieces (id length)...   (launch: 0 inside, 1 CKY, 2 fused)
+    //   X kind m first_byte end_byte id length                               (workspace records)
+    std::printf("G %d %d %d %d %d %lld %d %d %d\n", kp.tile_on, kp.tile_long, kp.tile_scratch, kp.tile_cky, kp.tile_threads,
+                (long long)p->scratch_bytes, st.mbr_fused, st.lds_bytes_inside, st.lds_bytes_cky);
+    const crf::TileSchedule *const launches[] = {&kp.tile_io, &kp.tile_ck, &kp.tile_mix};
+    for (int l = 0; l < 3; ++l)
+        for (int b = 0; b < launches[l]->n; ++b) {
+            const int32_t *r = launches[l]->recs + (size_t)b * kp.tile_stride;
+            const int m = r[crf::kTrM], S = r[crf::kTrCount];
+            if ((uint32_t)r[crf::kTrMagic] != crf::div_magic(S)) {
+                std::printf("E tile magic\n");
+                return 1;
+            }
+            const long long used = r[crf::kTrKind] == crf::kKindInside ? crf::tile_io_bytes(m, S, r[crf::kTrPitch])
+                                                                       : crf::tile_ck_bytes(m, S);
+            std::printf("B %d %d %d %d %d %d %lld %d", l, r[crf::kTrKind], m, S, r[crf::kTrPitch], launches[l]->lds_bytes,
+                        used, crf::tile_pieces(m, S));
+            for (int t = 0; t < 2 * S; ++t) std::printf(" %d", r[crf::kTrHeader + t]);
+            std::printf("\n");
         }
-        const long long ib = crf::inside_bundle_bytes(n, count, si != 0);
-        std::printf("M %d %d %d %d %d %d %d %lld", n, count, r[crf::kRecSplitWs], si, sc, kp.mbr_grid, kp.mbr_lds, ib);
-        for (int t = 0; t < count; ++t) std::printf(" %d", r[crf::kRecHeader + t]);
-        std::printf("\n");
+    for (int b = 0; b < 2 * kp.tile_ws.n; ++b) {
+        const int32_t *r = kp.tile_ws.recs + (size_t)b * (crf::kTrHeader + 2);
+        const int m = r[crf::kTrM];
+        const long long at = 256LL * r[crf::kTrPitch];
+        std::printf("X %d %d %lld %lld %d %d\n", r[crf::kTrKind], m, at,
+                    at + (r[crf::kTrKind] == crf::kKindInside ? crf::tile_ws_io_bytes(m) : crf::tile_ws_ck_bytes(m)),
+                    r[crf::kTrHeader], r[crf::kTrHeader + 1]);
     }
+    for (int b = 0; b < kp.inside.n_spill; ++b)   // the charts of single spans in the workspace
+        std::printf("V %d %d %lld %lld\n", kp.inside.order_spill[b], kp.cky.order_spill[b], (long long)kp.inside.ws_off[b],
+                    (long long)kp.cky.ws_off[b]);
     // Labelled plans have no fused queue: their inside bundles, as
     //   I n count id...
     for (int b = 0; kp.n_mix == 0 && b < kp.inside.n_bundles; ++b) {

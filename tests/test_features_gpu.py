@@ -227,6 +227,12 @@ def test_labeled_cky_label_counts(torch, labels):
     lcky_check(torch, W.custom([1, 2, 5, 17, 40, 64], seed=400 + labels, sd=1.0, labels=labels))
 
 
+def test_labeled_cky_step_shape_boundaries(torch):
+    # both sides of every change of step shape (a step per width), and of LDS
+    lcky_check(torch, W.custom([2, 3, 4, 5, 6, 9, 10, 17, 18, 33, 34, 49, 50, 65, 66, 97, 98, 129, 130, 141, 142, 143],
+                               seed=45, sd=1.0, labels=2))
+
+
 def test_labeled_cky_ties_and_workspace(torch):
     # integer scores: equal labels and equal trees; a 150-word sentence on the
     # workspace kernel

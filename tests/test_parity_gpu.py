@@ -191,7 +191,7 @@ def test_short_and_padded(torch):
 def test_scores_beyond_the_linear_range(torch, sd, mean):
     # sd 10: a spread that a float32 chart of exp2 values cannot hold past a
     # few words -- the sweeps detect it and redo those bundles in the log
-    # domain, on LDS charts (n <= 142) and workspace charts alike (every
+    # domain, on LDS charts and workspace charts alike (every
     # sentence but the 3-word one, measured with a build that skips the redo).
     # Offsets of +-60 nats stay in the linear domain: the per-sentence shift,
     # seeded from the scores' mean, absorbs them.
@@ -319,13 +319,25 @@ def test_autograd_function(torch):
 
 def test_step_shape_boundaries(torch):
     # lengths on both sides of every change of step shape (split counts 1, 2,
-    # 3, 5, 9, 17, 33, 49, 65, 97, 129), the last length whose CKY chart fits
-    # in LDS (142) and the first that does not (143)
+    # 3, 5, 9, 17, 33, 49, 65, 97, 129), the last length whose charts of single
+    # spans fit in LDS (141) and the first ones that do not.  Unlabelled calls
+    # run on tile charts; the steps of single spans are test_step_shape_boundaries_labeled
     lengths = [2, 3, 4, 5, 6, 9, 10, 17, 18, 33, 34, 49, 50, 65, 66, 97, 98, 129, 130, 142, 143]
     b = W.custom(lengths, seed=21, sd=2.0)
     out, worst = full_check(torch, b)
     assert out["info"]["spill_count"] >= 1
     print(f"shape boundaries: max |marginal error| {worst:.2e}")
+
+
+def test_step_shape_boundaries_labeled(torch):
+    # the same lengths on the charts of single spans, which labelled plans use
+    # (CKY there: test_features_gpu.py)
+    lengths = [2, 3, 4, 5, 6, 9, 10, 17, 18, 33, 34, 49, 50, 65, 66, 97, 98, 129, 130, 141, 142, 143]
+    b = W.custom(lengths, seed=21, sd=2.0, labels=2)
+    out = gpu_run(torch, b)
+    assert out["info"]["spill_count"] == 2
+    worst = check_labeled_chunks(out, b, chunk=b.B)
+    print(f"shape boundaries, labelled: max |marginal error| {worst:.2e}")
 
 
 def test_many_short_sentences(torch):
@@ -342,8 +354,13 @@ def test_bundle_counts_and_chart_strides(torch, n, count):
     # counts of various factors of two: the inside chart strides depend on
     # both (strict and loose layouts, spans interleaved across half-wavefronts
     # or side by side, rows changing inside a half).
+    # (The inside charts of unlabelled plans are tiles; CKY alone, with a
+    # sentence of more than 28 words, takes a width a step, and the inside of a
+    # labelled plan does.)
     b = W.custom([n] * count + [99] * 200, seed=100 + n + count, sd=2.0)
     full_check(torch, b)
+    b = W.custom([n] * count + [99] * 40, seed=200 + n + count, sd=2.0, labels=2)
+    check_labeled_chunks(gpu_run(torch, b), b, chunk=b.B)
 
 
 def test_longest_sentence(torch):
@@ -354,12 +371,16 @@ def test_longest_sentence(torch):
     print(f"n = 1023: max |marginal error| {worst:.2e}")
 
 
-def test_workspace_teams(torch):
-    # 16 sentences of 150..256 words: few enough that the workspace launches
-    # split each sentence pass over a team of 8 (fused, 32 passes) or 16
-    # workgroups of one XCD, several teams per XCD; every entry point against
-    # the oracle
+@pytest.mark.parametrize("longest", [256, 410])
+def test_workspace_teams(torch, longest):
+    # 16 sentences of 150..256 words, or one of them of more than 400: then the
+    # workspace launches split each sentence pass over a team of 8 (fused, 32
+    # passes) or 16 workgroups of one XCD, several teams per XCD (else a
+    # workgroup a sentence, on tile charts); every entry point against the
+    # oracle
     lengths = [int(x) for x in np.random.default_rng(25).integers(150, 257, size=16)]
+    if longest > 256:
+        lengths[5] = longest
     b = W.custom(lengths, seed=25, sd=2.0)
     out, worst = full_check(torch, b)
     assert out["info"]["spill_count"] == b.B
@@ -370,12 +391,13 @@ def test_workspace_teams_bit_identical(torch):
     # teams split each step's lanes over workgroups but keep every span's
     # arithmetic: every workspace entry point gives the same bits as with one
     # workgroup per sentence pass (CRF_NO_TEAMS), LDS bundles beside them
-    b = W.custom([256, 201, 150, 143, 30, 7], seed=26, sd=2.0)
+    # (one sentence of more than 400 words: else no team takes them)
+    b = W.custom([402, 256, 201, 150, 143, 141, 30, 7], seed=26, sd=2.0)
     gold, _ = orc.cky(b.scores, b.lengths)
     dev = torch.device("cuda", 0)
     s = torch.from_numpy(b.scores).to(dev)
     g = torch.from_numpy(np.ascontiguousarray(gold, np.int32)).to(dev)
-    grad = torch.tensor([1.0, -0.5, 2.0, 0.25, 1.0, 3.0], dtype=torch.float32, device=dev)
+    grad = torch.tensor([1.0, -0.5, 2.0, 0.25, 1.0, 3.0, -1.0, 0.5], dtype=torch.float32, device=dev)
 
     def run(flags):
         with B.Plan(b.lengths, n1=b.n1, flags=flags, device=dev) as plan:
@@ -387,14 +409,16 @@ def test_workspace_teams_bit_identical(torch):
 
     teams, info_t = run(0)
     lone, info_l = run(B.CRF_NO_TEAMS)
-    assert info_t["spill_count"] == 4 and info_l["spill_count"] == 4
+    # (141 words: in the workspace too, but on tile charts)
+    assert info_t["spill_count"] == 6 and info_l["spill_count"] == 6
     for i, (x, y) in enumerate(zip(teams, lone)):
         assert np.array_equal(x, y, equal_nan=True), f"output {i} differs between teams and lone workgroups"
     assert np.all(np.isfinite(teams[0]))
 
 
 def test_split_tables_in_workspace(torch):
-    # sentences whose CKY chart leaves no room in half a CU for the split
+    # sentences whose CKY chart of single spans (CKY alone, labelled or with no
+    # sentence in the workspace) leaves no room in half a CU for the split
     # table keep it in global memory; a longer one moves every bundle to a
     # whole CU
     b = W.custom([97, 97, 98, 99, 99, 120, 3, 40], seed=24, sd=2.0)
@@ -403,8 +427,8 @@ def test_split_tables_in_workspace(torch):
 
 @pytest.mark.parametrize("name", ["tiny", "mixed"])
 def test_fused_repeat_launches(torch, name):
-    # the fused kernel's workgroups pull bundles from a counter that the last
-    # claim resets: back-to-back launches on one plan give the same bits
+    # back-to-back fused launches on one plan give the same bits, and those of
+    # the separate calls
     b = W.make(name)
     dev = torch.device("cuda", 0)
     s = torch.from_numpy(b.scores).to(dev)

@@ -2,7 +2,8 @@
 allocation calls (tests/plan_host_stub.cpp) and checked on synthetic batches:
 every sentence in exactly one inside and one CKY bundle, each bundle within
 the launch's LDS, the chart layouts' stride congruences (the condition under
-which the sweeps' LDS reads are bank-conflict free), and the fused queue.
+which the sweeps' LDS reads are bank-conflict free), the fused queue of the
+no-allocation call, and the tile charts' bundles and workspace charts.
 """
 import os
 import shutil
@@ -61,11 +62,17 @@ def plan_of(harness, tmp_path, lengths, labels=None, flags=0):
             v = list(map(int, t[1:]))
             head["n1"] = v[0]
             head.setdefault("tiles", []).append(v[1:])
-        elif t[0] == "M":
+        elif t[0] == "G":
+            head.update(zip(["tile_on", "tile_long", "tile_scratch", "tile_cky", "tile_threads", "scratch_bytes",
+                             "mbr_fused", "info_lds_in", "info_lds_ck"], map(int, t[1:])))
+        elif t[0] == "B":
             v = list(map(int, t[1:]))
-            head.setdefault("mbr", []).append(dict(n=v[0], count=v[1], split_ws=v[2], inside_strict=v[3],
-                                                   cky_strict=v[4], grid=v[5], lds=v[6], inside_bytes=v[7],
-                                                   ids=v[8:]))
+            head.setdefault("bundles", []).append(dict(launch=v[0], kind=v[1], m=v[2], count=v[3], pitch=v[4], lds=v[5],
+                                                       used=v[6], pieces=v[7], ids=v[8::2], lens=v[9::2]))
+        elif t[0] == "X":
+            head.setdefault("ws_tiles", []).append(tuple(map(int, t[1:])))
+        elif t[0] == "V":
+            head.setdefault("ws_spans", []).append(tuple(map(int, t[1:])))
     return head, recs
 
 
@@ -156,7 +163,7 @@ def test_workspace_users_reported(harness, tmp_path):
     long_ones = int(np.sum(b.lengths >= 97))
     assert long_ones >= 1
     assert head["split_ws"] == long_ones and head["ws_users"] == long_ones
-    assert head["ws_bytes"] > 0 and head["fused_queue"] == 1
+    assert head["ws_bytes"] > 0
     # a batch of short sentences uses no workspace at all
     head, _ = plan_of(harness, tmp_path, [5, 9, 30, 60] * 10)
     assert head["ws_users"] == 0 and head["ws_bytes"] == 0
@@ -215,29 +222,96 @@ def test_team_launch_shapes(harness):
     assert res.stdout.splitlines()[-1] == "N 1 5"     # no team area: a workgroup per job
 
 
-@pytest.mark.parametrize("name", ["tiny", "mixed", "longer"])
-def test_mbr_bundles(harness, tmp_path, name):
-    # MBR bundles: every sentence in exactly one, of its own length, within
-    # the launch's LDS with either chart; split tables of long sentences in
-    # the workspace; one workgroup slot per CU per bundle LDS that fits
-    b = W.make(name)
-    head, _ = plan_of(harness, tmp_path, b.lengths)
-    mb = head["mbr"]
-    ids = sorted(i for r in mb for i in r["ids"])
-    assert ids == list(range(b.B))
-    lds = mb[0]["lds"]
-    for r in mb:
-        assert r["count"] == len(r["ids"]) and all(b.lengths[i] == r["n"] for i in r["ids"])
-        assert r["inside_bytes"] <= lds
-        assert (r["split_ws"] >= 0) == (r["n"] >= 97)
-        assert r["grid"] == min(len(mb), 256 * min(4, max(1, 163840 // lds)))
-    if name == "mixed":
-        assert lds <= head["half_cu"]          # two workgroups per CU
+SCRATCH_WS = (8 << 20) - 256   # the no-allocation call's workspace
 
 
-def test_mbr_not_fused_when_all_in_workspace(harness, tmp_path):
-    head, _ = plan_of(harness, tmp_path, [200, 150])
-    assert "mbr" not in head
+def check_tile_charts(head, lengths, teams=False, force=False):
+    """The tile charts' schedule: every sentence of up to 139 words in one
+    bundle of each launch and kind, of its own block count, within the LDS of
+    the launch (two workgroups a CU, or one), the lanes and the score pieces a
+    thread keeps; the others on charts of their own in the workspace.  teams:
+    sentences of more than 142 words are left to the kernels of single spans."""
+    lengths = np.asarray(lengths)
+    in_lds = np.flatnonzero(lengths <= 139) if not force else np.array([], int)
+    on_spans = np.flatnonzero((lengths > 142) | force) if teams else np.array([], int)
+    in_ws = np.setdiff1d(np.setdiff1d(np.arange(len(lengths)), in_lds), on_spans)
+    assert head["tile_on"] == 1 and head["tile_long"] == (0 if teams else 1)
+    bundles = head.get("bundles", [])
+    for launch, kinds in ((0, [1]), (1, [0]), (2, [0, 1])):
+        here = [r for r in bundles if r["launch"] == launch]
+        for kind in kinds:
+            assert sorted(i for r in here if r["kind"] == kind for i in r["ids"]) == list(in_lds)
+        assert sorted({r["kind"] for r in here}) == (kinds if len(in_lds) else [])
+    budget = head["half_cu"] if head["tile_threads"] == 256 else 163840 - 512
+    for r in bundles:
+        assert r["count"] == len(r["ids"]) >= 1 and [lengths[i] for i in r["ids"]] == r["lens"]
+        assert all(n // 4 + 1 == r["m"] for n in r["lens"])
+        assert r["used"] <= r["lds"] <= budget
+        assert r["m"] * r["count"] <= head["tile_threads"] or r["count"] == 1
+        if r["kind"] == 1:
+            assert r["pieces"] <= 6 * head["tile_threads"]
+            assert r["pitch"] >= r["m"] * r["count"] and (r["pitch"] % 2 == 0 or r["count"] == 1)
+        if r["launch"] == 0:   # MBR decoding runs CKY in the inside bundle's LDS
+            assert r["count"] * (72 * r["m"] * (r["m"] + 1) + 8) <= r["lds"]
+    charts = head.get("ws_tiles", [])
+    for kind in (0, 1):
+        assert sorted(c[4] for c in charts if c[0] == kind) == list(in_ws)
+    assert all(c[5] == lengths[c[4]] and c[1] == c[5] // 4 + 1 for c in charts)
+    spans = [(c[2], c[3]) for c in charts]
+    if teams:
+        assert sorted(v[0] for v in head["ws_spans"]) == sorted(v[1] for v in head["ws_spans"]) == list(on_spans)
+        spans.append((0, head["scratch_bytes"]))   # their charts, in use at the same time
+    spans.sort()
+    assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and (not spans or spans[-1][1] <= head["ws_bytes"])
+    assert head["spill"] == head["cky_spill"] == len(in_ws) + len(on_spans)
+    assert head["mbr_fused"] == (1 if len(in_lds) else 0)
+    # what does not fit the scratch as tiles runs on the fused queue, which must be there
+    need = max([c[3] for c in charts], default=0)
+    assert head["tile_scratch"] == (0 if need > SCRATCH_WS else 1)
+    if not head["tile_scratch"] and head["scratch_bytes"] <= SCRATCH_WS:
+        assert head["n_mix"] > 0 or len(in_lds) + np.sum(lengths[in_ws] <= 142) == 0
+
+
+@pytest.mark.parametrize("name", ["tiny", "mixed", "longer", "stress"])
+def test_tile_charts_of_workloads(harness, tmp_path, name):
+    lengths = W.make(name).lengths
+    head, _ = plan_of(harness, tmp_path, lengths)
+    check_tile_charts(head, lengths)
+
+
+@pytest.mark.parametrize("seed", range(8))
+def test_tile_charts_of_random_batches(harness, tmp_path, seed):
+    rng = np.random.default_rng(100 + seed)
+    lengths = rng.integers(1, [8, 30, 99, 100, 139, 142, 200, 400][seed] + 1, size=int(rng.integers(1, 1500)))
+    head, _ = plan_of(harness, tmp_path, lengths)
+    check_tile_charts(head, lengths)
+
+
+@pytest.mark.parametrize("lengths,flags,teams", [
+    ([400] * 3 + [30], 0, False),              # up to 400 words: tiles
+    ([401, 30], 0, True),
+    ([402, 141, 150, 30], 0, True),            # 140..142 words: tile charts behind the others' charts
+    ([500, 140, 141, 143, 139, 5], 0, True),
+    ([401] + [256] * 15, 0, True),             # 16 past LDS: teams
+    ([401] + [256] * 16, 0, False),            # 17: tiles
+    ([1023], 0, True),
+    ([1023] * 20, 0, False),
+    ([402, 141, 150, 30], 2, True),            # CRF_NO_TEAMS: the same kernels, a workgroup a pass, for the same bits
+    ([402, 141, 150, 30], 1, True),            # CRF_FORCE_SPILL
+    ([200, 141, 150, 30], 1, False),
+])
+def test_tile_charts_or_teams(harness, tmp_path, lengths, flags, teams):
+    head, _ = plan_of(harness, tmp_path, lengths, flags=flags)
+    check_tile_charts(head, lengths, teams, force=(flags & 1) != 0)
+
+
+def test_tile_charts_past_the_scratch(harness, tmp_path):
+    # sentences of 140..142 words keep their charts of single spans in LDS, so
+    # that a plan can fit the no-allocation call's scratch on those alone
+    lengths = [141] * 40 + [30] * 100
+    head, _ = plan_of(harness, tmp_path, lengths)
+    check_tile_charts(head, lengths)
+    assert not head["tile_scratch"] and head["scratch_bytes"] <= SCRATCH_WS and head["n_mix"] > 0
 
 
 def check_tiles(head, lengths, rows=64):

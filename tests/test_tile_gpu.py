@@ -26,7 +26,7 @@ CASES = {
     # around the first rescale (12 blocks) and half a CU (25 and 26 blocks)
     "rescale_and_half_cu": dict(lengths=[43, 44, 47, 48, 95, 96, 99]),
     "whole_cu": dict(lengths=[99, 100, 103, 104, 127, 128, 139]),
-    # 140 words and more are not tile sentences
+    # 140 words and more: past LDS
     "past_tiles": dict(lengths=[139, 140, 142, 143, 5]),
     "padding": dict(lengths=[9, 1, 30, 2], n1=41),
     # integer scores: ties between splits inside a block, between blocks and
@@ -42,6 +42,9 @@ CASES = {
     # charts in the workspace beside bundles in LDS: one block past LDS, splits
     # past 8 bits, the rescales of long sentences
     "workspace": dict(lengths=[140, 143, 255, 256, 260, 30]),
+    # few long sentences of which one has more than 400 words: teams take
+    # those, tile charts behind theirs the ones of 140 and 141
+    "teams_beside_tiles": dict(lengths=[402, 30, 141, 150, 140, 142, 12]),
     # too many long sentences for teams, and one of more than 400 words
     "workspace_many": dict(lengths=[150] * 16 + [402], sd=1.0),
     # scores of a trained model: one tree's spans far above the rest

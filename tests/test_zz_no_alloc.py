@@ -3,10 +3,11 @@ C ABI, against the entry point it is a variant of (crf_inside_fwd_bwd_cky,
 which the parity tests hold to the oracle) and against the oracle itself.
 
 Two calls in a row share the library's static scratch: the first on the
-5,000-sentence mixed batch (its 99-word sentence keeps a CKY split table in
-the workspace), the second on a smaller batch whose 200-word sentence keeps
-both charts there; then the first plan again.  A plan that needs more
-workspace than the scratch holds is rejected before any launch.
+5,000-sentence mixed batch (all in LDS), the second on a smaller batch whose
+200-word sentence keeps both charts there; then the first plan again.  A plan
+whose tile charts the scratch does not hold runs on charts of single spans, and
+one that needs more workspace than it holds for those is rejected before any
+launch.
 """
 import ctypes
 
@@ -81,7 +82,7 @@ def _against_oracle(batch, got, grad=None):
 def test_noalloc_matches_fused_call_twice_in_a_row(torch):
     big = W.make("mixed")
     plan1, s1, _, ref1, got1 = _run_both(torch, big)
-    assert plan1.info["split_ws_count"] >= 1            # the scratch is really used
+    assert plan1.info["split_ws_count"] >= 1            # (CKY alone: a width a step, a split table in the workspace)
     _same(ref1, got1)
     _against_oracle(big, got1)
 
@@ -99,6 +100,37 @@ def test_noalloc_matches_fused_call_twice_in_a_row(torch):
     _same(ref1, [x.cpu().numpy() for x in again])
     plan1.close()
     plan2.close()
+
+
+@pytest.mark.parametrize("lengths", [
+    [141] * 40 + [30, 99, 12, 5] * 30,       # 40 charts in tiles take 11 MB; of single spans they fit in LDS
+    [140] * 30 + [150] * 2 + [60] * 50,      # two sentences past LDS either way
+])
+def test_noalloc_tile_charts_beyond_scratch(torch, lengths):
+    # the charts of single spans: the fused queue of parse_kernel, twice (its
+    # counter is cleared by the call)
+    b = W.custom(lengths, seed=79, sd=2.0)
+    dev = torch.device("cuda", 0)
+    s = torch.from_numpy(b.scores).to(dev)
+    grad = np.linspace(-1.0, 2.0, b.B).astype(np.float32)
+    g = torch.from_numpy(grad).to(dev)
+    with B.Plan(b.lengths, n1=b.n1, device=dev) as plan:
+        assert plan.info["workspace_bytes"] > SCRATCH_WS
+        outs = []
+        for _ in range(2):
+            outs.append(_outputs(torch, plan, s, -3.0))
+            _call(torch, B.crf_inside_fwd_bwd_cky_noalloc, plan, s, g, outs[-1])
+        torch.cuda.synchronize()
+    first, second = ([x.cpu().numpy() for x in o] for o in outs)
+    _same(first, second)
+    lz, mu, sp, be = first
+    lz_ref, mu_ref = orc.marginals(b.scores, b.lengths, grad=grad, threads=16)
+    assert np.all(np.abs(lz - lz_ref) <= 1e-5 * np.maximum(1.0, np.abs(lz_ref)))
+    v = W.valid_mask(b.lengths, b.n1)
+    scale = np.maximum(1.0, np.abs(grad))[:, None, None]
+    assert np.max((np.abs(mu - mu_ref) / scale)[v]) <= 1e-4 and np.all(mu[~v] == np.float32(-3.0))
+    sp_ref, be_ref = orc.cky(b.scores, b.lengths, threads=16)
+    assert np.array_equal(sp, sp_ref) and np.array_equal(be, be_ref.astype(np.float32))
 
 
 def test_noalloc_rejects_plan_beyond_scratch(torch):
