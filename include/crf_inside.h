@@ -300,7 +300,7 @@ int crf_biaffine_scores(const crf_plan *plan, const uint16_t *rl, const uint16_t
  * (with one workgroup per workspace sentence pass: no teams).
  *   Returns CRF_EINVAL when the plan needs more workspace than the array
  *   holds (8 MiB less 256 bytes), e.g. a batch with many sentences longer
- *   than 142 words.  The need counted is that of the charts of single spans,
+ *   than 141 words.  The need counted is that of the charts of single spans,
  *   which can be less than crf_plan_info's workspace_bytes (that also covers
  *   the charts in tiles of spans); a plan whose tile charts do not fit the
  *   array runs on the charts of single spans.

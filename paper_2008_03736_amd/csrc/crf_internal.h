@@ -366,11 +366,10 @@ constexpr int kLabelChunk = 256;
 constexpr int kLabInBundleMaxN = 48;
 constexpr int kLabelRowChunk = 1024;
 
-// Longest sentence whose CKY chart could sit in one CU's LDS (160 KiB):
-// 8 (n+1)^2 <= 163840 (with row padding, its split table and tables the
-// plan finds somewhat less).  The plan sends longer ones to the workspace
-// kernels.
-constexpr int kMaxLenInLds = 142;
+// Longest sentence whose charts of single spans fit in one CU's LDS (160 KiB:
+// 161,912 bytes for the inside, 161,976 for CKY at 141 words).  The plan sends
+// longer ones to the workspace kernels.
+constexpr int kMaxLenInLds = 141;
 
 // A bundle: `count` sentences of identical length `n`, processed together by
 // one workgroup; their ids are order[first .. first+count).

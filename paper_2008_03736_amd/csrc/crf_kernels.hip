@@ -645,8 +645,8 @@ __device__ __forceinline__ void io_run(const Bundle_ctx<T> &bx, int t0, int t1, 
 }
 
 // Calls RUN(G, C, MF) for the shape of a step of more than 128 splits
-// (the fixed runs take the others).  Charts in LDS hold at most 142 words
-// (K <= 141), so their sweeps need only (16, 12); only the workspace (WIDE)
+// (the fixed runs take the others).  Charts in LDS hold at most 141 words
+// (K <= 140), so their sweeps need only (16, 12); only the workspace (WIDE)
 // kernels build the wider shapes.
 #define CRF_DISPATCH_WIDE_SHAPE(SH, RUN)                     \
     do {                                                     \

@@ -230,10 +230,10 @@ def check_tile_charts(head, lengths, teams=False, force=False):
     bundle of each launch and kind, of its own block count, within the LDS of
     the launch (two workgroups a CU, or one), the lanes and the score pieces a
     thread keeps; the others on charts of their own in the workspace.  teams:
-    sentences of more than 142 words are left to the kernels of single spans."""
+    sentences of more than 141 words are left to the kernels of single spans."""
     lengths = np.asarray(lengths)
     in_lds = np.flatnonzero(lengths <= 139) if not force else np.array([], int)
-    on_spans = np.flatnonzero((lengths > 142) | force) if teams else np.array([], int)
+    on_spans = np.flatnonzero((lengths > 141) | force) if teams else np.array([], int)
     in_ws = np.setdiff1d(np.setdiff1d(np.arange(len(lengths)), in_lds), on_spans)
     assert head["tile_on"] == 1 and head["tile_long"] == (0 if teams else 1)
     bundles = head.get("bundles", [])
@@ -269,7 +269,7 @@ def check_tile_charts(head, lengths, teams=False, force=False):
     need = max([c[3] for c in charts], default=0)
     assert head["tile_scratch"] == (0 if need > SCRATCH_WS else 1)
     if not head["tile_scratch"] and head["scratch_bytes"] <= SCRATCH_WS:
-        assert head["n_mix"] > 0 or len(in_lds) + np.sum(lengths[in_ws] <= 142) == 0
+        assert head["n_mix"] > 0 or len(in_lds) + np.sum(lengths[in_ws] <= 141) == 0
 
 
 @pytest.mark.parametrize("name", ["tiny", "mixed", "longer", "stress"])
@@ -290,8 +290,8 @@ def test_tile_charts_of_random_batches(harness, tmp_path, seed):
 @pytest.mark.parametrize("lengths,flags,teams", [
     ([400] * 3 + [30], 0, False),              # up to 400 words: tiles
     ([401, 30], 0, True),
-    ([402, 141, 150, 30], 0, True),            # 140..142 words: tile charts behind the others' charts
-    ([500, 140, 141, 143, 139, 5], 0, True),
+    ([402, 141, 150, 30], 0, True),            # 140 and 141 words: tile charts behind the others' charts
+    ([500, 140, 141, 142, 143, 139, 5], 0, True),   # 142 words: not in both
     ([401] + [256] * 15, 0, True),             # 16 past LDS: teams
     ([401] + [256] * 16, 0, False),            # 17: tiles
     ([1023], 0, True),
@@ -306,7 +306,7 @@ def test_tile_charts_or_teams(harness, tmp_path, lengths, flags, teams):
 
 
 def test_tile_charts_past_the_scratch(harness, tmp_path):
-    # sentences of 140..142 words keep their charts of single spans in LDS, so
+    # sentences of 140 and 141 words keep their charts of single spans in LDS, so
     # that a plan can fit the no-allocation call's scratch on those alone
     lengths = [141] * 40 + [30] * 100
     head, _ = plan_of(harness, tmp_path, lengths)
