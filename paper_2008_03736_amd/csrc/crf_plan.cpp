@@ -650,7 +650,8 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
                 return S == 1 && crf::tile_io_bytes(m, 1, ev) > half_cu && crf::tile_io_bytes(m, 1, m) <= half_cu ? m : ev;
             };
             auto io_bytes = [=](int m, int S) { return crf::tile_io_bytes(m, S, pitch(m, S)); };
-            const bool small = io_bytes(m_max, 1) <= half_cu;
+            // (512 threads beside workspace sentences, which share the launch)
+            const bool small = io_bytes(m_max, 1) <= half_cu && kp.tile_ws.n == 0;
             const int64_t budget = small ? half_cu : full_cu;
             kp.tile_threads = small ? crf::kTileThreads : crf::kTileThreadsMax;
             // Full bundles: a stage costs about the same whatever share of its

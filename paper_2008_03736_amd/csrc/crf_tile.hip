@@ -1638,12 +1638,104 @@ CRF_TILE_WS_KERNEL tile_ws_parse_kernel(KernelPlan p, const float *__restrict__ 
     else tile_cky<true>(p, rec, ws_chart(p, rec), smem_raw, scores, spans, best);
 }
 
+CRF_TILE_WS_KERNEL tile_ws_mbr_kernel(KernelPlan p, const float *__restrict__ scores, float *__restrict__ logZ, float *marg,
+                                      int32_t *__restrict__ spans, float *__restrict__ best) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const int32_t *rec = ws_record(p, 2 * (int)blockIdx.x);
+    tile_inside<true, false, true>(p, rec, ws_chart(p, rec), smem_raw, scores, nullptr, logZ, marg);
+    __syncthreads();   // the marginals are written (each row piece by the thread that reads it back)
+    rec += kTrHeader + 2;
+    tile_cky<true>(p, rec, ws_chart(p, rec), smem_raw, marg, spans, best);
+}
+
+// Batches with sentences on both sides of LDS, in one launch: the workspace
+// sentences' passes first (they are the longest), then the bundles, all of 512
+// threads, so that a bundle does not wait for the last long sentence.  As two
+// launches the times added up, and a batch clipped at 140 words (a block past
+// LDS, where a width a step still fits) lost to the width-step kernels.  1,000
+// sentences of up to 140 words, us (a width a step, two launches, one):
+// @@FIG@@
+// A workgroup's record, and whether its charts are in the workspace.  per:
+// passes of a workspace sentence in the launch.  (The charts' address is taken
+// on each side of the branch: a pointer that may be either would be a generic
+// one, @@FLAT@@.)
+struct Both_work {
+    const int32_t *rec;
+    bool glob;
+};
+__device__ __forceinline__ Both_work both_work(const KernelPlan &p, const TileSchedule &lds, int per, int pass) {
+    const int b = (int)blockIdx.x, n_ws = per * p.tile_ws.n;
+    if (b >= n_ws) return Both_work{lds.recs + (size_t)(b - n_ws) * p.tile_stride, false};
+    return Both_work{ws_record(p, per == 2 ? b : 2 * b + pass), true};
+}
+
+template <bool REV>
+CRF_TILE_KERNEL tile_both_inside_kernel(KernelPlan p, const float *__restrict__ scores, const float *__restrict__ grad,
+                                        float *__restrict__ logZ, float *__restrict__ marg) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const Both_work k = both_work(p, p.tile_io, 1, 0);
+    if (k.glob) tile_inside<REV, false, true>(p, k.rec, ws_chart(p, k.rec), smem_raw, scores, grad, logZ, marg);
+    else tile_inside<REV>(p, k.rec, smem_raw, smem_raw, scores, grad, logZ, marg);
+}
+
+CRF_TILE_KERNEL tile_both_loss_kernel(KernelPlan p, const float *__restrict__ scores, const int32_t *__restrict__ gold,
+                                      const float *__restrict__ grad, float *__restrict__ loss,
+                                      float *__restrict__ marg) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const Both_work k = both_work(p, p.tile_io, 1, 0);
+    if (k.glob) tile_inside<true, true, true>(p, k.rec, ws_chart(p, k.rec), smem_raw, scores, grad, nullptr, marg, gold, loss);
+    else tile_inside<true, true>(p, k.rec, smem_raw, smem_raw, scores, grad, nullptr, marg, gold, loss);
+}
+
+CRF_TILE_KERNEL tile_both_cky_kernel(KernelPlan p, const float *__restrict__ scores, int32_t *__restrict__ spans,
+                                     float *__restrict__ best) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const Both_work k = both_work(p, p.tile_ck, 1, 1);
+    if (k.glob) tile_cky<true>(p, k.rec, ws_chart(p, k.rec), smem_raw, scores, spans, best);
+    else tile_cky(p, k.rec, smem_raw, smem_raw, scores, spans, best);
+}
+
+CRF_TILE_KERNEL tile_both_parse_kernel(KernelPlan p, const float *__restrict__ scores, const float *__restrict__ grad,
+                                       float *__restrict__ logZ, float *__restrict__ marg, int32_t *__restrict__ spans,
+                                       float *__restrict__ best) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const Both_work k = both_work(p, p.tile_mix, 2, 0);
+    const bool inside = k.rec[kTrKind] == kKindInside;
+    if (k.glob) {
+        if (inside) tile_inside<true, false, true>(p, k.rec, ws_chart(p, k.rec), smem_raw, scores, grad, logZ, marg);
+        else tile_cky<true>(p, k.rec, ws_chart(p, k.rec), smem_raw, scores, spans, best);
+    } else {
+        if (inside) tile_inside<true>(p, k.rec, smem_raw, smem_raw, scores, grad, logZ, marg);
+        else tile_cky(p, k.rec, smem_raw, smem_raw, scores, spans, best);
+    }
+}
+
+// (a workspace sentence too: its inside record is followed by its CKY record)
+CRF_TILE_KERNEL tile_both_mbr_kernel(KernelPlan p, const float *__restrict__ scores, float *__restrict__ logZ, float *marg,
+                                     int32_t *__restrict__ spans, float *__restrict__ best) {
+    extern __shared__ __align__(16) char smem_raw[];
+    const Both_work k = both_work(p, p.tile_io, 1, 0);
+    if (k.glob) {
+        tile_inside<true, false, true>(p, k.rec, ws_chart(p, k.rec), smem_raw, scores, nullptr, logZ, marg);
+        __syncthreads();
+        const int32_t *rec = k.rec + kTrHeader + 2;
+        tile_cky<true>(p, rec, ws_chart(p, rec), smem_raw, marg, spans, best);
+    } else {
+        tile_inside<true>(p, k.rec, smem_raw, smem_raw, scores, nullptr, logZ, marg);
+        __syncthreads();
+        tile_cky(p, k.rec, smem_raw, smem_raw, marg, spans, best);
+    }
+}
+
 }  // namespace
 
 hipError_t set_tile_attributes(int max_lds_bytes) {
     const void *fns[] = {(const void *)tile_inside_kernel<false>, (const void *)tile_inside_kernel<true>,
                          (const void *)tile_loss_kernel, (const void *)tile_cky_kernel, (const void *)tile_parse_kernel,
-                         (const void *)tile_mbr_kernel};
+                         (const void *)tile_mbr_kernel, (const void *)tile_both_inside_kernel<false>,
+                         (const void *)tile_both_inside_kernel<true>, (const void *)tile_both_loss_kernel,
+                         (const void *)tile_both_cky_kernel, (const void *)tile_both_parse_kernel,
+                         (const void *)tile_both_mbr_kernel};
     for (const void *f : fns) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, max_lds_bytes);
         if (e != hipSuccess) return e;
@@ -1651,80 +1743,51 @@ hipError_t set_tile_attributes(int max_lds_bytes) {
     return hipSuccess;
 }
 
+// A plan's workspace sentences (ws), bundles (lds), or both in one launch:
+// `per` passes a workspace sentence.
+template <typename... KA, typename... A>
+static hipError_t launch_tile(const KernelPlan &p, const TileSchedule &lds, int per, hipStream_t stream,
+                              void (*k_ws)(KernelPlan, KA...), void (*k_lds)(KernelPlan, KA...),
+                              void (*k_both)(KernelPlan, KA...), A... args) {
+    const int n_ws = per * p.tile_ws.n;
+    const size_t ws_bytes = (size_t)p.tile_ws.lds_bytes, lds_bytes = (size_t)lds.lds_bytes;
+    if (n_ws > 0 && lds.n > 0)
+        hipLaunchKernelGGL(k_both, dim3(n_ws + lds.n), dim3(kTileThreadsMax), ws_bytes > lds_bytes ? ws_bytes : lds_bytes,
+                           stream, p, args...);
+    else if (n_ws > 0)
+        hipLaunchKernelGGL(k_ws, dim3(n_ws), dim3(kTileThreadsWs), ws_bytes, stream, p, args...);
+    else if (lds.n > 0)
+        hipLaunchKernelGGL(k_lds, dim3(lds.n), dim3(p.tile_threads), lds_bytes, stream, p, args...);
+    else
+        return hipSuccess;
+    return hipGetLastError();
+}
+
 hipError_t launch_tile_inside(const KernelPlan &p, const float *scores, const float *grad, float *logZ, float *marg,
                               hipStream_t stream) {
-    if (p.tile_ws.n > 0) {
-        const dim3 grid(p.tile_ws.n), block(kTileThreadsWs);
-        const size_t lds = (size_t)p.tile_ws.lds_bytes;
-        if (marg != nullptr)
-            hipLaunchKernelGGL(tile_ws_inside_kernel<true>, grid, block, lds, stream, p, scores, grad, logZ, marg);
-        else
-            hipLaunchKernelGGL(tile_ws_inside_kernel<false>, grid, block, lds, stream, p, scores, grad, logZ, marg);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (p.tile_io.n == 0) return hipSuccess;
-    const dim3 grid(p.tile_io.n), block(p.tile_threads);
-    const size_t lds = (size_t)p.tile_io.lds_bytes;
     if (marg != nullptr)
-        hipLaunchKernelGGL(tile_inside_kernel<true>, grid, block, lds, stream, p, scores, grad, logZ, marg);
-    else
-        hipLaunchKernelGGL(tile_inside_kernel<false>, grid, block, lds, stream, p, scores, grad, logZ, marg);
-    return hipGetLastError();
+        return launch_tile(p, p.tile_io, 1, stream, tile_ws_inside_kernel<true>, tile_inside_kernel<true>,
+                           tile_both_inside_kernel<true>, scores, grad, logZ, marg);
+    return launch_tile(p, p.tile_io, 1, stream, tile_ws_inside_kernel<false>, tile_inside_kernel<false>,
+                       tile_both_inside_kernel<false>, scores, grad, logZ, marg);
 }
 hipError_t launch_tile_loss(const KernelPlan &p, const float *scores, const int32_t *gold, const float *grad,
                             float *loss, float *grad_scores, hipStream_t stream) {
-    if (p.tile_ws.n > 0) {
-        hipLaunchKernelGGL(tile_ws_loss_kernel, dim3(p.tile_ws.n), dim3(kTileThreadsWs), (size_t)p.tile_ws.lds_bytes, stream,
-                           p, scores, gold, grad, loss, grad_scores);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (p.tile_io.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(tile_loss_kernel, dim3(p.tile_io.n), dim3(p.tile_threads), (size_t)p.tile_io.lds_bytes, stream,
-                       p, scores, gold, grad, loss, grad_scores);
-    return hipGetLastError();
+    return launch_tile(p, p.tile_io, 1, stream, tile_ws_loss_kernel, tile_loss_kernel, tile_both_loss_kernel, scores, gold,
+                       grad, loss, grad_scores);
 }
 hipError_t launch_tile_cky(const KernelPlan &p, const float *scores, int32_t *spans, float *best, hipStream_t stream) {
-    if (p.tile_ws.n > 0) {
-        hipLaunchKernelGGL(tile_ws_cky_kernel, dim3(p.tile_ws.n), dim3(kTileThreadsWs), (size_t)p.tile_ws.lds_bytes, stream,
-                           p, scores, spans, best);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (p.tile_io.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(tile_cky_kernel, dim3(p.tile_ck.n), dim3(p.tile_threads), (size_t)p.tile_ck.lds_bytes, stream, p,
-                       scores, spans, best);
-    return hipGetLastError();
+    return launch_tile(p, p.tile_ck, 1, stream, tile_ws_cky_kernel, tile_cky_kernel, tile_both_cky_kernel, scores, spans, best);
 }
 hipError_t launch_tile_parse(const KernelPlan &p, const float *scores, const float *grad, float *logZ, float *marg,
                              int32_t *spans, float *best, hipStream_t stream) {
-    if (p.tile_ws.n > 0) {
-        hipLaunchKernelGGL(tile_ws_parse_kernel, dim3(2 * p.tile_ws.n), dim3(kTileThreadsWs), (size_t)p.tile_ws.lds_bytes, stream,
-                           p, scores, grad, logZ, marg, spans, best);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (p.tile_io.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(tile_parse_kernel, dim3(p.tile_mix.n), dim3(p.tile_threads), (size_t)p.tile_mix.lds_bytes, stream,
-                       p, scores, grad, logZ, marg, spans, best);
-    return hipGetLastError();
+    return launch_tile(p, p.tile_mix, 2, stream, tile_ws_parse_kernel, tile_parse_kernel, tile_both_parse_kernel, scores,
+                       grad, logZ, marg, spans, best);
 }
 hipError_t launch_tile_mbr(const KernelPlan &p, const float *scores, float *logZ, float *marg, int32_t *spans,
                            float *best, hipStream_t stream) {
-    if (p.tile_ws.n > 0) {   // the marginals, then CKY over them
-        hipLaunchKernelGGL(tile_ws_inside_kernel<true>, dim3(p.tile_ws.n), dim3(kTileThreadsWs),
-                           (size_t)p.tile_ws.lds_bytes, stream, p, scores, nullptr, logZ, marg);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(tile_ws_cky_kernel, dim3(p.tile_ws.n), dim3(kTileThreadsWs), (size_t)p.tile_ws.lds_bytes,
-                           stream, p, marg, spans, best);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    if (p.tile_io.n == 0) return hipSuccess;
-    hipLaunchKernelGGL(tile_mbr_kernel, dim3(p.tile_io.n), dim3(p.tile_threads), (size_t)p.tile_io.lds_bytes, stream, p,
-                       scores, logZ, marg, spans, best);
-    return hipGetLastError();
+    return launch_tile(p, p.tile_io, 1, stream, tile_ws_mbr_kernel, tile_mbr_kernel, tile_both_mbr_kernel, scores, logZ,
+                       marg, spans, best);
 }
 
 }  // namespace crf
