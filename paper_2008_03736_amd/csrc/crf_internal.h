@@ -418,7 +418,7 @@ struct Schedule {
 // length).
 constexpr int kTileMaxLen = 139;      // 35 blocks: the longest whose two inside squares fit in one CU's LDS
 constexpr int kTileThreads = 256;      // two workgroups per CU
-constexpr int kTileThreadsMax = 512;  // one workgroup per CU (bundles past half the LDS)
+constexpr int kTileThreadsMax = 512;  // one workgroup per CU (bundles past half the LDS, or beside workspace charts)
 constexpr int kTileThreadsWs = 512;  // workspace charts: a sentence and pass per workgroup
 constexpr int kTileTabWords = 8;
 // An inside bundle's score rows in 16-byte pieces (tiles are walked in folded

@@ -39,7 +39,9 @@ EXPECTED = [
     "tile_inside_kernel<false>", "tile_inside_kernel<true>", "tile_loss_kernel", "tile_cky_kernel",
     "tile_parse_kernel", "tile_mbr_kernel",
     "tile_ws_inside_kernel<false>", "tile_ws_inside_kernel<true>", "tile_ws_loss_kernel", "tile_ws_cky_kernel",
-    "tile_ws_parse_kernel",
+    "tile_ws_parse_kernel", "tile_ws_mbr_kernel",
+    "tile_both_inside_kernel<false>", "tile_both_inside_kernel<true>", "tile_both_loss_kernel", "tile_both_cky_kernel",
+    "tile_both_parse_kernel", "tile_both_mbr_kernel",
 ]
 
 

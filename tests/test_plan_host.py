@@ -242,6 +242,8 @@ def check_tile_charts(head, lengths, teams=False, force=False):
         for kind in kinds:
             assert sorted(i for r in here if r["kind"] == kind for i in r["ids"]) == list(in_lds)
         assert sorted({r["kind"] for r in here}) == (kinds if len(in_lds) else [])
+    if len(in_lds) and len(in_ws):   # one launch holds both
+        assert head["tile_threads"] == 512
     budget = head["half_cu"] if head["tile_threads"] == 256 else 163840 - 512
     for r in bundles:
         assert r["count"] == len(r["ids"]) >= 1 and [lengths[i] for i in r["ids"]] == r["lens"]
