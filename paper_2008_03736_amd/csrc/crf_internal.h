@@ -518,13 +518,16 @@ struct KernelPlan {
 // no-allocation call run the same kernels with a workgroup a pass, slower: the
 // flag then changes no bit of a result.
 constexpr int kTileTeamCount = 16, kTileTeamLen = 400;
-// CKY alone, every sentence in LDS: tile charts when the longest has up to
+// CKY alone, every sentence in LDS (a width a step: up to kMaxLenInLds words):
+// tile charts when the longest has up to
 // this many words, a step per width past that.  A float64 tile's chain is as
 // long as its four width steps', so only the saved barriers of short charts
 // pay (us, a step per width and tiles): one sentence of 23 words 14.8 and
 // 13.3, 40 of 10 to 28 17.8 both, 300 of 10 to 32 20.95 and 21.2, 20 of 40 to
 // 60 36.3 and 38.1, 300 of up to 80 59.2 and 61.1, 8 of 110
-// to 130 104.2 and 112.1.  Beside the inside chain it is the other way round:
+// to 130 104.2 and 112.1, 1,000 of up to 140 128 and 161 (the longest in the
+// workspace).  With sentences that neither chart keeps in LDS tiles win (143
+// and 1,000 of up to 99: 377 and 158).  Beside the inside chain it is the other way round:
 // the fused and MBR launches stay on tiles.
 constexpr int kTileCkyLen = 28;
 // Bytes of a sentence's tile charts in the workspace: inside (alpha and O', each

@@ -702,7 +702,7 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
         }
     }
 
-    kp.tile_cky = kp.tile_on && (max_len <= crf::kTileCkyLen || kp.tile_ws.n > 0 || !kp.tile_long);
+    kp.tile_cky = kp.tile_on && (max_len <= crf::kTileCkyLen || (kp.tile_long && !sc.spill.empty()));
 
     if ((e = upload(p, len, &kp.len)) != hipSuccess ||
         (e = upload(p, rec_in, &kp.inside.recs)) != hipSuccess ||
@@ -794,17 +794,18 @@ int crf_plan_info(const crf_plan *plan, crf_plan_stats *out) {
     out->max_len = plan->max_len;
     const crf::KernelPlan &kp = plan->kp;
     // Unlabelled plans run on tile charts, in LDS or in the workspace, but for
-    // what tile_long and tile_cky leave to the charts of single spans; every
-    // sentence is on the same side for the inside and for CKY.
+    // what tile_long and tile_cky leave to the charts of single spans.  (CKY
+    // alone there: 140 and 141 words in LDS, their split tables, as those of
+    // every sentence of 96 words and more, in the workspace.)
     const int32_t ws = kp.tile_ws.n + (kp.tile_long ? 0 : kp.inside.n_spill);
     out->spill_count = kp.tile_on ? ws : kp.inside.n_spill;
     out->lds_count = plan->B - out->spill_count;
     out->workspace_bytes = plan->ws_bytes;
     out->lds_bytes_inside = kp.tile_on ? kp.tile_io.lds_bytes : kp.inside.lds_bytes;
     out->lds_bytes_cky = kp.tile_cky ? kp.tile_ck.lds_bytes : kp.cky.lds_bytes;
-    out->cky_spill_count = kp.tile_on ? ws : kp.cky.n_spill;
+    out->cky_spill_count = kp.tile_cky ? ws : kp.cky.n_spill;
     out->split_ws_count = kp.tile_cky ? 0 : plan->split_ws_count;
-    out->workspace_users = kp.tile_on ? ws + out->split_ws_count : plan->workspace_users;
+    out->workspace_users = kp.tile_cky ? ws : plan->workspace_users;
     out->fused_queue = 0;
     out->mbr_fused = kp.tile_io.n > 0 ? 1 : 0;
     return ok();

@@ -265,7 +265,16 @@ def check_tile_charts(head, lengths, teams=False, force=False):
         spans.append((0, head["scratch_bytes"]))   # their charts, in use at the same time
     spans.sort()
     assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and (not spans or spans[-1][1] <= head["ws_bytes"])
-    assert head["spill"] == head["cky_spill"] == len(in_ws) + len(on_spans)
+    assert head["spill"] == len(in_ws) + len(on_spans)
+    # CKY alone: a width a step unless the sentences are short or some fit in
+    # LDS neither way (teams take those a width a step too)
+    assert head["tile_cky"] == int(lengths.max() <= 28 or (not teams and (force or lengths.max() > 141)))
+    assert head["cky_spill"] == (head["spill"] if head["tile_cky"] else len(on_spans))
+    if head["tile_cky"]:
+        assert head["ws_users"] == head["spill"] and head["split_ws"] == 0
+    else:
+        assert head["ws_users"] == len(on_spans) + head["split_ws"]
+        assert head["split_ws"] == np.sum(np.delete(lengths, on_spans) >= 96)
     assert head["mbr_fused"] == (1 if len(in_lds) else 0)
     # what does not fit the scratch as tiles runs on the fused queue, which must be there
     need = max([c[3] for c in charts], default=0)

@@ -28,6 +28,8 @@ CASES = {
     "whole_cu": dict(lengths=[99, 100, 103, 104, 127, 128, 139]),
     # 140 words and more: past LDS
     "past_tiles": dict(lengths=[139, 140, 142, 143, 5]),
+    # (CKY alone keeps these in LDS, a width a step)
+    "one_block_past": dict(lengths=[140, 12, 141, 99, 30, 140]),
     "padding": dict(lengths=[9, 1, 30, 2], n1=41),
     # integer scores: ties between splits inside a block, between blocks and
     # between the lanes that share a tile
