@@ -1068,24 +1068,48 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
     if constexpr (!REV) return true;
 
     if constexpr (GOLD) {
-        // A wavefront per sentence: the gold spans' scores summed in float64
-        // (a fixed order) and marked in the transposed outside tiles, which
-        // nothing reads any more (diagonal tiles: below their diagonal).
-        const int R = 2 * (N1 - 1) - 1, lane = tid & 63;
-        for (int sb = wave; sb < S; sb += nw) {
+        // The gold spans' scores summed in float64 (a fixed order) and marked
+        // in the transposed outside tiles, which nothing reads any more
+        // (diagonal tiles: below their diagonal).  A wavefront per sentence, or
+        // 16 lanes where the bundle has more sentences than wavefronts: each
+        // has kAhead rows' two round trips to memory in flight (4,000 of up to
+        // 60 words, mean 8: loss 65 us with a wavefront each and a row a lane,
+        // 51 on the width-step kernels, 45 so).
+        const int R = 2 * (N1 - 1) - 1, per = S > nw ? 16 : 64, lane = tid & (per - 1);
+        for (int sb = S > nw ? tid >> 4 : wave; sb < S; sb += NT / per) {
             const int id = tab<int>(cx, kTabId, sb), n = tab<int>(cx, kTabN, sb);
             const int32_t *g2 = gold + (size_t)id * R * 2;
             double acc = 0.0;
-            for (int r = lane; r < 2 * n - 1; r += 64) {
-                const int i = g2[2 * r], j = g2[2 * r + 1];
-                if (0 <= i && i < j && j <= n) {
-                    acc += (double)scores[(size_t)id * sent_stride + (size_t)i * N1 + j];
-                    const int g = (j >> 2) * S + sb;
-                    *reinterpret_cast<int *>(sm + cx.ot(i >> 2, j >> 2, sb) + ((j + cx.rot(g)) & 3) * cx.rs((j >> 2) - (i >> 2)) + 4 * (i & 3)) = kGoldMark;
+            const int rows = 2 * n - 1;
+            constexpr int kAhead = 4;   // rows a lane has in flight
+            for (int r0 = lane; r0 < rows; r0 += kAhead * per) {
+                int gi[kAhead], gj[kAhead];
+                float v[kAhead];
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const int r = min(r0 + u * per, rows - 1);
+                    gi[u] = g2[2 * r];
+                    gj[u] = r0 + u * per < rows ? g2[2 * r + 1] : -1;
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    if (!(0 <= gi[u] && gi[u] < gj[u] && gj[u] <= n)) gi[u] = -1, gj[u] = 0;
+                    v[u] = gi[u] >= 0 ? scores[(size_t)id * sent_stride + (size_t)gi[u] * N1 + gj[u]] : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    const int i = gi[u], j = gj[u], g = (j >> 2) * S + sb;
+                    acc += (double)v[u];
+                    if (i >= 0)
+                        *reinterpret_cast<int *>(sm + cx.ot(i >> 2, j >> 2, sb) +
+                                                 ((j + cx.rot(g)) & 3) * cx.rs((j >> 2) - (i >> 2)) + 4 * (i & 3)) = kGoldMark;
                 }
             }
-#pragma unroll
-            for (int s = 32; s >= 1; s >>= 1) acc += __shfl_xor(acc, s, 64);
+            acc = row_sum(acc);
+            if (per == 64) {
+                acc += __shfl_xor(acc, 16, 64);
+                acc += __shfl_xor(acc, 32, 64);
+            }
             if (lane == 0) loss[id] = (float)(log_z(sb) - acc);
         }
         __syncthreads();
