@@ -101,7 +101,7 @@ __device__ __forceinline__ uint32_t keep_word(int k, int d) {
 // (sentence b, fence post i) or -1.  KS = K / 32 steps of the first product
 // (K = d + 1 padded to 256 or 512); each wavefront takes KS / 4 of them.
 constexpr int kRAhead = 3;   // chunks of r^r in flight
-template <int KS, int P>
+template <int KS, int P, bool ONE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void biaffine_kernel(
     const int32_t *__restrict__ tiles, const int32_t *__restrict__ len, int N1, int d, int ldw, int L, int n_work,
     int groups, int per_group, const uint16_t *__restrict__ rl, const uint16_t *__restrict__ rr, const uint16_t *__restrict__ w,
@@ -121,12 +121,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // Workgroup b runs on XCD b mod 8 (dealt in turn); each XCD takes a
     // contiguous share of the work, a tile's label groups side by side: a
     // cell's labels are neighbours in memory, and lines written by several
-    // workgroups meet in one L2.
-    const int per_xcd = (n_work + 7) >> 3;
-    const int work = groups > 1 ? ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
-    if (work >= n_work) return;
-    const int tile = groups > 1 ? work / groups : work, l0 = (work - tile * groups) * per_group;
-    const int l1 = min(l0 + per_group, L);
+    // workgroups meet in one L2.  ONE: a label a workgroup, a label's tiles side
+    // by side, whose W they share.
+    int tile, l0, l1;
+    if constexpr (ONE) {
+        tile = blockIdx.x;
+        l0 = blockIdx.y;
+        l1 = l0 + 1;
+    } else {
+        const int per_xcd = (n_work + 7) >> 3;
+        const int work = groups > 1 ? ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3) : (int)blockIdx.x;
+        if (work >= n_work) return;
+        tile = work / groups;
+        l0 = (work - tile * groups) * per_group;
+        l1 = min(l0 + per_group, L);
+    }
     const int32_t *rec = tiles + (size_t)tile * (kBiaRows + kBiaCols);
     const uint16_t *wl = w + (size_t)l0 * d * ldw;
 
@@ -197,8 +206,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
 
     // A label at a time: the tile's rows stay in registers.
-    for (int l = l0; l < l1; ++l) {
-    if (l > l0) {
+    for (int l = l0; ONE ? l == l0 : l < l1; ++l) {
+    if (!ONE && l > l0) {
         wl += (size_t)d * ldw;
         load_wq<KQ, P>(wf, wl, 0, d, ldw, kq0, lane);
         load_first_rr();
@@ -479,8 +488,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }  // namespace
 
 hipError_t set_biaffine_attributes() {
-    const void *fns[] = {(const void *)biaffine_kernel<8, 4>, (const void *)biaffine_kernel<16, 4>,
-                         (const void *)biaffine_kernel<8, 8>, (const void *)biaffine_kernel<16, 8>};
+    const void *fns[] = {(const void *)biaffine_kernel<8, 4, false>, (const void *)biaffine_kernel<16, 4, false>,
+                         (const void *)biaffine_kernel<8, 8, false>, (const void *)biaffine_kernel<16, 8, false>,
+                         (const void *)biaffine_kernel<8, 4, true>, (const void *)biaffine_kernel<16, 4, true>,
+                         (const void *)biaffine_kernel<8, 8, true>, (const void *)biaffine_kernel<16, 8, true>};
     for (const void *f : fns) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)biaffine_lds_bytes(kBiaMaxD));
         if (e != hipSuccess) return e;
@@ -499,7 +510,7 @@ int64_t biaffine_lds_bytes(int) {
 }
 
 template <int P>
-static void launch_biaffine_p(const KernelPlan &p, int n_work, int groups, int per_group, size_t lds,
+static void launch_biaffine_p(const KernelPlan &p, int n_work, int groups, int per_group, bool one, size_t lds,
                               hipStream_t stream, const uint16_t *rl, const uint16_t *rr, const uint16_t *w, int d,
                               int ldw, int L, float *scores) {
     const dim3 grid(groups > 1 ? (n_work + 7) / 8 * 8 : n_work), block(256);
@@ -509,12 +520,13 @@ static void launch_biaffine_p(const KernelPlan &p, int n_work, int groups, int p
     if (d <= kBiaSmallD)
         hipLaunchKernelGGL((biaffine_small_kernel<P>), grid, block, (size_t)small_lds_bytes(d), stream, p.bia_tiles, p.len,
                            p.n1, d, ldw, L, n_work, groups, per_group, rl, rr, w, scores);
-    else if (kp == 256)
-        hipLaunchKernelGGL((biaffine_kernel<8, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L,
-                           n_work, groups, per_group, rl, rr, w, scores);
+    else if (one)
+        hipLaunchKernelGGL((kp == 256 ? biaffine_kernel<8, P, true> : biaffine_kernel<16, P, true>),
+                           dim3(p.n_bia_tiles, L), block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L, n_work, groups,
+                           per_group, rl, rr, w, scores);
     else
-        hipLaunchKernelGGL((biaffine_kernel<16, P>), grid, block, lds, stream, p.bia_tiles, p.len, p.n1, d, ldw, L,
-                           n_work, groups, per_group, rl, rr, w, scores);
+        hipLaunchKernelGGL((kp == 256 ? biaffine_kernel<8, P, false> : biaffine_kernel<16, P, false>), grid, block, lds,
+                           stream, p.bia_tiles, p.len, p.n1, d, ldw, L, n_work, groups, per_group, rl, rr, w, scores);
 }
 
 hipError_t launch_biaffine(const KernelPlan &p, const uint16_t *rl, const uint16_t *rr, const uint16_t *w, int d,
@@ -527,13 +539,22 @@ hipError_t launch_biaffine(const KernelPlan &p, const uint16_t *rl, const uint16
     // d = 100, with the labelling stage: 96 us at one label a workgroup, 77 at
     // two, 76 at five).
     const int64_t all = (int64_t)p.n_bia_tiles * L;
-    const int per_group = (int)std::min<int64_t>(kBiaLabels, std::max<int64_t>(1, all / 2048));
+    const int per_group = (int)std::min<int64_t>(std::min(L, kBiaLabels), std::max<int64_t>(1, all / 2048));
     const int groups = (L + per_group - 1) / per_group, n_work = p.n_bia_tiles * groups;
+    // The split product with one label a workgroup (d > kBiaSmallD) and nothing
+    // kept for another.  For a single label (5,000 sentences at d = 128, 200,
+    // 252: 50.7, 66.5, 77.3 us with the label loop, 48.0, 64.0, 74.9 without),
+    // for many labels of few tiles, whose W the tiles of a label share (13
+    // tiles, 138 labels: d = 128 41.0 and 39.2, 252 63.3 and 57.5, 500 136.7 and
+    // 121.5), and for the smallest calls (8.3 and 8.0).  Not between (13 tiles,
+    // 40 labels: d = 200 26.3 and 28.5, 500 42.2 and 38.7; 8: d = 400 23.9 and
+    // 25.1) nor for more tiles (220, 8 labels: d = 252 60.8 and 67.5).
+    const bool one = per_group == 1 && (L == 1 || (p.n_bia_tiles <= 32 && (all <= 64 || all > 1024)));
     // 16-byte W pieces when every row starts 16-byte aligned
     if (ldw % 8 == 0 && ((uintptr_t)w & 15) == 0)
-        launch_biaffine_p<8>(p, n_work, groups, per_group, lds, stream, rl, rr, w, d, ldw, L, scores);
+        launch_biaffine_p<8>(p, n_work, groups, per_group, one, lds, stream, rl, rr, w, d, ldw, L, scores);
     else
-        launch_biaffine_p<4>(p, n_work, groups, per_group, lds, stream, rl, rr, w, d, ldw, L, scores);
+        launch_biaffine_p<4>(p, n_work, groups, per_group, one, lds, stream, rl, rr, w, d, ldw, L, scores);
     return hipGetLastError();
 }
 

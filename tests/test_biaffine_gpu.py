@@ -104,3 +104,10 @@ def test_biaffine_label_groups(torch, d, ldw):
     # number of groups that the XCDs do not share evenly
     inp = W.biaffine_inputs([70, 61, 62, 63] * 8 + [130, 9], d, labels=137, seed=d + ldw)
     check(run(torch, inp, ldw=ldw), inp)
+
+
+@pytest.mark.parametrize("d,ldw", [(128, 136), (252, 256), (500, 504), (500, 508)])
+def test_biaffine_many_labels_of_few_tiles(torch, d, ldw):
+    # a dozen tiles and 137 labels: a label a workgroup, its tiles side by side
+    inp = W.biaffine_inputs([70, 61, 62, 63] * 2 + [9], d, labels=137, seed=d + ldw)
+    check(run(torch, inp, ldw=ldw), inp)
