@@ -46,7 +46,7 @@
  *   Teams.  When a call has only a few workspace sentences, each pass may run
  *   on a team of 8 or 16 workgroups of one XCD that wait for each other at
  *   every width step: unlabelled plans with at most 16 workspace sentences of
- *   which one has more than 400 words, and calls of labelled plans with at
+ *   which one has more than 450 words, and calls of labelled plans with at
  *   most 32 workspace sentence passes in one launch.
  *   Such a launch waits until all its workgroups are resident at once (it
  *   is sized to fit an otherwise idle device); work from other streams

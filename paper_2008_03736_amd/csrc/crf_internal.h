@@ -511,13 +511,16 @@ struct KernelPlan {
 };
 // Batches of at most kTileTeamCount sentences past LDS whose longest has more
 // than kTileTeamLen words leave those sentences to the workspace kernels'
-// teams: one workgroup a sentence (tile charts) loses to 16 there (a lone
-// sentence fused: 256 words 493 against 1,095 us in teams, 400 words 1,411
-// against about 1,530, 512 words 2,100 in teams).
+// teams.  A tile chart's one workgroup grows slower with the length than 16
+// do, CKY first (us, teams and tiles): one sentence of 430 words fused 1,651
+// and 1,660, CKY 1,675 and 1,664, with marginals 1,554 and 1,005; of 460 1,929
+// and 2,011, 1,973 and 2,018, 1,801 and 1,289; of 512 2,224 and 2,671, 2,279 and
+// 2,692, 1,908 and 2,216; one of 401 and 15 of 256 words fused 2,074 and 1,391,
+// one of 512 and 15 of 256 2,553 and 2,666.
 // A plan with CRF_NO_TEAMS, a device without room for teams and the
 // no-allocation call run the same kernels with a workgroup a pass, slower: the
 // flag then changes no bit of a result.
-constexpr int kTileTeamCount = 16, kTileTeamLen = 400;
+constexpr int kTileTeamCount = 16, kTileTeamLen = 450;
 // CKY alone, every sentence in LDS (a width a step: up to kMaxLenInLds words):
 // tile charts when the longest has up to
 // this many words, a step per width past that.  A float64 tile's chain is as

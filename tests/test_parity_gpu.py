@@ -371,9 +371,9 @@ def test_longest_sentence(torch):
     print(f"n = 1023: max |marginal error| {worst:.2e}")
 
 
-@pytest.mark.parametrize("longest", [256, 410])
+@pytest.mark.parametrize("longest", [256, 460])
 def test_workspace_teams(torch, longest):
-    # 16 sentences of 150..256 words, or one of them of more than 400: then the
+    # 16 sentences of 150..256 words, or one of them of more than 450: then the
     # workspace launches split each sentence pass over a team of 8 (fused, 32
     # passes) or 16 workgroups of one XCD, several teams per XCD (else a
     # workgroup a sentence, on tile charts); every entry point against the
@@ -391,8 +391,8 @@ def test_workspace_teams_bit_identical(torch):
     # teams split each step's lanes over workgroups but keep every span's
     # arithmetic: every workspace entry point gives the same bits as with one
     # workgroup per sentence pass (CRF_NO_TEAMS), LDS bundles beside them
-    # (one sentence of more than 400 words: else no team takes them)
-    b = W.custom([402, 256, 201, 150, 143, 141, 30, 7], seed=26, sd=2.0)
+    # (one sentence of more than 450 words: else no team takes them)
+    b = W.custom([460, 256, 201, 150, 143, 141, 30, 7], seed=26, sd=2.0)
     gold, _ = orc.cky(b.scores, b.lengths)
     dev = torch.device("cuda", 0)
     s = torch.from_numpy(b.scores).to(dev)
@@ -454,8 +454,8 @@ LOG_DOMAIN_ATOL = 2.1e-4
     # short sentences, whose outside sums are the first to go
     (2, 10.0, [8] * 300, 1108, MARG_ATOL),
     (3, 10.0, [12] * 300, 1112, MARG_ATOL),
-    # unlabelled, few long sentences and one past 400 words: teams
-    (1, 4.5, [402, 150, 180, 210, 240, 270, 300], 4, LOG_DOMAIN_ATOL),
+    # unlabelled, few long sentences and one past 450 words: teams
+    (1, 4.5, [460, 150, 180, 210, 240, 270, 300], 4, LOG_DOMAIN_ATOL),
 ])
 def test_sums_lost_to_underflow(torch, labels, sd, lengths, seed, tol):
     # scores spread so far that sums of the linear domain leave float32 below

@@ -299,16 +299,16 @@ def test_tile_charts_of_random_batches(harness, tmp_path, seed):
 
 
 @pytest.mark.parametrize("lengths,flags,teams", [
-    ([400] * 3 + [30], 0, False),              # up to 400 words: tiles
-    ([401, 30], 0, True),
-    ([402, 141, 150, 30], 0, True),            # 140 and 141 words: tile charts behind the others' charts
+    ([450] * 3 + [30], 0, False),              # up to 450 words: tiles
+    ([451, 30], 0, True),
+    ([460, 141, 150, 30], 0, True),            # 140 and 141 words: tile charts behind the others' charts
     ([500, 140, 141, 142, 143, 139, 5], 0, True),   # 142 words: not in both
-    ([401] + [256] * 15, 0, True),             # 16 past LDS: teams
-    ([401] + [256] * 16, 0, False),            # 17: tiles
+    ([451] + [256] * 15, 0, True),             # 16 past LDS: teams
+    ([451] + [256] * 16, 0, False),            # 17: tiles
     ([1023], 0, True),
     ([1023] * 20, 0, False),
-    ([402, 141, 150, 30], 2, True),            # CRF_NO_TEAMS: the same kernels, a workgroup a pass, for the same bits
-    ([402, 141, 150, 30], 1, True),            # CRF_FORCE_SPILL
+    ([460, 141, 150, 30], 2, True),            # CRF_NO_TEAMS: the same kernels, a workgroup a pass, for the same bits
+    ([460, 141, 150, 30], 1, True),            # CRF_FORCE_SPILL
     ([200, 141, 150, 30], 1, False),
 ])
 def test_tile_charts_or_teams(harness, tmp_path, lengths, flags, teams):

@@ -44,11 +44,11 @@ CASES = {
     # charts in the workspace beside bundles in LDS: one block past LDS, splits
     # past 8 bits, the rescales of long sentences
     "workspace": dict(lengths=[140, 143, 255, 256, 260, 30]),
-    # few long sentences of which one has more than 400 words: teams take
+    # few long sentences of which one has more than 450 words: teams take
     # those, tile charts behind theirs the ones of 140 and 141
-    "teams_beside_tiles": dict(lengths=[402, 30, 141, 150, 140, 142, 12]),
-    # too many long sentences for teams, and one of more than 400 words
-    "workspace_many": dict(lengths=[150] * 16 + [402], sd=1.0),
+    "teams_beside_tiles": dict(lengths=[460, 30, 141, 150, 140, 142, 12]),
+    # too many long sentences for teams, and one of more than 450 words
+    "workspace_many": dict(lengths=[150] * 16 + [460], sd=1.0),
     # scores of a trained model: one tree's spans far above the rest
     "planted": dict(lengths=[8, 25, 26, 50, 99, 130], sd=1.0, plant=9.0),
 }
