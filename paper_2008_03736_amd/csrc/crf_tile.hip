@@ -71,16 +71,24 @@ constexpr float NEG = -1.0e30f;
 // whose every tree holds a near-forbidden score); it is off by some 2^-142 (of
 // at most 2^8 terms, 2^-150 each), times 2^R by the rescales that follow, and
 // log Z and the marginals by that times the span's outside over Z (a lost
-// outside sum: times its inside).  So the bundle is redone when a sentence
-// has a low sum and its largest value or sum, times 2^R, exceeds
-// 2^kHarmLog2 Z: 2^-42 a span, which leaves some 2^20 for the number of spans
-// and for sums being looked at on a quarter of the spans only (the tiles'
-// diagonals).  Calls without the outside redo any bundle with a low sum.
+// outside sum: times its inside).  So where a sentence has a low sum and its
+// largest value or sum, times 2^R, exceeds 2^kHarmLog2 Z, its bundle's spans are
+// looked at one by one, and it is redone when that holds of the outside of a
+// span whose inside sum was below 2^-100 (or lost whole), or the other way
+// round, with 2^kSpanHarmLog2 and the rescales of that span: 2^-26 at most a
+// span, of which a few come near it.  (The stages look at a quarter of the
+// spans, the tiles' diagonals, hence the lower bound for the sentence.  The log
+// domain's own error is larger than what is let through: 24 sentences of 200
+// words at deviation 4, marginals 3.0e-6 off (2-norm) after a redo in 772 us,
+// 1.0e-6 without in 232.  64 of 256 words at deviation 3, a twentieth of the
+// spans near-forbidden: two batches in ten hold a sentence whose largest values
+// call for the look, which finds nothing: fused 1,615 us with a redo, 531 so.)
+// Calls without the outside redo any bundle with a low sum.
 constexpr uint32_t kLinLowBits = 0x0D800000u;   // 2^-100
 constexpr uint32_t kLinMaxBits = 0x71800000u;   // 2^100; infinities and NaN compare above it
 constexpr float kLinMin = 0x1p-100f, kLinMax = 0x1p+100f;
 constexpr uint32_t kLinTopBits = 0x4F800000u;   // 2^32: larger values and sums are noted
-constexpr float kLinTopLog2 = 32.f, kHarmLog2 = 100.f;
+constexpr float kLinTopLog2 = 32.f, kHarmLog2 = 100.f, kSpanHarmLog2 = 116.f;
 constexpr int kGoldMark = 0x7FBADBAD;           // a NaN bit pattern: no finite chart value has it
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -315,8 +323,9 @@ __device__ __forceinline__ Io_ctx<GLOB> io_ctx(const int32_t *rec, char *lds) {
 // (kTabTop: the bits of the largest value or sum noted; kTabR: log2 of what
 // rescales may have added to an early sum's error)
 enum { kTabD = 0, kTabDl, kTabG, kTabLz, kTabId, kTabN, kTabTop, kTabR, kTabWords };
-// a bundle's flags: out of range, a low sum, and early values far from 1
-enum { kFlagOut = 0, kFlagLow, kFlagWide, kFlags };
+// a bundle's flags: out of range, a low sum, early values far from 1, and low
+// sums that may matter
+enum { kFlagOut = 0, kFlagLow, kFlagWide, kFlagHarm, kFlags };
 template <typename T, typename CX>
 __device__ __forceinline__ T &tab(const CX &c, int which, int sb) {
     return *reinterpret_cast<T *>(c.tb + c.tab + 4 * (which * c.S + sb));
@@ -1011,6 +1020,12 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
     }
     __syncthreads();
     tile_seed(cx, sm);
+    // What the q-th rescale moved a sentence's shift by (in place of the forced
+    // sums' partials; a rescale needs 5 blocks, and there are 4 at most).
+    auto rescale_of = [&](int q, int sb) -> float & {
+        return *reinterpret_cast<float *>(cx.tb + cx.partd + 8 * (q * S + sb));
+    };
+    int rescales = 0;
 
     // The stages.
     const int nw = NT >> 6, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1034,7 +1049,12 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
         __syncthreads();
         if (t == tr) {
             // (the flag is uniform: no later stage writes it)
-            if (!LIN || m >= kWideBlocks || flags[kFlagWide] != 0) tile_rescale<LIN, REV>(cx, sm, t);
+            if (!LIN || m >= kWideBlocks || flags[kFlagWide] != 0) {
+                tile_rescale<LIN, REV>(cx, sm, t);
+                if constexpr (LIN && REV)
+                    for (int sb = tid; sb < S; sb += NT) rescale_of(rescales, sb) = tab<float>(cx, kTabDl, sb);
+            }
+            ++rescales;
             tr = tile_rescale_after<LIN>(t + 1, m);
         }
     }
@@ -1055,15 +1075,56 @@ __device__ __forceinline__ bool tile_inside_impl(const KernelPlan &p, const int3
             bool bad = !(r >= kLinMin) || !(r <= kLinMax);
             if (flags[kFlagLow] != 0) {
                 const float top = __builtin_fmaxf(kLinTopLog2, fast_log2(tab<float>(cx, kTabTop, sb)));
-                bad = bad || !REV || top + tab<float>(cx, kTabR, sb) > lz + kHarmLog2;
+                if constexpr (!REV) bad = true;
+                else if (top + tab<float>(cx, kTabR, sb) > lz + kHarmLog2) flags[kFlagHarm] = 1;
             }
             if (bad) flags[kFlagOut] = 1;
         }
         tab<float>(cx, kTabLz, sb) = LIN ? 1.0f / r : lz;
     }
     __syncthreads();
+    int redo = LIN ? flags[kFlagOut] : 0;
+    if constexpr (LIN && REV) {
+        const int harm = flags[kFlagHarm];
+        if (harm != 0 && redo == 0) {   // (uniform: both are written before the barrier)
+            __syncthreads();
+            const bool moved = m >= kWideBlocks || flags[kFlagWide] != 0;
+            for (int c0 = tid_e; c0 < rw.total; c0 += NT) {
+                const typename Row_walk::At a = rw.at(c0);
+                const int sb = a.sb, n = tab<int>(cx, kTabN, sb), i = 4 * a.I + a.r, j0 = 4 * a.J;
+                if (!a.ok || i >= n) continue;
+                const f4 s = load_row(scores + (size_t)tab<int>(cx, kTabId, sb) * sent_stride, N1, i, a.J, n);
+                const int rr = ((a.r + cx.rot(a.I * S + sb)) & 3) * cx.rs(a.J - a.I);
+                const f4 al = ld4(sm, cx.a(a.I, a.J, sb) + rr), ou = ld4(sm, cx.o(a.I, a.J, sb) + rr);
+                // The rescales since the tile was finished, per node: its sums
+                // have moved by that (w - 2 nodes inside a span's sum, n - w - 1
+                // outside), and so have their errors.
+                float di = 0.f, dout = 0.f;
+                int q = 0;
+                for (int t = tile_rescale_after<LIN>(1, m); t > 0; t = tile_rescale_after<LIN>(t + 1, m), ++q) {
+                    const float dl = moved ? rescale_of(q, sb) : 0.f;
+                    di += a.J - a.I <= t ? dl : 0.f;
+                    dout += a.J - a.I >= m - t ? dl : 0.f;
+                }
+                float x = NEG;   // log2 of the largest partner of a low sum, times how its error grew
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int j = j0 + c, w = j - i;
+                    const float e = __builtin_fmaf(s[c], LOG2E_F, tab<float>(cx, kTabD, sb));
+                    const float la = fast_log2(al[c]), lo = fast_log2(ou[c]);
+                    const float gi = di * (float)(w - 2), go = dout * (float)(n - w - 1);
+                    float y = la - e - gi < -100.f ? lo + gi : NEG;
+                    y = lo - e - go < -100.f ? __builtin_fmaxf(y, la + go) : y;
+                    x = w > 1 && j <= n && !(i == 0 && j == n) ? __builtin_fmaxf(x, y) : x;
+                }
+                if (x + fast_log2(tab<float>(cx, kTabLz, sb)) > kSpanHarmLog2) flags[kFlagOut] = 1;
+            }
+            __syncthreads();
+            redo = flags[kFlagOut];
+        }
+    }
     if constexpr (LIN)
-        if (flags[kFlagOut] != 0) return false;
+        if (redo != 0) return false;
     auto log_z = [&](int sb) {
         const int n = tab<int>(cx, kTabN, sb);
         const float r = root_of(sb);

@@ -203,3 +203,22 @@ def test_marginals_of_short_sentences_keep_float32s_digits(length):
     valid = W.valid_mask(b.lengths, b.n1)
     err = (mu.cpu().numpy() - mu_ref)[valid]
     assert np.linalg.norm(err) <= 1.5e-7 * np.linalg.norm(mu_ref[valid])
+
+
+@pytest.mark.parametrize("length,count,sd,forbid,seed,tol", [(200, 24, 4.0, 0.0, 1, 1.5e-6), (300, 8, 3.0, 0.05, 4, 1.7e-6)])
+def test_low_sums_that_do_not_matter_stay_linear(length, count, sd, forbid, seed, tol):
+    # sums below 2^-100 beside values far above 1, but not of the same span:
+    # no redo in the log domain, whose rounding would show (2-norm of the
+    # marginals' error 1.0e-6 and 1.4e-6 of their own; 3.0e-6 and 2.2e-6 after
+    # one)
+    import torch
+
+    b = W.custom([length] * count, seed=seed, sd=sd, forbid=forbid)
+    s = torch.from_numpy(b.scores).to("cuda:0")
+    _, mu_ref = orc.marginals(b.scores, b.lengths, threads=16)
+    with B.Plan(b.lengths, n1=b.n1, device=s.device) as plan:
+        _, mu = plan.inside_fwd_bwd(s)
+        torch.cuda.synchronize()
+    valid = W.valid_mask(b.lengths, b.n1)
+    err = (mu.cpu().numpy() - mu_ref)[valid]
+    assert np.linalg.norm(err) <= tol * np.linalg.norm(mu_ref[valid])
