@@ -659,6 +659,8 @@ int crf_plan_create(crf_plan **out, const int32_t *lengths_host, int32_t batch, 
             // (of 512 slots), which LDS caps first on large batches: the
             // 5,000-sentence mixed batch fused 85.0 us at one share per slot,
             // 72.6 here, 72.9 at half or a fifth of the slots, 123 at twice.
+            // (205 and 256 measure the same.)  The work and duration models are
+            // rough, not fits: they set proportions and the launch order only.
             const int slots = small ? 205 : 102;
             tio = make_tile_schedule(tile_order, lengths_host, budget, slots, kp.tile_threads, io_bytes,
                                      [](int m, int S) { return (m + 1) * (1.0 + 0.004 * m * S); });

@@ -39,9 +39,10 @@
 // What bounds it: latency, in a stage's chain of address arithmetic, one LDS
 // round trip, the products (a wavefront issues an independent vector
 // instruction every 5 to 6 cycles, a dependent one every 9), the lanes'
-// combining, the finish and the barrier: about 3,000 cycles a stage where a
-// width step took 2,000, for four widths; not LDS (conflict-free but for the
-// shared tiles' lanes) and not HBM.  Measured against the one-width-a-step
+// combining, the finish and the barrier: about 4,800 cycles a stage (26 stages of
+// one 99-word sentence with marginals in 57 us, launch and ends included) where a
+// width step took 2,000, for four widths; LDS adds 3.4 conflict cycles to an
+// instruction (the lanes that share a tile), a seventh of the busy cycles; not HBM.  Measured against the one-width-a-step
 // kernels (us): 5,000 mixed sentences fused 96.5 -> 70.8, 2,000 longer ones
 // 130.5 -> 112.9, MBR of 1,700 134.5 -> 114.0, gold loss of 200 39.4 -> 33.6,
 // 32 short ones fused 26.7 -> 23.0, CKY of one sentence of 23 words 14.8 ->
